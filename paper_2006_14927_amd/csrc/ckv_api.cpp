@@ -365,6 +365,10 @@ static int array_create(const double* x_m, const double* y_m, const double* r_m,
     arr->x.assign(x_m, x_m + n_tel);
     arr->y.assign(y_m, y_m + n_tel);
     arr->r.assign(r_m, r_m + n_tel);
+    for (int32_t k = 0; k < n_tel; ++k) {
+        arr->rmax = std::max(arr->rmax, r_m[k]);
+        arr->dmax = std::max(arr->dmax, std::hypot(x_m[k], y_m[k]));
+    }
     arr->soft_sigma = sigma;
     int rc = build_array_grid(arr, arr->r, &arr->hit);
     std::vector<double> tel_screen;
@@ -504,9 +508,7 @@ int run_checked(const ckv_segments* segs, const ckv_showers* showers, const ckv_
     int n_cu = 256;
     if (int rc = device_cu_count(&n_cu)) return rc;
     plan.emit_grid = params->grid > 0 ? params->grid : std::min(n_cu, kMaxEmitGrid);
-    // default: 16 waves for the mixed kernel, 8 for FP64 (16 is its narrow build)
-    plan.emit_waves = params->waves_per_group > 0 ? params->waves_per_group
-                      : params->precision == CKV_FP64 ? kMaxEmitWaves / 2 : kMaxEmitWaves;
+    plan.emit_waves = params->waves_per_group > 0 ? params->waves_per_group : kMaxEmitWaves;
     return launch_run(plan);
 }
 

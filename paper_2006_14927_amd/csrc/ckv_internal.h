@@ -56,17 +56,14 @@ constexpr int kRunTelShift = 40;
 constexpr int64_t kRunValueMask = ((int64_t)1 << kRunTelShift) - 1;
 
 // Control block in the workspace (zeroed by the first kernel of a run).  The
-// counters every wave claims from (tiles, staging blocks, run blocks, screening
-// tiles) sit on cache lines of their own: same-line atomics from all waves would
+// counters every wave claims from (tiles, staging blocks, run blocks) sit on cache lines of their own: same-line atomics from all waves would
 // serialise in one L2 channel.
+constexpr int kTileClasses = 16;
 enum CtrlSlot {
-    kTileCounter = 0,   // next tile to claim (the mixed bunch kernel: tiles claimed past
-                        // each wave's first, the next being the grid's wave count plus this)
+    kTileCounter = 0,   // next tile to claim (the soft tile kernels)
     kBlockCounter = 32, // next staging block to claim
     kRunCounter = 64,   // next run block to claim
-    kScreenCounter = 96,  // as kTileCounter, for the soft response's screening pass (the
-                          // FP64 tile forward that may follow claims from kTileCounter)
-    kNumTiles = 128,    // tiles of this run
+    kNumTiles = 96,    // tiles of this run
     kNumRowBlocks,      // row blocks of the per-telescope scan
     kHits,              // crossings found
     kBunches,           // bunches generated
@@ -77,7 +74,10 @@ enum CtrlSlot {
     kCutBlocks,         // row blocks holding them
     kRecords,           // their crossings
     kDrop0,             // CKV_N_DROP drop counters follow
-    kCtrlSlots = kDrop0 + CKV_N_DROP + 4
+    // the bunch kernel's claim counters, kTileClasses of them on lines of their own: tiles
+    // claimed past each wave's first
+    kClaimCounter = 128,
+    kCtrlSlots = kClaimCounter + 32 * kTileClasses
 };
 
 }  // namespace ckv
@@ -91,6 +91,7 @@ struct ckv_atmo {
     std::vector<double> P;           // host, 5 x n_nodes
     double psi_min = 0, psi_max = 0; // range of psi over the nodes
     bool psi_falls = false;          // psi non-increasing with altitude at every node
+    double psi_slope = 0;            // largest |dpsi/dh| of a cell
     double* d_node64 = nullptr;      // device, n_nodes x kNode64
     float* d_cell32 = nullptr;       // device, (n_nodes - 1) x kCell32
     std::vector<double> depth;       // host, n_nodes, vertical depth [g/cm^2]; empty: none
@@ -121,6 +122,7 @@ struct ckv_array {
     int device = 0;
     int32_t n_tel = 0;
     std::vector<double> x, y, r;
+    double rmax = 0, dmax = 0;       // largest radius, largest distance of a centre from the origin
     double* d_tel = nullptr;         // device, n_tel x 4: X, Y, R, R^2
     ckv_grid hit;                    // radii R (sphere crossings)
     ckv_grid soft;                   // radii sqrt(R^2 + 2 R sigma z_cut) + margin (soft response)
@@ -139,7 +141,7 @@ int build_atmo_tables(const double* alt, const double* eta, int64_t n, double h_
                       ckv_atmo* a);
 // tables on the input's own altitudes above h_obs (node tables)
 int build_node_tables(const double* alt, const double* eta, int64_t n, double h_obs, ckv_atmo* a);
-// psi_min, psi_max and psi_falls of a's node values
+// psi_min, psi_max, psi_falls and psi_slope of a's node values
 void psi_range(ckv_atmo* a);
 // depth at the nodes of a (after build_atmo_tables), the same interpolation as eta
 void build_depth_table(const double* alt, const double* depth, int64_t n, ckv_atmo* a);
@@ -212,7 +214,7 @@ int launch_count(const ckv_segments* segs, const ckv_params* p, const ckv_atmo* 
                  int64_t* n_b, hipStream_t stream);
 // waves per bunch-kernel workgroup (at most max_waves) and its LDS bytes
 int emit_config(int precision, int n_tel, int prof_bins, const ckv_atmo* atmo, int tile_segs,
-                int max_waves, int* waves, size_t* lds_bytes, bool narrow_ok);
+                int max_waves, int* waves, size_t* lds_bytes, bool many_nodes_ok);
 
 struct SoftPlan {
     const int64_t* n_b_frozen;

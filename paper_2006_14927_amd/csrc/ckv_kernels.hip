@@ -5,13 +5,15 @@
 //               (a tile = up to tile_segs consecutive steps of one shower);
 //   emit      - persistent: each wavefront claims tiles; per tile it computes
 //               the step setups (FP64, one step per lane: photon yield, bunch
-//               count, Cherenkov angle, frame), scans the bunch counts across
-//               the wave, then walks the tile's bunches 64 at a time (one per
-//               lane): Philox draws, sub-step emission point, direction on the
-//               cone, LDS-staged atmosphere tables, refraction series, ground
-//               point, candidate spheres, and records every crossing in a
-//               staging area together with its rank among the tile's crossings
-//               of the same telescope;
+//               count, Cherenkov angle, frame) and the azimuths at which each
+//               step's light can reach a sphere; a first pass over the bunches of
+//               the steps that can (one per lane) takes the azimuth's draw only
+//               and queues the bunches in those azimuths; the queue's bunches,
+//               64 at a time, get their draws, sub-step emission point, direction
+//               on the cone, table lookup, refraction series, ground point and
+//               candidate spheres, and every crossing is recorded in a staging
+//               area together with its rank among the tile's crossings of the
+//               same telescope;
 //   finalize  - per-telescope prefix sums over tiles, CSR offsets per
 //               (shower, telescope), and a scatter of the staged records to
 //               their final slots (ascending step, then bunch).
@@ -49,7 +51,6 @@ struct Args {
     double h_obs, step, inv_step, h_top, n_obs;
     const double* node64;
     const float* cell32;
-    int32_t lds_entries;        // table entries staged in LDS (the rest read from HBM)
     // node tables (binary-search lookups): n_nodes altitudes then n_nodes-1 inverse
     // widths; NULL for the uniform grid
     const double* hnodes;
@@ -107,11 +108,16 @@ struct Args {
     uint64_t* list_ids;
     int64_t list_cap;
     int64_t* list_count;
-    // the screening pass's per-step cull (cull_rmax = 0: off): the largest screening
+    // the soft tile kernels' per-step cull (cull_rmax = 0: off): the largest screening
     // radius; x0 = (psi_max - psi_min) / (1 + psi_min); b0 = x0 times the bound of
     // |1 - T4(x)| / |x| (1/2 for psi non-increasing with altitude, 4/5 otherwise); a
     // bound of (n_e / n_obs)^2
     double cull_rmax, cull_x0, cull_b0, cull_rho2;
+    // the bunch kernel's azimuth sectors (light_cone; sec_rmax = 0: off): the largest
+    // sphere radius and the largest distance of a centre from the origin; psi's largest
+    // slope with altitude (0 where psi is not non-increasing), largest and smallest value
+    double sec_rmax, sec_dmax, sec_slope, sec_psi_max, sec_psi_min;
+    int32_t sec_falls;          // psi non-increasing with altitude at every node
 };
 
 // Memory accesses whose address space is explicit.  Where one access may go to LDS
@@ -274,6 +280,7 @@ struct Setup {
     double photons, cos_t, sin_t, ds, inv_bc;
     double b1x, b1y, b1z, b2x, b2y, b2z;
     double x0, y0, h0, t0, u, v, w;   // the step's inputs as loaded (for its record)
+    double len, psi;                  // its length; psi at its midpoint
 };
 
 __device__ __forceinline__ double psi_fp64(const Args& a, double h)
@@ -325,6 +332,7 @@ __device__ __forceinline__ void step_setup(const Args& a, int64_t i, Setup& st)
     const double L = a.len[i], t0 = a.t0[i], E = a.energy[i];
     const double m = a.ptype[i] == CKV_MUON ? kMassMuon : kMassElectron;
     st.x0 = x0; st.y0 = y0; st.h0 = h0; st.t0 = t0; st.u = u; st.v = v; st.w = w;
+    st.len = L;
     // (E c with c = m / 1 GeV in (0, 1) is finite exactly when E is; testing it, with
     // every test evaluated (no short circuit), puts all the step's loads in one round)
     const int n_finite = (int)isfinite(x0) + (int)isfinite(y0) + (int)isfinite(h0) + (int)isfinite(u) +
@@ -343,6 +351,7 @@ __device__ __forceinline__ void step_setup(const Args& a, int64_t i, Setup& st)
         h_mid = h0 - (0.5 * L) * w;
     }
     const double psi = psi_fp64(a, h_mid);
+    st.psi = psi;
     const double n2 = 1.0 + psi;
     const double num = psi - n2 * r2;                  // beta^2 n^2 - 1
     if (!(num > 0.0)) { st.status = CKV_DROP_THRESHOLD; return; }
@@ -431,12 +440,6 @@ __device__ __forceinline__ double rcp64(double x)
     return fma(r, fma(-x, r, 1.0), r);
 }
 
-// --------------------------------------------------------------------------
-// LDS layout of the bunch kernel
-//   [atmosphere table][wave 0 area][wave 1 area]...
-// wave area: TS step entries (the emitting steps of the current tile,
-// compacted), a 64-entry flag row used to map bunches to steps, the per-
-// telescope crossing counters of the tile, and the wave's run counters.
 // --------------------------------------------------------------------------
 // Exact propagation of a grazing bunch (0 < w <= w_min), cell by cell in FP64
 // from the FP64 node table, where the moment series is not used (sec. 4.3.1 and
@@ -627,10 +630,8 @@ struct alignas(16) StepEntry<1> {
     double x0, y0, h0, t0, u, v, w, cos_t, ds, inv_bc;
     double photons;  // FP64: the longitudinal profile sums it
     float sb1x, sb1y, sb1z, sb2x, sb2y, sb2z;
-    int32_t boff;   // first bunch of the step inside the tile
     int32_t sidx;   // index of the step inside the tile
     uint32_t ctr1;  // counter word 1 of the step's random numbers
-    int32_t pad;
 };
 static_assert(sizeof(StepEntry<1>) == 128, "step entry size");
 
@@ -638,7 +639,6 @@ template <>
 struct alignas(16) StepEntry<0> {
     double x0, y0, h0, t0, u, v, w, cos_t, ds, inv_bc;
     double sb1x, sb1y, sb1z, sb2x, sb2y, sb2z, photons;
-    int32_t boff;
     int32_t sidx;
 };
 static_assert(sizeof(StepEntry<0>) == 144, "step entry size");
@@ -646,27 +646,43 @@ static_assert(sizeof(StepEntry<0>) == 144, "step entry size");
 // per-wave counters kept in LDS (wave-uniform increments by lane 0)
 enum WaveCounter { kWcBunches = 0, kWcEmitting, kWcHits, kWcDrop0, kWcCount = kWcDrop0 + CKV_N_DROP };
 
-// Without the profile the whole table is staged in LDS.  With it, only the
-// lowest kLdsTableEntries entries (nodes for FP64, cells for mixed, i.e. up to
-// 76.8 km above the observation level on a 50 m grid) are, to leave room for
-// the per-wave histograms; lookups above them read the same entries from HBM.
-constexpr int kLdsTableEntries = 1536;
+// Azimuth sectors of a step's light cone: the bunches of a step leave at azimuths
+// uniform in [0, 1) turns (the top bits of their second draw); one bit per sector says
+// whether its light may reach a sphere.
+constexpr int kSectorBits = 8;
+constexpr int kSectors = 1 << kSectorBits;
+constexpr int kSectorWords = kSectors / 32;
 
-__host__ __device__ inline int lds_entries(int prec, int n_nodes, bool prof)
-{
-    const int n = prec == 0 ? n_nodes : n_nodes - 1;
-    return prof && n > kLdsTableEntries ? kLdsTableEntries : n;
-}
+// Per step, what the bunch loop's first pass needs: first bunch in the pass, step in
+// the tile, and the product of the second Philox round that depends on the step only.
+struct alignas(16) StepPass {
+    int32_t boff;
+    int32_t sidx;
+    uint32_t hi0, lo0;
+};
 
-__host__ __device__ inline size_t table_bytes(int prec, int n_nodes, bool prof)
+// Bunches that the first pass let through, waiting for a full chunk of 64.
+constexpr int kQueue = 2 * kWave;
+constexpr int kPairs = 2 * kWave;      // (step, sphere) pairs of the tile setup, same room
+
+// The largest atmosphere table the library takes: as much as the bunch kernel's LDS
+// would hold beside one wave's area with the table staged there whole (with the profile
+// or the screening pass, its lowest 1536 entries), or, for FP64 runs that ask for 16
+// waves, those entries beside 16 waves' areas.
+constexpr int kTableLimitEntries = 1536;
+
+__host__ __device__ inline size_t table_bytes(int prec, int n_nodes, bool part)
 {
-    return (size_t)lds_entries(prec, n_nodes, prof) *
-           (prec == 0 ? kNode64 * sizeof(double) : kCell32 * sizeof(float));
+    int n = prec == 0 ? n_nodes : n_nodes - 1;
+    if (part && n > kTableLimitEntries) n = kTableLimitEntries;
+    return (size_t)n * (prec == 0 ? kNode64 * sizeof(double) : kCell32 * sizeof(float));
 }
 
 __host__ __device__ inline size_t wave_bytes(int prec, int tile_segs, int n_tel, int prof_bins)
 {
     size_t b = (size_t)tile_segs * (prec == 0 ? sizeof(StepEntry<0>) : sizeof(StepEntry<1>));
+    b += (size_t)tile_segs * (kSectorWords * sizeof(uint32_t) + sizeof(StepPass));
+    b += (size_t)kQueue * (sizeof(uint32_t) + sizeof(uint8_t));  // queue (tile setup: pairs)
     b += kWave * sizeof(int32_t);                       // flag row
     if (prec == 0) b += (size_t)tile_segs * sizeof(uint32_t);   // counter words (FP64 path)
     b += (size_t)kWcCount * sizeof(int64_t);            // counters
@@ -675,73 +691,19 @@ __host__ __device__ inline size_t wave_bytes(int prec, int tile_segs, int n_tel,
     return (b + 15) & ~(size_t)15;
 }
 
+// one wave's area beside the table in the limit above
+constexpr size_t kLimitScreenBytes = 70 * sizeof(int64_t);
+
+__host__ __device__ inline size_t limit_wave_bytes(int prec, int tile_segs, int n_tel, int prof_bins)
+{
+    size_t b = (size_t)tile_segs * (prec == 0 ? 148 : 128) + 256 + (size_t)kWcCount * sizeof(int64_t);
+    b += ((size_t)n_tel * sizeof(int32_t) + 15) & ~(size_t)15;
+    b += (size_t)prof_bins * (sizeof(double) + sizeof(uint32_t));
+    return (b + 15) & ~(size_t)15;
+}
+
 constexpr int kSoftIdBits = 24;                          // bunch index bits of a list id
 constexpr unsigned long long kSoftListInvalid = 1ull << 62;   // or-ed into the count
-
-// Screening pass: the candidate bunches of ballot words bits[0..nw-1] (bit b of
-// word q: bunch j0 + 64 q + b of the tile) go to the list.  One atomic claims exactly
-// their slots; lane q writes the ids of word q, the step of its first bunch found
-// by binary search over the tile's stash (first-bunch offsets ascend) and the
-// later ones by moving forward from there (the lanes' searches overlap; this
-// measured faster than word-by-word writes with consecutive slots).  lst (its
-// offset in the dynamic LDS, as for bits and stash) holds
-// {tile's first step, ids, capacity, count, tile's emitting steps}.  Called by
-// the whole wave.
-template <typename E>
-__device__ __noinline__ void soft_list_flush(uint32_t lst_at, uint32_t bits_at, uint32_t stash_at, int64_t j0,
-                                             int nw, int lane)
-{
-    // the wave's areas, by their offsets in the dynamic LDS (LDS accesses, not
-    // generic ones)
-    extern __shared__ __align__(16) unsigned char lds[];
-    const int64_t* lst = reinterpret_cast<const int64_t*>(lds + lst_at);
-    const uint64_t* bits = reinterpret_cast<const uint64_t*>(lds + bits_at);
-    const E* stash = reinterpret_cast<const E*>(lds + stash_at);
-    // (the caller's lane 0 wrote lst before the call; the wave's LDS accesses are in order)
-    const int64_t l_g0 = lst[0], l_ids = lst[1], l_cap = lst[2], l_count = lst[3], l_emit = lst[4];
-    uint64_t word = lane < nw ? bits[lane] : 0ull;
-    const int c = __popcll(word);
-    const int64_t incl = wave_incl_scan((int64_t)c);
-    const int64_t tot = wave_last(incl);
-    if (tot == 0) return;
-    using GU64 = __attribute__((address_space(1))) unsigned long long;
-    unsigned long long* count = (unsigned long long*)reinterpret_cast<GU64*>(l_count);
-    unsigned long long base = 0;
-    if (lane == 0) base = atomicAdd(count, (unsigned long long)tot);
-    base = __shfl(base, 0);
-    const int64_t g0 = l_g0, cap = l_cap;
-    uint64_t* ids = (uint64_t*)reinterpret_cast<GU64*>(l_ids);
-    int64_t slot = (int64_t)base + (incl - c);
-    if (!word) return;
-    const int n_emit = (int)l_emit;
-    const int32_t jw = (int32_t)(j0 + kWave * lane);     // bunch of bit 0
-    int32_t jj = jw + __builtin_ctzll(word);
-    int lo = 0, hi = n_emit;
-    while (hi - lo > 1) {
-        const int mid = (lo + hi) >> 1;
-        if (stash[mid].boff <= jj) lo = mid; else hi = mid;
-    }
-    int32_t boff = stash[lo].boff;
-    int32_t next = lo + 1 < n_emit ? stash[lo + 1].boff : INT_MAX;
-    uint64_t step = (uint64_t)(g0 + stash[lo].sidx);
-    for (;;) {
-        while (jj >= next) {
-            ++lo;
-            boff = next;
-            next = lo + 1 < n_emit ? stash[lo + 1].boff : INT_MAX;
-            step = (uint64_t)(g0 + stash[lo].sidx);
-        }
-        const int32_t k = jj - boff;
-        if ((uint32_t)k >= (1u << kSoftIdBits) || step >= (1ull << (64 - kSoftIdBits)))
-            atomicOr(count, kSoftListInvalid);
-        else if (slot < cap)
-            ids[slot] = (step << kSoftIdBits) | (uint64_t)(uint32_t)k;
-        ++slot;
-        word &= word - 1;
-        if (!word) break;
-        jj = jw + __builtin_ctzll(word);
-    }
-}
 
 // --------------------------------------------------------------------------
 // the bunch kernel
@@ -753,51 +715,32 @@ constexpr int kFeatProfile = 1;
 constexpr int kFeatExact = 2;
 constexpr int kFeatSearch = 4;   // node tables: binary search per bunch (alone, 32-step tiles)
 constexpr int kFeatCurved = 8;   // spherical shells, every bunch traced exactly (alone, 32-step tiles)
-constexpr int kFeatWide = 16;    // mixed kernel built for <= 8 waves per workgroup (twice the registers)
 // soft-response screening (mixed, alone, 32-step tiles): bunch counts frozen, each
 // bunch tested against spheres of the soft cut radius plus a margin, the candidates'
 // ids listed; no records
 constexpr int kFeatScreen = 32;
-// FP64 kernel built for 16 waves per workgroup (128 registers, four waves per SIMD):
-// only the lowest kLdsTableEntries nodes of the table fit the LDS beside 16 wave
-// areas, the rare lookups above them read HBM (alone, no other feature)
-constexpr int kFeatNarrow = 64;
-// per wave, after the regular area: list state {tile's first step, ids, capacity,
-// count, emitting steps, unused} and the ballot words of the candidate bunches
-constexpr int kScreenWords = 64;
-constexpr size_t kScreenWaveBytes = (6 + kScreenWords) * sizeof(int64_t);
 
 __host__ __device__ inline size_t search_bytes(int n_nodes)
 {
     return ((size_t)(2 * n_nodes - 1) * sizeof(double) + 15) & ~(size_t)15;
 }
 
-// LDS layout of the bunch kernel: the atmosphere table (whole or in part), the node
-// altitudes of the search variant, then the sphere table {X, Y, R^2}
-template <int PREC, int FEAT>
-__device__ __forceinline__ size_t tel_lds_offset(const Args& a)
-{
-    constexpr bool PARTIAL = (FEAT & (kFeatProfile | kFeatScreen | kFeatNarrow)) != 0;
-    constexpr bool SEARCH = (FEAT & kFeatSearch) != 0;
-    return ((table_bytes(PREC, a.n_nodes, PARTIAL) + 15) & ~(size_t)15) + (SEARCH ? search_bytes(a.n_nodes) : 0);
-}
-
+// LDS layout of the bunch kernel: the node altitudes of the search variant, the sphere
+// table {X, Y, R^2}, then the waves.  The atmosphere table stays in global memory: only
+// the bunches that can reach a sphere look it up (1-3 % of them; their cells, 11 KB
+// between 2 and 20 km on a 50 m grid, stay in the vector cache).
 // sphere table in LDS: {X, Y, R^2} per sphere (at most CKV_MAX_TEL: 24 KB)
 __host__ __device__ inline size_t tel_bytes(int n_tel)
 {
     return ((size_t)n_tel * 3 * sizeof(double) + 15) & ~(size_t)15;
 }
 
-// Workgroup size the variant is compiled for: the FP64 kernel and the exact-path
-// variants (grazing, curved) carry FP64 tracing state and get the registers of
-// 8 waves; the mixed kernel is built for 16 waves (128 registers, the most
-// waves per SIMD) and, as the wide variant, for up to 8 (256 registers: no
-// spills, faster where step setup weighs more than bunches, e.g. at large
-// zenith angles); the launch's wave count picks the build.
+// Workgroup size the variant is compiled for: the exact-path variants (grazing,
+// curved) carry FP64 tracing state and get the registers of 8 waves; the others are
+// built for 16 waves (128 registers, four waves per SIMD).
 constexpr int emit_threads(int prec, int feat)
 {
-    return (feat & kFeatNarrow) ? 1024
-           : (prec == 0 || (feat & (kFeatExact | kFeatCurved | kFeatWide)) != 0) ? 512 : 1024;
+    return (feat & (kFeatExact | kFeatCurved)) != 0 ? 512 : 1024;
 }
 
 // Screening cull (soft response, plane-parallel atmosphere, FP64 pass as computed by
@@ -883,35 +826,217 @@ __device__ __forceinline__ bool annulus_holds_centre(const double* tel, int n_te
     return (((rm >> src) | (rm >> (src + kWave / 2))) & 1ull) != 0;
 }
 
-// Step setups of a tile, one per lane (emitting steps compacted into the stash),
-// the bunch-count scan and the step-level counters; returns the tile's bunch
-// count and this lane's step state.  Not inlined: the step arrays' pointers and
-// the setup's registers then take no room in the bunch loop.  Called by the
-// whole wave.
+// A wave's area in the bunch kernel's LDS.
+template <int PREC, int TS>
+struct WaveArea {
+    StepEntry<PREC>* stash;    // steps of the tile with bunches in the pass, compacted
+    uint32_t* masks;           // kSectorWords per step of the tile
+    StepPass* pass;            // compacted like the stash
+    uint32_t* qk;              // waiting bunches: bunch in its step ...
+    uint8_t* qs;               // ... and stash entry; tile setup: (sphere << 8) | step pairs
+    int32_t* flags;
+    uint32_t* sctr;            // FP64 path: counter word per step of the tile
+    int64_t* wcnt;
+    int32_t* tcount;
+    double* hph;               // profile of the current tile: photons (FP64) and bunches
+    uint32_t* hbu;
+    __device__ __forceinline__ WaveArea(unsigned char* at, int n_tel, int prof_bins)
+    {
+        auto take = [&](size_t b) { unsigned char* q = at; at += b; return q; };
+        stash = reinterpret_cast<StepEntry<PREC>*>(take(TS * sizeof(StepEntry<PREC>)));
+        masks = reinterpret_cast<uint32_t*>(take(TS * kSectorWords * sizeof(uint32_t)));
+        pass = reinterpret_cast<StepPass*>(take(TS * sizeof(StepPass)));
+        qk = reinterpret_cast<uint32_t*>(take(kQueue * sizeof(uint32_t)));
+        qs = take(kQueue);
+        flags = reinterpret_cast<int32_t*>(take(kWave * sizeof(int32_t)));
+        sctr = reinterpret_cast<uint32_t*>(take(PREC == 0 ? TS * sizeof(uint32_t) : 0));
+        wcnt = reinterpret_cast<int64_t*>(take(kWcCount * sizeof(int64_t)));
+        tcount = reinterpret_cast<int32_t*>(take(((size_t)n_tel * sizeof(int32_t) + 15) & ~(size_t)15));
+        hph = reinterpret_cast<double*>(take(prof_bins * sizeof(double)));
+        hbu = reinterpret_cast<uint32_t*>(at);
+    }
+};
+static_assert(kPairs * sizeof(uint32_t) <= kQueue * sizeof(uint32_t), "pairs share the queue's room");
+
+// --------------------------------------------------------------------------
+// Which bunches of a step can reach a sphere, from their azimuth alone.
+//
+// The bunches of a step leave from E(s) = P0 + s a, s in [0, L], in directions
+// p = cos_t a + sin_t (cos(phi) b1 + sin(phi) b2).  All of E(s) lie on one line, so a
+// point y of a bunch's straight emission line, tau > 0 ahead of E(s), has
+//   (y - P0) . a = s + tau cos_t,   (y - P0) normal to a = tau sin_t (cos(phi), sin(phi)):
+// its azimuth about the axis is phi wherever on the step the bunch was emitted, and its
+// distance from the axis obeys  n(y) - t (y - P0) . a = -t s  with t = tan(theta_c).
+// A bunch crosses a sphere (centre c, radius R) only if its observed line has a point
+// y' within R of c.  light_cone gives `base`, a bound of the distance from y' to the
+// straight emission line of a shifted centre c' (the shift px - x0, py - y0 is applied to
+// P0 instead), so some y lies within rho = R + base of c' and
+//   - n(c') - t A in [-t L - rho / cos_t, rho / cos_t], A = (c' - P0) . a  (n(y) - t (y .
+//     a) changes by at most 1 / cos_t per metre), and
+//   - |phi - azimuth of c'| <= asin(rho / n(c')), any phi when rho >= n(c').
+// A step's azimuths that no sphere's window covers hold no crossing.
+//
+// Plane-parallel: the path's ground point is g = E_h + T(p) S, T(p) = p_h / w_p, S = dh
+// (1 - beta) with beta in [0, B] for psi non-increasing with altitude, else in [-B, B]:
+// S = int T4(x) dh with T4 the four-term series of (1 + x)^(-1/2), x = q (psi - psi_e),
+// q = 1 / (n_e w_p)^2; for x in [0, 1/2] 0 <= 1 - T4(x) <= x / 2, for |x| <= 1/2
+// |1 - T4(x)| <= 4 |x| / 5; x <= (psi_obs - psi_e) / (n_e w_p)^2 with psi_e taken at the
+// step's start from the midpoint's and the table's largest slope.  The straight line's
+// ground point is g + beta T(p) dh; with beta0 = B / 2 the centre moves by beta0 T(a) dh0
+// and the rest is bounded by (B / 2) t_max dh0 + beta0 (|T(p) - T(a)| dh0 + |T(a)| w L),
+// |T(p) - T(a)| <= sin_t / (w_p w).  The observed direction is within |1 - n_e / n_obs|
+// (1 + 2 / w_p) of p, over at most R / w_o of the line.
+// Spherical shells: the ray bends by at most t_max (n_obs - n_e), t_max the largest
+// tangent of the local zenith angle along it (Bouguer: sin grows by r_e / r_obs at most),
+// so it leaves the straight line by at most that times the path length; the planar
+// array lies up to d^2 / (2 r_obs) above the observation sphere.
+// On the 20 degree TeV shower (100 spheres) 19 % of the bunches are in steps with some
+// window and 1.7 % lie in one (1.0 % cross), so 81 % of the bunches cost nothing and 98 %
+// no propagation: 3083 VALU instructions per 32-step tile against 9570 with every bunch
+// propagated; mixed kernel 1150 -> 550 us, FP64 2036 -> 580 us (2e6 steps); spherical
+// shells at 70 degrees, where a propagated bunch walks 250 cells, 3608 -> 360 us (1e5
+// steps).  A bitmask of 256 sectors (2.9 m of a 120 m ring) takes any number of windows at
+// one LDS read per bunch.
+// Margins: 5 cm, 1e-6 of the distance (FP32 window arithmetic) and the mixed path's
+// ground-point error, twice the screening pass's bound of it.
+//
+// false where the bound does not hold (direction not unit, flat rays, psi's range too
+// large) or where a bunch of the step might be dropped: the caller then takes every
+// bunch, so drops are counted bunch by bunch as ever.
+// --------------------------------------------------------------------------
+template <bool CURVED, bool SCREEN>
+__device__ __forceinline__ bool light_cone(const Args& a, const Setup& st, double& px, double& py, double& base)
+{
+    const double u = st.u, v = st.v, w = st.w, ct = st.cos_t;
+    const double dh0 = st.h0 - a.h_obs;
+    px = st.x0;
+    py = st.y0;
+    base = 0.0;
+    if (!(fabs(u * u + v * v + w * w - 1.0) <= 1e-9) || !(w >= 0.05)) return false;
+    const double s_hi = st.sin_t * (1.0 + 1e-9) + 1e-12;
+    const double sa = sqrt(fmax(0.0, (1.0 - w) * (1.0 + w)));
+    double wp = w * ct - sa * s_hi - 1e-12;          // lower bound of w_p
+    // (the FP64 pass behind the screen drops w_p <= w_min itself)
+    if (SCREEN) wp = fmax(wp, a.w_min);
+    if (!(wp >= 0.03) || (!SCREEN && !(wp > a.w_min + 1e-6))) return false;
+    // psi_obs - psi_e, with psi_e at the step's start, its highest point
+    const double x_psi = a.sec_falls ? fmax(a.sec_psi_max - st.psi + a.sec_slope * (0.5 * st.len), 0.0)
+                                     : a.sec_psi_max - a.sec_psi_min;
+    const double iw = rcp64(wp), iw2 = iw * iw;
+    double m = 0.05 + dh0 * (1e-6 * iw);
+    if (CURVED) {
+        if (!a.sec_falls) return false;
+        // local zenith angle at both ends: r cos(zeta) from the downward vertical
+        const double R = a.earth_r;
+        const double rz0 = R + st.h0;
+        const double r0 = sqrt(st.x0 * st.x0 + st.y0 * st.y0 + rz0 * rz0);
+        const double alt0 = curved_altitude(R, st.x0, st.y0, st.h0);
+        const double x1 = st.x0 + st.len * u, y1 = st.y0 + st.len * v, h1 = st.h0 - st.len * w;
+        const double alt1 = curved_altitude(R, x1, y1, h1);
+        const double c1 = (w * (R + h1) - u * x1 - v * y1) / (R + alt1);   // the smaller cosine
+        if (!(c1 > 0.03) || !(alt0 < a.h_top - 1.0)) return false;
+        const double c_lo = c1 * ct - sqrt(fmax(0.0, (1.0 - c1) * (1.0 + c1))) * s_hi - 1e-12;
+        if (!(c_lo > 0.03)) return false;
+        const double s_max = (r0 / a.r_obs) * sqrt((1.0 - c_lo) * (1.0 + c_lo)) * (1.0 + 1e-9);
+        if (!(s_max < 0.9995)) return false;
+        const double c_ray = sqrt((1.0 - s_max) * (1.0 + s_max));
+        const double bend = (s_max / c_ray) * (0.5 * x_psi) * (1.0 + 1e-6);
+        if (!(wp - bend >= 0.03)) return false;
+        const double reach = a.sec_rmax / (wp - bend);
+        const double d = a.sec_dmax + reach;
+        base = bend * (alt0 - a.h_obs) / c_ray + 0.51 * d * d / a.r_obs + reach * bend +
+               m + 1e-6 * (alt0 - a.h_obs) / c_ray;
+        if (!(alt1 - a.h_obs > a.sec_rmax + base + 1.0)) return false;
+    } else {
+        const double x0 = x_psi / (1.0 + a.sec_psi_min);
+        if (!(x0 * iw2 <= 0.5) || !(st.h0 < a.h_top - 1.0)) return false;
+        const double B = (a.sec_falls ? 0.5 : 0.8) * x0 * iw2;
+        const double t_max = sqrt((1.0 - wp) * (1.0 + wp)) * iw;
+        const double iwa = rcp64(w), beta0 = a.sec_falls ? 0.5 * B : 0.0;
+        double wo2 = wp * wp;
+        if (!a.sec_falls) {
+            wo2 = 1.0 - (1.0 + a.sec_psi_max) / (1.0 + a.sec_psi_min) * (1.0 - wp) * (1.0 + wp);
+            if (!(wo2 > 1e-3)) return false;
+        }
+        m += dh0 * ((1e-6 * st.sin_t + 2e-9) * (iw + iw2) + 4e-6 * a.sec_psi_max * iw * iw2);
+        base = (B - beta0) * t_max * dh0 + beta0 * (s_hi * iw * iwa * dh0 + sa * st.len) +
+               a.sec_rmax * rcp64(sqrt(wo2)) * (0.51 * x0 * (1.0 + 2.0 * iw)) + m;
+        px = st.x0 - beta0 * dh0 * (u * iwa);
+        py = st.y0 - beta0 * dh0 * (v * iwa);
+    }
+    return dh0 - st.len * w > a.sec_rmax + base + 1.0;
+}
+
+// What the windows need of a step (in its stash entry's room during the tile setup).
+struct alignas(16) ConeStep {
+    double px, py;
+    float b1x, b1y, b1z, b2x, b2y, b2z;
+    float u, v, w, dh0, t, ict, len, base;
+};
+static_assert(sizeof(ConeStep) <= sizeof(StepEntry<1>), "cone steps share the stash's room");
+
+// Sectors of step c's azimuths whose light may reach sphere (X, Y, R^2), or-ed into its
+// mask words.  FP32: its errors are inside light_cone's margin and the 2e-5 turns here.
+__device__ __forceinline__ void add_window(const ConeStep& c, double X, double Y, double R2, uint32_t* words)
+{
+    const float dx = (float)(X - c.px), dy = (float)(Y - c.py), dz = -c.dh0;
+    const float v1 = dx * c.b1x + dy * c.b1y + dz * c.b1z;
+    const float v2 = dx * c.b2x + dy * c.b2y + dz * c.b2z;
+    const float A = dx * c.u + dy * c.v - dz * c.w;
+    const float rho = __builtin_amdgcn_sqrtf((float)R2) * 1.00001f + c.base;
+    const float s2 = v1 * v1 + v2 * v2;
+    const float n = __builtin_amdgcn_sqrtf(s2);
+    const float rc = rho * c.ict + 1e-5f * n;
+    if (!(n <= c.t * A + rc) || !(n >= c.t * (A - c.len) - rc)) return;
+    const float q2 = rho * rho * __builtin_amdgcn_rcpf(s2);
+    int pos = 0, left = kSectors;
+    if (q2 < 0.64f) {
+        // asin(q) <= q / sqrt(1 - q^2)
+        const float half = __builtin_amdgcn_sqrtf(q2 * __builtin_amdgcn_rcpf(1.0f - q2)) * 0.15916f + 2e-5f;
+        const float mid = atan2f(v2, v1) * 0.15915494f;
+        const int lo = (int)floorf((mid - half) * (float)kSectors);
+        const int hi = (int)floorf((mid + half) * (float)kSectors);
+        pos = lo & (kSectors - 1);
+        left = min(hi - lo + 1, kSectors);
+    }
+    while (left > 0) {
+        const int bit = pos & 31, n_bits = min(32 - bit, left);
+        atomicOr(&words[pos >> 5], (0xFFFFFFFFu >> (32 - n_bits)) << bit);
+        pos = (pos + n_bits) & (kSectors - 1);
+        left -= n_bits;
+    }
+}
+
+// Step setups of a tile: the bunch counts, which steps' light can reach a sphere and at
+// which azimuths, the records of the steps that stay and the step-level counters.
+// Lane l sets up step l mod TS (the lanes past TS repeat it and share the search over
+// the spheres).  Called by the whole wave.
 struct TileSetup {
-    int64_t total;
-    int excl;
-    bool emits;
+    int32_t total;      // bunches in the pass
+    int32_t excl;       // first of this lane's step
+    bool in_pass;       // this lane's step has bunches in the pass
+    bool direct;        // every bunch in the pass is taken, whatever its azimuth
 };
 
 template <int PREC, int TS, int FEAT>
 __device__ __forceinline__ TileSetup tile_setup(const Args& a, int64_t g0, int nseg, int64_t seg_id0,
-                                                int lane, uint64_t lt_mask, StepEntry<PREC>* stash,
-                                                uint32_t* sctr, int64_t* wcnt, int64_t* lst)
+                                                uint32_t shower_id, int lane, uint64_t lt_mask,
+                                                const WaveArea<PREC, TS>& wa, const double* tel_sh)
 {
     constexpr bool SCREEN = (FEAT & kFeatScreen) != 0;
+    constexpr bool PROF = (FEAT & kFeatProfile) != 0;
+    constexpr bool CURVED = (FEAT & kFeatCurved) != 0;
     using T = typename std::conditional<PREC == 0, double, float>::type;
     using Entry = StepEntry<PREC>;
+    const int l = lane & (TS - 1);
+    const bool own = lane < TS;
     int64_t nb = 0;
     int status = -2;   // -2: no step in this lane
     Setup st;
-    double len = 0.0;
-    if (lane < nseg) {
-        // screening: the frozen count and the length loaded with the step's inputs,
-        // not after them
-        const int64_t f = SCREEN ? a.nb_frozen[g0 + lane] : 0;
-        if (SCREEN) len = a.len[g0 + lane];
-        step_setup(a, g0 + lane, st);
+    if (l < nseg) {
+        // screening: the frozen count loaded with the step's inputs, not after them
+        const int64_t f = SCREEN ? a.nb_frozen[g0 + l] : 0;
+        step_setup(a, g0 + l, st);
         status = st.status;
         if (st.status < 0) nb = st.nb;
         if (SCREEN && st.status < 0) {
@@ -919,75 +1044,130 @@ __device__ __forceinline__ TileSetup tile_setup(const Args& a, int64_t g0, int n
             // the current atmosphere decided above
             if (f > 0) {
                 nb = f;
-                st.ds = len / (double)f;
+                st.ds = st.len / (double)f;
             } else {
                 nb = 0;
                 status = -4;
             }
         }
     }
-    // the tile-size limit on the frozen counts, before the screening cull
-    const int64_t nb_all = nb;
-    if constexpr (SCREEN) {
-        static_assert(TS <= kWave / 2, "the cull splits the spheres between half-waves");
-        extern __shared__ __align__(16) unsigned char lds[];
-        const double* tel_sh = reinterpret_cast<const double*>(lds + tel_lds_offset<PREC, FEAT>(a));
-        // steps whose bunches can weight no sphere are not screened (screen_annulus)
-        double cgx = 0.0, cgy = 0.0, cmid = 0.0, chalf = -1.0;
-        int ok = 0;
-        if (lane < nseg && status == -1 && a.cull_rmax > 0.0)
-            ok = screen_annulus(a, st.x0, st.y0, st.h0, st.u, st.v, st.w, len, st.cos_t, st.sin_t, cgx, cgy,
-                                cmid, chalf) ? 1 : 0;
-        const bool reached = annulus_holds_centre<3>(tel_sh, a.n_tel, lane, ok, cgx, cgy, cmid, chalf);
-        if (ok && !reached) {
-            nb = 0;
-            status = -4;
-        }
-    }
-    int64_t incl = PREC == 1 ? wave_incl_scan_shfl(nb) : wave_incl_scan(nb);
-    int64_t total = scalar64(wave_last(incl));
-    const int64_t total_all =
-        SCREEN ? scalar64(wave_last(PREC == 1 ? wave_incl_scan_shfl(nb_all) : wave_incl_scan(nb_all))) : total;
+    const int64_t total_all = scalar64(wave_last(wave_incl_scan(own ? nb : 0)));
     if (total_all >= ((int64_t)1 << 30)) {
         // bunch offsets inside a tile are 32-bit: refuse such a tile
         if (lane == 0 && a.result) atomicOr(&a.result->error, 2);
-        total = 0;
-        incl = 0;
         nb = 0;
         status = status == -1 ? -3 : status;
     }
     const bool emits = status == -1;
-    const uint64_t emit_mask = __ballot(emits);
-    if (SCREEN && lane == 0) {
-        lst[0] = g0;
-        lst[4] = __popcll(emit_mask);
+    // ---- azimuth sectors: the pairs (step, sphere) that pass the cone test, then their
+    // windows, a pair per lane
+    bool cone = false, seen = true;
+    const bool live = emits && nb > 0;
+    if (a.sec_rmax > 0.0) {
+        double px = 0.0, py = 0.0, base = 0.0;
+        if (live) cone = light_cone<CURVED, SCREEN>(a, st, px, py, base);
+        if (__ballot(cone)) {
+            for (int q = lane; q < TS * kSectorWords; q += kWave) wa.masks[q] = 0u;
+            const double ict = cone ? rcp64(st.cos_t) : 0.0;
+            const double t = cone ? st.sin_t * ict : 0.0;
+            const double dh0 = cone ? st.h0 - a.h_obs : 0.0;
+            ConeStep* cs = reinterpret_cast<ConeStep*>(wa.stash);
+            if (cone && own) {
+                ConeStep& c = cs[l];
+                c.px = px; c.py = py;
+                c.b1x = (float)st.b1x; c.b1y = (float)st.b1y; c.b1z = (float)st.b1z;
+                c.b2x = (float)st.b2x; c.b2y = (float)st.b2y; c.b2z = (float)st.b2z;
+                c.u = (float)st.u; c.v = (float)st.v; c.w = (float)st.w;
+                c.dh0 = (float)dh0;
+                c.t = (float)t; c.ict = (float)ict; c.len = (float)st.len; c.base = (float)base * 1.00001f;
+            }
+            wave_lds_sync();
+            uint32_t* pairs = wa.qk;
+            const double du = cone ? st.u : 0.0, dv = cone ? st.v : 0.0;
+            const double rc = cone ? (a.sec_rmax + base) * ict : -1.0;
+            const double kA = cone ? dh0 * st.w : 0.0, kz = dh0 * dh0;
+            const double rl = cone ? -(t * st.len + rc) : 0.0;
+            constexpr int G = kWave / TS;
+            const int nh = (a.n_tel + G - 1) / G;
+            const int k_first = (lane / TS) * nh, k_last = a.n_tel - 1;
+            auto passes = [&](int k) {
+                const double dx = tel_sh[3 * k] - px, dy = tel_sh[3 * k + 1] - py;
+                const double A = fma(dx, du, fma(dy, dv, kA));
+                const double n2 = fma(-A, A, fma(dx, dx, fma(dy, dy, kz)));
+                const double hi = fma(t, A, rc), lo = fmax(fma(t, A, rl), 0.0);
+                return cone && fma(-hi, hi, n2) <= 0.0 && fma(-lo, lo, n2) >= 0.0;
+            };
+            int np = 0;
+            auto push = [&](bool p, int k) {
+                const uint64_t m = __ballot(p);
+                if (p) pairs[np + __popcll(m & lt_mask)] = ((uint32_t)k << 8) | (uint32_t)l;
+                np += __popcll(m);
+            };
+            auto windows = [&]() {
+                wave_lds_sync();
+                if (lane < np) {
+                    const uint32_t e = pairs[lane];
+                    const double* tq = tel_sh + 3 * (e >> 8);
+                    add_window(cs[e & 0xFFu], tq[0], tq[1], tq[2], wa.masks + kSectorWords * (e & 0xFFu));
+                }
+                wave_lds_sync();
+                if (np > kWave && lane < np - kWave) pairs[lane] = pairs[kWave + lane];
+                np = np > kWave ? np - kWave : 0;
+            };
+            for (int i = 0; i < nh; ++i) {
+                const int k = min(k_first + i, k_last);
+                const bool p = passes(k);
+                if (__ballot(p)) push(p, k);
+                if (np >= kWave || (i + 1 == nh && np > 0)) windows();
+            }
+            while (np > 0) windows();
+            wave_lds_sync();
+            if (cone) {
+                uint32_t any = 0;
+#pragma unroll
+                for (int q = 0; q < kSectorWords; ++q) any |= wa.masks[kSectorWords * l + q];
+                seen = any != 0u;
+            }
+            // (the reads above before the stash's writes below)
+            wave_lds_sync();
+        }
     }
-    const int excl = (int)(incl - nb);      // first bunch of this lane's step
-    if (emits) {
-        Entry& e = stash[__popcll(emit_mask & lt_mask)];
+    const bool direct = __ballot(live && cone && (PROF || seen)) == 0ull;
+    // steps the bunch loop's first pass walks: all that emit when the profile counts them
+    const bool in_pass = own && live && (PROF || seen);
+    if (in_pass && !cone && !direct) {
+        // no bound for this step: every azimuth
+#pragma unroll
+        for (int q = 0; q < kSectorWords; ++q) wa.masks[kSectorWords * l + q] = 0xFFFFFFFFu;
+    }
+    const int64_t nbp = in_pass ? nb : 0;
+    const int64_t incl = wave_incl_scan(nbp);
+    const int32_t total = __builtin_amdgcn_readfirstlane((int)wave_last(incl));
+    const int excl = (int)(incl - nbp);      // first bunch of this lane's step
+    const uint64_t pass_mask = __ballot(in_pass);
+    if (in_pass) {
+        const int at = __popcll(pass_mask & lt_mask);
+        Entry& e = wa.stash[at];
         const int64_t g = g0 + lane;
         const uint32_t ctr1 = a.step_id ? a.step_id[g] : (uint32_t)(seg_id0 + lane);
         if constexpr (PREC == 1) e.ctr1 = ctr1;
-        else sctr[lane] = ctr1;
-        if constexpr (PREC == 1 && (FEAT & kFeatProfile) == 0) {
-            // the called setup keeps the inputs it loaded rather than a second round
-            // (the profile build, short of registers, measured faster reloading)
-            e.x0 = st.x0;
-            e.y0 = st.y0;
-            e.h0 = st.h0;
-            e.t0 = st.t0;
-            e.u = st.u;
-            e.v = st.v;
-            e.w = st.w;
-        } else {
-            e.x0 = a.x0[g];
-            e.y0 = a.y0[g];
-            e.h0 = a.h0[g];
-            e.t0 = a.t0[g];
-            e.u = a.u[g];
-            e.v = a.v[g];
-            e.w = a.w[g];
-        }
+        else wa.sctr[lane] = ctr1;
+        // Philox: the first round's word 0 is the same for all bunches of the step, and
+        // with it the second round's product of that word
+        const uint32_t w0 = __umulhi(0xCD9E8D57u, shower_id) ^ ctr1 ^ a.key0;
+        StepPass sp;
+        sp.boff = excl;
+        sp.sidx = lane;
+        sp.hi0 = __umulhi(0xD2511F53u, w0);
+        sp.lo0 = 0xD2511F53u * w0;
+        wa.pass[at] = sp;
+        e.x0 = st.x0;
+        e.y0 = st.y0;
+        e.h0 = st.h0;
+        e.t0 = st.t0;
+        e.u = st.u;
+        e.v = st.v;
+        e.w = st.w;
         e.cos_t = st.cos_t;
         e.ds = st.ds;
         e.inv_bc = st.inv_bc;
@@ -998,31 +1178,30 @@ __device__ __forceinline__ TileSetup tile_setup(const Args& a, int64_t g0, int n
         e.sb2y = (T)(st.sin_t * st.b2y);
         e.sb2z = (T)(st.sin_t * st.b2z);
         e.photons = st.photons;
-        e.boff = excl;
         e.sidx = lane;
     }
     {
-        const int d_mass = __popcll(__ballot(status == CKV_DROP_MASS));
-        const int d_thr = __popcll(__ballot(status == CKV_DROP_THRESHOLD));
-        const int d_nf = __popcll(__ballot(status == CKV_DROP_NONFINITE));
+        const int n_emit = __popcll(__ballot(own && emits));
+        const int d_mass = __popcll(__ballot(own && status == CKV_DROP_MASS));
+        const int d_thr = __popcll(__ballot(own && status == CKV_DROP_THRESHOLD));
+        const int d_nf = __popcll(__ballot(own && status == CKV_DROP_NONFINITE));
         if (lane == 0) {
-            wcnt[kWcBunches] += total;
-            wcnt[kWcEmitting] += __popcll(emit_mask);
-            wcnt[kWcDrop0 + CKV_DROP_MASS] += d_mass;
-            wcnt[kWcDrop0 + CKV_DROP_THRESHOLD] += d_thr;
-            wcnt[kWcDrop0 + CKV_DROP_NONFINITE] += d_nf;
+            if (total_all < ((int64_t)1 << 30)) wa.wcnt[kWcBunches] += total_all;
+            wa.wcnt[kWcEmitting] += n_emit;
+            wa.wcnt[kWcDrop0 + CKV_DROP_MASS] += d_mass;
+            wa.wcnt[kWcDrop0 + CKV_DROP_THRESHOLD] += d_thr;
+            wa.wcnt[kWcDrop0 + CKV_DROP_NONFINITE] += d_nf;
         }
     }
-    return TileSetup{total, (int)(incl - nb), status == -1};
+    return TileSetup{total, excl, in_pass, direct};
 }
 
-// The same as a called function (the mixed kernel's choice: its step setup's
-// registers and the step arrays' pointers then take no room in the bunch loop,
-// 100 -> 8 scalar spills; the FP64 kernel, with 256 registers, runs faster inline).
+// The same as a called function: its step setup's registers and the step arrays'
+// pointers then take no room in the bunch loop.
 template <int PREC, int TS, int FEAT>
 __device__ __noinline__ TileSetup tile_setup_call(uint64_t args_at, int64_t g0, int nseg, int64_t seg_id0,
-                                                  int lane, uint64_t lt_mask, uint32_t stash_at,
-                                                  uint32_t sctr_at, uint32_t wcnt_at, uint32_t lst_at)
+                                                  uint32_t shower_id, int lane, uint64_t lt_mask,
+                                                  uint32_t area_at, uint32_t tel_at)
 {
     extern __shared__ __align__(16) unsigned char lds[];
     // the launch's argument block, at the address the kernel passes: wave-uniform and
@@ -1030,11 +1209,27 @@ __device__ __noinline__ TileSetup tile_setup_call(uint64_t args_at, int64_t g0, 
     const uint64_t at_u = ((uint64_t)(uint32_t)__builtin_amdgcn_readfirstlane((int)(args_at >> 32)) << 32) |
                           (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)args_at);
     const Args& a = *(const Args*)reinterpret_cast<const __attribute__((address_space(4))) Args*>(at_u);
-    return tile_setup<PREC, TS, FEAT>(a, g0, nseg, seg_id0, lane, lt_mask,
-                                      reinterpret_cast<StepEntry<PREC>*>(lds + stash_at),
-                                      reinterpret_cast<uint32_t*>(lds + sctr_at),
-                                      reinterpret_cast<int64_t*>(lds + wcnt_at),
-                                      reinterpret_cast<int64_t*>(lds + lst_at));
+    const WaveArea<PREC, TS> wa(lds + __builtin_amdgcn_readfirstlane((int)area_at), a.n_tel,
+                                (FEAT & kFeatProfile) != 0 ? a.prof_bins : 0);
+    return tile_setup<PREC, TS, FEAT>(a, g0, nseg, seg_id0, shower_id, lane, lt_mask, wa,
+                                      reinterpret_cast<const double*>(
+                                          lds + __builtin_amdgcn_readfirstlane((int)tel_at)));
+}
+
+// Screening pass: the n ids of a wave's buffer to the list; one atomic claims exactly
+// their slots.  Called by the whole wave.
+constexpr int kScreenBuf = 256;
+
+__device__ __forceinline__ void flush_list(const Args& a, const uint64_t* buf, int n, int lane)
+{
+    if (n == 0) return;
+    int64_t base = 0;
+    if (lane == 0) base = (int64_t)atomicAdd((unsigned long long*)a.list_count, (unsigned long long)n);
+    base = scalar64(base);
+    wave_lds_sync();
+    for (int q = lane; q < n; q += kWave)
+        if (base + q >= 0 && base + q < a.list_cap) a.list_ids[base + q] = buf[q];
+    wave_lds_sync();
 }
 
 template <int PREC, int TS, int FEAT>
@@ -1045,8 +1240,6 @@ __global__ void __launch_bounds__(emit_threads(PREC, FEAT)) emit_kernel(Args a)
     constexpr bool SEARCH = (FEAT & kFeatSearch) != 0;
     constexpr bool CURVED = (FEAT & kFeatCurved) != 0;
     constexpr bool SCREEN = (FEAT & kFeatScreen) != 0;
-    constexpr bool NARROW = (FEAT & kFeatNarrow) != 0;
-    constexpr bool PARTIAL = PROF || SCREEN || NARROW;   // table staged in part, the rest from HBM
     constexpr bool SLOWPATH = EXACT || CURVED;    // lanes that leave the moment series
     using T = typename std::conditional<PREC == 0, double, float>::type;
     using Entry = StepEntry<PREC>;
@@ -1055,57 +1248,40 @@ __global__ void __launch_bounds__(emit_threads(PREC, FEAT)) emit_kernel(Args a)
     const int lane = lane_id();
     const int wave = threadIdx.x / kWave;
 
-    // ---- stage the atmosphere table once per workgroup
-    const size_t tab_bytes = table_bytes(PREC, a.n_nodes, PARTIAL);
-    {
-        const uint4* src = reinterpret_cast<const uint4*>(PREC == 0 ? (const void*)a.node64
-                                                                    : (const void*)a.cell32);
-        uint4* dst = reinterpret_cast<uint4*>(lds);
-        const int n16 = (int)(tab_bytes / 16);
-        for (int q = threadIdx.x; q < n16; q += blockDim.x) dst[q] = src[q];
-    }
-    // node tables: altitudes and inverse widths after the table
-    double* hn_lds = reinterpret_cast<double*>(lds + ((tab_bytes + 15) & ~(size_t)15));
+    // node tables: altitudes and inverse widths
+    double* hn_lds = reinterpret_cast<double*>(lds);
     const size_t srch_bytes = SEARCH ? search_bytes(a.n_nodes) : 0;
     if (SEARCH)
         for (int q = threadIdx.x; q < 2 * a.n_nodes - 1; q += blockDim.x) hn_lds[q] = a.hnodes[q];
     // sphere table {X, Y, R^2} after them
-    double* tel_sh = reinterpret_cast<double*>(lds + tel_lds_offset<PREC, FEAT>(a));
+    double* tel_sh = reinterpret_cast<double*>(lds + srch_bytes);
     for (int q = threadIdx.x; q < a.n_tel; q += blockDim.x) {
         tel_sh[3 * q] = a.tel[4 * q];
         tel_sh[3 * q + 1] = a.tel[4 * q + 1];
         tel_sh[3 * q + 2] = a.tel[4 * q + 3];
     }
-    const size_t wv_bytes = wave_bytes(PREC, TS, a.n_tel, PROF ? a.prof_bins : 0);
-    unsigned char* wbase = lds + ((tab_bytes + 15) & ~(size_t)15) + srch_bytes + tel_bytes(a.n_tel) +
-                           (size_t)wave * (wv_bytes + (SCREEN ? kScreenWaveBytes : 0));
-    // screening: list state and ballot words after the wave's regular area
-    int64_t* lst = reinterpret_cast<int64_t*>(wbase + wv_bytes);
-    uint64_t* bits = reinterpret_cast<uint64_t*>(lst + 6);
-    if (SCREEN && lane == 0) {
-        lst[1] = (int64_t)a.list_ids;
-        lst[2] = a.list_cap;
-        lst[3] = (int64_t)a.list_count;
-    }
-    Entry* stash = reinterpret_cast<Entry*>(wbase);
-    int32_t* flags = reinterpret_cast<int32_t*>(wbase + TS * sizeof(Entry));
-    // FP64 path: counter word per step (the mixed path keeps it in its step record)
-    uint32_t* sctr = reinterpret_cast<uint32_t*>(flags + kWave);
-    int64_t* wcnt = reinterpret_cast<int64_t*>(sctr + (PREC == 0 ? ((TS + 1) & ~1) : 0));
-    int32_t* tcount = reinterpret_cast<int32_t*>(wcnt + kWcCount);
-    // profile of the current tile: photons (FP64) and bunches per depth bin
-    double* hph = reinterpret_cast<double*>(
-        reinterpret_cast<unsigned char*>(tcount) + (((size_t)a.n_tel * sizeof(int32_t) + 15) & ~(size_t)15));
-    uint32_t* hbu = reinterpret_cast<uint32_t*>(hph + a.prof_bins);
+    const int prof_bins = PROF ? a.prof_bins : 0;
+    const size_t wv_bytes = wave_bytes(PREC, TS, a.n_tel, prof_bins);
+    const size_t wv_stride = wv_bytes + (SCREEN ? kScreenBuf * sizeof(uint64_t) : 0);
+    unsigned char* wbase = lds + srch_bytes + tel_bytes(a.n_tel) + (size_t)wave * wv_stride;
+    const WaveArea<PREC, TS> wa(wbase, a.n_tel, prof_bins);
+    // screening: ids on their way to the list
+    uint64_t* const buf = reinterpret_cast<uint64_t*>(wbase + wv_bytes);
+    int buf_n = 0;
+    Entry* const stash = wa.stash;
+    int32_t* const flags = wa.flags;
+    uint32_t* const sctr = wa.sctr;
+    int64_t* const wcnt = wa.wcnt;
+    int32_t* const tcount = wa.tcount;
+    double* const hph = wa.hph;
+    uint32_t* const hbu = wa.hbu;
     for (int k = lane; k < a.n_tel; k += kWave) tcount[k] = 0;
     if (PROF)
-        for (int k = lane; k < a.prof_bins; k += kWave) { hph[k] = 0.0; hbu[k] = 0u; }
+        for (int k = lane; k < prof_bins; k += kWave) { hph[k] = 0.0; hbu[k] = 0u; }
     if (lane < kWcCount) wcnt[lane] = 0;
     flags[lane] = 0;
     __syncthreads();
 
-    const double* tab64 = reinterpret_cast<const double*>(lds);
-    const float* tab32 = reinterpret_cast<const float*>(lds);
     const T a1 = (T)-0.5, a2 = (T)0.375, a3 = (T)-0.3125, a4 = (T)0.2734375;
     const double inv_c = 1.0 / kSpeedOfLight;
     const uint64_t lt_mask = (lane == 0) ? 0ull : (~0ull >> (64 - lane));
@@ -1140,42 +1316,15 @@ __global__ void __launch_bounds__(emit_threads(PREC, FEAT)) emit_kernel(Args a)
     struct CellMoments { T psi_e, D1, D2, D3, D4, D5; };
     auto cell_moments = [&](int ci, T f, double dcell_) {
         T psi_i, dpsi, P0, P1, P2, P3, P4, P5;
-        // LDS read always (index clamped into the staged part); the rare
-        // lookups above it are replaced by a read from HBM.  The FP32 table's two
-        // reads go through their own address spaces, so the compiler cannot fuse
-        // them into one generic (flat) load for every lookup.  The FP64 narrow build
-        // keeps the fused generic load: typed, it spills more and runs 0.5 %
-        // slower.
         if (PREC == 0) {
-            double n0[6], n1;
-            {
-                const int cl = PARTIAL ? min(ci, a.lds_entries - 2) : ci;
-                const double* nd = tab64 + (size_t)kNode64 * cl;
-                for (int q = 0; q < 6; ++q) n0[q] = nd[q];
-                n1 = nd[kNode64];
-            }
-            if (PARTIAL && ci + 1 >= a.lds_entries) {
-                const double* nd = a.node64 + (size_t)kNode64 * ci;
-                for (int q = 0; q < 6; ++q) n0[q] = __builtin_nontemporal_load(nd + q);
-                n1 = __builtin_nontemporal_load(nd + kNode64);
-            }
-            psi_i = n0[0];
-            dpsi = n1 - n0[0];
+            const HbmF64* nd = as_hbm(a.node64) + (size_t)kNode64 * ci;
+            psi_i = nd[0];
+            dpsi = nd[kNode64] - psi_i;
             P0 = SEARCH ? hn_lds[ci] - a.h_obs : (double)ci * a.step;
-            P1 = n0[1]; P2 = n0[2]; P3 = n0[3]; P4 = n0[4]; P5 = n0[5];
+            P1 = nd[1]; P2 = nd[2]; P3 = nd[3]; P4 = nd[4]; P5 = nd[5];
         } else {
-            f32x4 c_a, c_b;
-            {
-                const int cl = PARTIAL ? min(ci, a.lds_entries - 1) : ci;
-                const LdsF32x4* cc = as_lds4(tab32 + (size_t)kCell32 * cl);
-                c_a = cc[0];
-                c_b = cc[1];
-            }
-            if (PARTIAL && ci >= a.lds_entries) {
-                const HbmF32x4* cg = as_hbm4(a.cell32 + (size_t)kCell32 * ci);
-                c_a = cg[0];
-                c_b = cg[1];
-            }
+            const HbmF32x4* cg = as_hbm4(a.cell32) + 2 * (size_t)ci;
+            const f32x4 c_a = cg[0], c_b = cg[1];
             psi_i = c_a.x; dpsi = c_a.y; P1 = c_a.z; P2 = c_a.w;
             P3 = c_b.x; P4 = c_b.y; P5 = c_b.z;
             P0 = c_b.w;
@@ -1240,23 +1389,22 @@ __global__ void __launch_bounds__(emit_threads(PREC, FEAT)) emit_kernel(Args a)
         return ctw * ix.inv_w * inv_c;
     };
 
-    // tiles are claimed from the counter.  The mixed kernel takes each wave's first
-    // tile by its index in the grid and offsets later claims by the grid's wave count,
-    // so the launch does not start with every wave's atomic on the one counter (the
-    // FP64 kernel measured slower with it: the extra scalar state spills)
-    constexpr bool kStaticFirst = PREC == 1;
-    const int64_t n_waves_grid = kStaticFirst ? (int64_t)gridDim.x * (blockDim.x / kWave) : 0;
-    const int64_t t_first = kStaticFirst ? scalar64((int64_t)blockIdx.x * (blockDim.x / kWave) + wave) : 0;
-    bool first_tile = kStaticFirst;
-    for (;;) {
-        int64_t t = t_first;
+    // Tiles are dealt in kTileClasses interleaved classes, one per group of workgroups, each
+    // with its claim counter on its own cache line: all waves' claims on one address came
+    // 13 ns apart, which bounded the kernel once a tile took less (62 500 tiles: 0.83 ms).
+    // Each wave's first tile goes by its place in the grid, a workgroup's first wave first.
+    const int n_cls = min(kTileClasses, (int)gridDim.x), cls = (int)blockIdx.x % n_cls;
+    const int cls_groups = ((int)gridDim.x - cls + n_cls - 1) / n_cls;
+    const int cls_waves = cls_groups * (int)(blockDim.x / kWave);
+    int64_t t_next = cls + (int64_t)n_cls * scalar64(wave * cls_groups + (int)blockIdx.x / n_cls);
+    for (bool first_tile = true;; first_tile = false) {
+        int64_t t = t_next;
         if (!first_tile) {
+            int64_t i = 0;
             if (lane == 0)
-                t = n_waves_grid +
-                    (int64_t)atomicAdd((unsigned long long*)&a.ctrl[SCREEN ? kScreenCounter : kTileCounter], 1ull);
-            t = kStaticFirst ? scalar64(t) : uniform(t);
+                i = (int64_t)atomicAdd((unsigned long long*)&a.ctrl[kClaimCounter + 32 * cls], 1ull);
+            t = cls + n_cls * (cls_waves + scalar64(i));
         }
-        first_tile = false;
         if (t >= n_tiles) break;
         // shower of the tile
         int lo = 0, hi = a.n_showers;   // tiles_before[lo] <= t < tiles_before[hi]
@@ -1273,46 +1421,149 @@ __global__ void __launch_bounds__(emit_threads(PREC, FEAT)) emit_kernel(Args a)
         const double t_ref = a.t_ref[s];
         int32_t thits = 0;         // crossings of this tile (wave-uniform)
 
-        // ---- step setups, one per lane; emitting steps are compacted.  The mixed
-        // kernel calls it out of line, handing the callee the arguments where the
-        // launch put them (the kernel argument segment) rather than a private copy.
-        TileSetup ts_;
-        if constexpr (PREC == 1) {
-            auto at = [&](const void* p) { return (uint32_t)((const unsigned char*)p - lds); };
-            const uint64_t args_at = (uint64_t)__builtin_amdgcn_kernarg_segment_ptr();
-            ts_ = tile_setup_call<PREC, TS, FEAT>(args_at, g0, nseg, seg_id0, lane, lt_mask, at(stash), at(sctr),
-                                                  at(wcnt), at(lst));
-        } else {
-            ts_ = tile_setup<PREC, TS, FEAT>(a, g0, nseg, seg_id0, lane, lt_mask, stash, sctr, wcnt, lst);
-        }
-        const int64_t total = ts_.total;
-        const bool emits = ts_.emits;
+        // ---- step setups (called out of line, with the arguments where the launch put
+        // them, the kernel argument segment, rather than a private copy)
+        const TileSetup ts_ = tile_setup_call<PREC, TS, FEAT>(
+            (uint64_t)__builtin_amdgcn_kernarg_segment_ptr(), g0, nseg, seg_id0, shower_id, lane, lt_mask,
+            (uint32_t)(wbase - lds), (uint32_t)(reinterpret_cast<unsigned char*>(tel_sh) - lds));
+        const int32_t total = __builtin_amdgcn_readfirstlane(ts_.total);
+        const bool in_pass = ts_.in_pass;
+        const bool direct = ts_.direct;
         const int excl = ts_.excl;
         wave_lds_sync();
 
-        // ---- bunches of the tile, one per lane
-        for (int64_t c0 = 0; c0 < total; c0 += kWave) {
-            const int32_t j = (int32_t)(c0 + lane);
-            const bool active = j < total;
-            // step of bunch j: emitting steps starting at or before c0, plus the
-            // steps starting inside this chunk at or before j (flag row)
-            const int cnt0 = __popcll(__ballot(emits && excl <= (int)c0));
-            if (emits && excl > (int)c0 && excl < (int)c0 + kWave) flags[excl - (int)c0] = 1;
+        // ---- bunches of the tile.  First pass, one bunch per lane: its azimuth's draw
+        // against its step's sectors; the bunches that may reach a sphere wait in the
+        // queue until 64 are there, in (step, bunch) order.
+        int c0 = 0, qn = 0;
+        for (;;) {
+            while (qn < kWave && c0 < total) {
+                const int32_t j = c0 + lane;
+                const bool active = j < total;
+                // step of bunch j: the pass's steps starting at or before c0, plus those
+                // starting inside this chunk at or before j (flag row)
+                const int cnt0 = __popcll(__ballot(in_pass && excl <= c0));
+                if (in_pass && excl > c0 && excl < c0 + kWave) flags[excl - c0] = 1;
+                wave_lds_sync();
+                const uint64_t starts = __ballot(flags[lane] != 0);
+                flags[lane] = 0;
+                const int si = cnt0 - 1 + __popcll(starts & le_mask);
+                // Philox round keys, advanced on the scalar unit inside the loop
+                const uint32_t opaque = (uint32_t)((uint64_t)(uint32_t)c0 >> 31);   // 0; keeps the schedule in the loop
+                uint32_t kr0 = a.key0 + opaque, kr1 = a.key1 + opaque;
+                bool take = active;
+                int32_t k = 0;
+                if (PROF) {
+                    // longitudinal profile: every bunch's emission altitude
+                    int pbin = -1;     // depth bin of the bunch, -1: not counted
+                    if (active) {
+                        const Entry& e = stash[si];
+                        k = j - wa.pass[si].boff;
+                        uint32_t c_1;
+                        if constexpr (PREC == 1) c_1 = e.ctr1;
+                        else c_1 = sctr[e.sidx];
+                        uint32_t r[4];
+                        philox4x32_10((uint32_t)k, c_1, shower_id, 0u, kr0, kr1, r);
+                        const double u0 = fma((double)r[0], 2.3283064365386963e-10, 1.1641532182693481e-10);
+                        const double s_along = ((double)k + u0) * e.ds;
+                        double he;
+                        {
+                            // rounded as the FP64 definition rounds it
+#pragma clang fp contract(off)
+                            he = e.h0 - s_along * e.w;
+                        }
+                        const double xcell = (he - a.h_obs) * a.inv_step;
+                        const int ci = min((int)xcell, a.n_nodes - 2);
+                        if (he >= a.h_obs && he < a.h_top) pbin = profile_bin(a, ci, xcell - (double)ci);
+                        if (!direct) {
+                            const uint32_t w = wa.masks[kSectorWords * e.sidx + (int)(r[1] >> 29)];
+                            take = ((w >> ((r[1] >> 24) & 31u)) & 1u) != 0;
+                        }
+                    }
+                    // runs of lanes with the same step and bin (bunches of a step are
+                    // consecutive lanes and their depth is monotonic in k): the first lane
+                    // of each run adds the whole run, so LDS atomics do not collide
+                    const bool member = pbin >= 0;
+                    const int key = member ? (si << 8) | pbin : -1;     // pbin < 256
+                    // the previous lane's key (DPP wave shift right by one; lane 0 gets -2)
+                    const int key_prev = __builtin_amdgcn_update_dpp(-2, key, 0x138, 0xf, 0xf, false);
+                    const bool head = member && key_prev != key;
+                    const uint64_t mem_mask = __ballot(member), head_mask = __ballot(head);
+                    if (head) {
+                        const uint64_t after = lane == kWave - 1 ? 0ull : (~0ull << (lane + 1));
+                        const uint64_t ends = (~mem_mask | head_mask) & after;
+                        const int len = (ends ? __builtin_ctzll(ends) : kWave) - lane;
+                        atomicAdd(&hph[pbin], (double)len * stash[si].photons);
+                        atomicAdd(&hbu[pbin], (uint32_t)len);
+                    }
+                } else if (active) {
+                    const StepPass sp = wa.pass[si];
+                    k = j - sp.boff;
+                    if (!direct) {
+                        // Philox as far as the second draw: its last two rounds need one
+                        // product each
+                        const uint64_t f0 = (uint64_t)0xD2511F53u * (uint32_t)k;
+                        const uint32_t f1_lo = 0xCD9E8D57u * shower_id;
+                        uint32_t c_0, c_1, c_2, c_3;
+                        {
+                            const uint64_t p1 = (uint64_t)0xCD9E8D57u * ((uint32_t)(f0 >> 32) ^ kr1);
+                            kr0 += 0x9E3779B9u;
+                            kr1 += 0xBB67AE85u;
+                            c_0 = __builtin_amdgcn_bitop3_b32((uint32_t)(p1 >> 32), f1_lo, kr0, 0x96);
+                            c_2 = __builtin_amdgcn_bitop3_b32(sp.hi0, (uint32_t)f0, kr1, 0x96);
+                            c_1 = (uint32_t)p1;
+                            c_3 = sp.lo0;
+                        }
+#pragma unroll
+                        for (int rr = 2; rr < 7; ++rr) {
+                            kr0 += 0x9E3779B9u;
+                            kr1 += 0xBB67AE85u;
+                            const uint64_t p0 = (uint64_t)0xD2511F53u * c_0;
+                            const uint64_t p1 = (uint64_t)0xCD9E8D57u * c_2;
+                            c_0 = __builtin_amdgcn_bitop3_b32((uint32_t)(p1 >> 32), c_1, kr0, 0x96);
+                            c_2 = __builtin_amdgcn_bitop3_b32((uint32_t)(p0 >> 32), c_3, kr1, 0x96);
+                            c_1 = (uint32_t)p1;
+                            c_3 = (uint32_t)p0;
+                        }
+                        kr0 += 0x9E3779B9u;      // eighth round: words 0 and 3
+                        kr1 += 0xBB67AE85u;
+                        c_3 = 0xD2511F53u * c_0;
+                        c_0 = __builtin_amdgcn_bitop3_b32(__umulhi(0xCD9E8D57u, c_2), c_1, kr0, 0x96);
+                        kr1 += 0xBB67AE85u;      // ninth: word 2
+                        c_2 = __builtin_amdgcn_bitop3_b32(__umulhi(0xD2511F53u, c_0), c_3, kr1, 0x96);
+                        const uint32_t r1 = 0xCD9E8D57u * c_2;     // tenth: word 1
+                        const uint32_t w = wa.masks[kSectorWords * sp.sidx + (int)(r1 >> 29)];
+                        take = ((w >> ((r1 >> 24) & 31u)) & 1u) != 0;
+                    }
+                }
+                const uint64_t m = __ballot(take);
+                if (take) {
+                    const int at = qn + __popcll(m & lt_mask);
+                    wa.qk[at] = (uint32_t)k;
+                    wa.qs[at] = (uint8_t)si;
+                }
+                qn += __popcll(m);
+                c0 += kWave;
+            }
+            if (qn == 0) break;
+            // ---- a chunk of the queue, one bunch per lane
             wave_lds_sync();
-            const uint64_t starts = __ballot(flags[lane] != 0);
-            flags[lane] = 0;
-            const int si = cnt0 - 1 + __popcll(starts & le_mask);
-            // Philox round keys, advanced on the scalar unit inside the loop
-            const uint32_t opaque = (uint32_t)(c0 >> 40);   // 0; keeps the schedule in the loop
+            const bool active = lane < qn;
+            const int32_t k = (int32_t)wa.qk[lane];
+            const int si = wa.qs[lane];
+            if (qn > kWave && lane < qn - kWave) {
+                wa.qk[lane] = wa.qk[kWave + lane];
+                wa.qs[lane] = wa.qs[kWave + lane];
+            }
+            qn = qn > kWave ? qn - kWave : 0;
+            const uint32_t opaque = (uint32_t)((uint64_t)(uint32_t)c0 >> 31);   // 0, as above
             uint32_t kr0 = a.key0 + opaque, kr1 = a.key1 + opaque;
 
             bool alive = false;
             int drop_why = -1;
             // read only in lanes that emit a live bunch: left undefined elsewhere
             double xg, yg, he;
-            int32_t k, sidx;
             double uod, vod;   // observed direction for the sphere test (live bunches)
-            int pbin = -1;     // depth bin of the bunch for the profile, -1: not counted
             bool screen_all = false;   // screening: listed whatever its sphere tests say
             double fcell, dcell = 0.0;   // fraction and height of the emission point in its cell
             int ci;
@@ -1325,13 +1576,11 @@ __global__ void __launch_bounds__(emit_threads(PREC, FEAT)) emit_kernel(Args a)
             uint32_t r2_rec;     // the wavelength's draw
             if (active) {
                 const Entry& e = stash[si];
-                k = j - e.boff;
-                sidx = e.sidx;
                 // Philox4x32-10 with counter (k, step index in shower, shower id, 0)
                 uint32_t c_0 = (uint32_t)k, c_2 = shower_id, c_3 = 0u;
                 uint32_t c_1;
                 if constexpr (PREC == 1) c_1 = e.ctr1;
-                else c_1 = sctr[sidx];
+                else c_1 = sctr[e.sidx];
 #pragma unroll
                 for (int rr = 0; rr < 10; ++rr) {
                     const uint64_t p0 = (uint64_t)0xD2511F53u * c_0;
@@ -1385,7 +1634,6 @@ __global__ void __launch_bounds__(emit_threads(PREC, FEAT)) emit_kernel(Args a)
                     ci = min((int)xcell, a.n_nodes - 2);
                     fcell = xcell - (double)ci;
                 }
-                if (PROF && he >= a.h_obs && he < a.h_top) pbin = profile_bin(a, ci, fcell);
                 const double ct = e.cos_t;
                 // direction on the Cherenkov cone
                 double pu, pv, pw;
@@ -1502,24 +1750,6 @@ __global__ void __launch_bounds__(emit_threads(PREC, FEAT)) emit_kernel(Args a)
                     wcnt[kWcDrop0 + CKV_DROP_GRAZING] += d3;
                 }
             }
-            if (PROF) {
-                // runs of lanes with the same step and bin (bunches of a step are
-                // consecutive lanes and their depth is monotonic in k): the first lane
-                // of each run adds the whole run, so LDS atomics do not collide
-                const bool member = pbin >= 0;
-                const int key = member ? (si << 8) | pbin : -1;     // pbin < 256
-                // the previous lane's key (DPP wave shift right by one; lane 0 gets -2)
-                const int key_prev = __builtin_amdgcn_update_dpp(-2, key, 0x138, 0xf, 0xf, false);
-                const bool head = member && key_prev != key;
-                const uint64_t mem_mask = __ballot(member), head_mask = __ballot(head);
-                if (head) {
-                    const uint64_t after = lane == kWave - 1 ? 0ull : (~0ull << (lane + 1));
-                    const uint64_t ends = (~mem_mask | head_mask) & after;
-                    const int len = (ends ? __builtin_ctzll(ends) : kWave) - lane;
-                    atomicAdd(&hph[pbin], (double)len * stash[si].photons);
-                    atomicAdd(&hbu[pbin], (uint32_t)len);
-                }
-            }
             // ---- candidate spheres (ascending telescope index)
             int cur = 0, cend = 0;
             int first = -1;          // the cell's first sphere, known without a list read
@@ -1557,17 +1787,22 @@ __global__ void __launch_bounds__(emit_threads(PREC, FEAT)) emit_kernel(Args a)
             };
             advance();
             if constexpr (SCREEN) {
-                // candidates of the soft response: one ballot word per 64 bunches,
-                // flushed to the list when the buffer is full and at the tile's end
-                const uint64_t m = __ballot(my_next != INT_MAX || screen_all);
-                const int w = (int)((c0 >> 6) & (kScreenWords - 1));
-                if (lane == 0) bits[w] = m;
-                if (w == kScreenWords - 1 || c0 + kWave >= total) {
-                    wave_lds_sync();
-                    soft_list_flush<Entry>((uint32_t)((unsigned char*)lst - lds), (uint32_t)((unsigned char*)bits - lds),
-                                           (uint32_t)((unsigned char*)stash - lds), c0 - (int64_t)w * kWave, w + 1,
-                                           lane);
+                // candidates of the soft response: gathered in the wave's buffer, which goes
+                // to the list when full (one atomic on the list's count for each 256 or so:
+                // claims of all waves come 13 ns apart)
+                const uint64_t step = (uint64_t)(g0 + stash[active ? si : 0].sidx);
+                bool cand = my_next != INT_MAX || screen_all;
+                if (cand && ((uint32_t)k >= (1u << kSoftIdBits) || step >= (1ull << (64 - kSoftIdBits)))) {
+                    atomicOr((unsigned long long*)a.list_count, kSoftListInvalid);
+                    cand = false;
                 }
+                const uint64_t m = __ballot(cand);
+                if (buf_n + __popcll(m) > kScreenBuf) {
+                    flush_list(a, buf, buf_n, lane);
+                    buf_n = 0;
+                }
+                if (cand) buf[buf_n + __popcll(m & lt_mask)] = (step << kSoftIdBits) | (uint64_t)(uint32_t)k;
+                buf_n += __popcll(m);
             } else {
                 // ---- the records of the crossing bunches.  About one chunk in five holds
                 // a crossing, so the wavelength and the record's roundings are done here,
@@ -1575,11 +1810,10 @@ __global__ void __launch_bounds__(emit_threads(PREC, FEAT)) emit_kernel(Args a)
                 // (the only user of D_5 and 1/n_e) here, recomputed from the table rather
                 // than kept live through the sphere tests.
                 float uo, vo, t_f, he_f, photons, lam;
-                int32_t k_rec, sidx_rec;
+                int32_t sidx_rec;
                 if (__ballot(my_next != INT_MAX)) {
                     if (my_next != INT_MAX) {
                         const Entry& er = stash[si];
-                        k_rec = j - er.boff;
                         sidx_rec = er.sidx;
                         photons = (float)er.photons;
                         if (PREC == 0) {
@@ -1641,7 +1875,7 @@ __global__ void __launch_bounds__(emit_threads(PREC, FEAT)) emit_kernel(Args a)
                             ef[1] = make_float4(t_f, he_f, photons, lam);
                             uint4* eu = reinterpret_cast<uint4*>(se);
                             eu[2] = make_uint4((uint32_t)t, (uint32_t)kmin | ((uint32_t)sidx_rec << 16),
-                                               (uint32_t)(rank0 + below), (uint32_t)k_rec);
+                                               (uint32_t)(rank0 + below), (uint32_t)k);
                         }
                     }
                     if (nmine > room) {
@@ -1719,6 +1953,7 @@ __global__ void __launch_bounds__(emit_threads(PREC, FEAT)) emit_kernel(Args a)
         wave_lds_sync();
     }
 
+    if (SCREEN) flush_list(a, buf, buf_n, lane);
     // ---- close the staging block and publish counters: the workgroup's waves are
     // summed in LDS and the first wave adds the sums, one atomic per counter and
     // workgroup (one per wave queued thousands of atomics on the counters' line at
@@ -1726,11 +1961,10 @@ __global__ void __launch_bounds__(emit_threads(PREC, FEAT)) emit_kernel(Args a)
     if (blk >= 0 && lane == 0) a.stage_fill[blk] = blk_fill;
     __syncthreads();
     if (wave == 0 && lane < kWcCount) {
-        const size_t wstride = wv_bytes + (SCREEN ? kScreenWaveBytes : 0);
         const unsigned char* w0 = reinterpret_cast<const unsigned char*>(wcnt);
         int64_t v = 0;
         for (int w = 0; w < (int)(blockDim.x / kWave); ++w)
-            v += reinterpret_cast<const int64_t*>(w0 + (size_t)w * wstride)[lane];
+            v += reinterpret_cast<const int64_t*>(w0 + (size_t)w * wv_stride)[lane];
         const int slot = lane == kWcBunches ? kBunches
                        : lane == kWcEmitting ? kEmitting
                        : lane == kWcHits ? kHits
@@ -3165,7 +3399,6 @@ Args make_args(const RunPlan& p)
     a.n_obs = at->n_obs;
     a.node64 = at->d_node64;
     a.cell32 = at->d_cell32;
-    a.lds_entries = lds_entries(p.params.precision, a.n_nodes, p.prof_bins > 0);
     a.hnodes = at->d_hnodes;
     a.search_pow2 = 0;
     while ((a.search_pow2 ? 2 * a.search_pow2 : 1) < a.n_nodes - 1)
@@ -3225,6 +3458,19 @@ Args make_args(const RunPlan& p)
     return a;
 }
 
+// The azimuth sectors' bound constants (light_cone) for spheres of radius up to rmax
+// with centres up to dmax from the origin.
+void set_sectors(Args& a, const ckv_atmo* at, double rmax, double dmax)
+{
+    if (!(1.0 + at->psi_min >= 0.5)) return;
+    a.sec_rmax = rmax;
+    a.sec_dmax = dmax;
+    a.sec_falls = at->psi_falls ? 1 : 0;
+    a.sec_slope = at->psi_slope;
+    a.sec_psi_max = at->psi_max;
+    a.sec_psi_min = at->psi_min;
+}
+
 int check_launch(const char* what)
 {
     hipError_t e = hipGetLastError();
@@ -3238,25 +3484,25 @@ int check_launch(const char* what)
 }  // namespace
 
 int emit_config(int precision, int n_tel, int prof_bins, const ckv_atmo* atmo, int tile_segs,
-                int max_waves, int* waves, size_t* lds_bytes, bool narrow_ok)
+                int max_waves, int* waves, size_t* lds_bytes, bool many_nodes_ok)
 {
     const size_t srch = atmo->h_nodes.empty() ? 0 : search_bytes((int)atmo->n_nodes);
     const size_t cap = 160 * 1024;
     const size_t per = wave_bytes(precision, tile_segs, n_tel, prof_bins);
-    // FP64: 16 waves only as the narrow build (partial table), else at most 8
-    if (precision == 0 && !narrow_ok) max_waves = std::min(max_waves, kMaxEmitWaves / 2);
-    for (int wv = kMaxEmitWaves; wv >= 1; wv /= 2) {
-        if (wv > max_waves) continue;
-        const bool partial = prof_bins > 0 || (precision == 0 && wv > kMaxEmitWaves / 2);
-        const size_t tab =
-            ((table_bytes(precision, (int)atmo->n_nodes, partial) + 15) & ~(size_t)15) + srch;
-        const size_t tot = tab + tel_bytes(n_tel) + (size_t)wv * per;
-        if (tot <= cap) {
-            *waves = wv;
-            *lds_bytes = tot;
-            return CKV_OK;
+    auto beside_table = [&](bool part, int wv) {
+        return ((table_bytes(precision, (int)atmo->n_nodes, part) + 15) & ~(size_t)15) + srch + tel_bytes(n_tel) +
+                   (size_t)wv * limit_wave_bytes(precision, tile_segs, n_tel, prof_bins) <= cap;
+    };
+    if (beside_table(prof_bins > 0, 1) || (many_nodes_ok && beside_table(true, kMaxEmitWaves)))
+        for (int wv = kMaxEmitWaves; wv >= 1; wv /= 2) {
+            if (wv > max_waves) continue;
+            const size_t tot = srch + tel_bytes(n_tel) + (size_t)wv * per;
+            if (tot <= cap) {
+                *waves = wv;
+                *lds_bytes = tot;
+                return CKV_OK;
+            }
         }
-    }
     set_error("atmosphere table too large for LDS");
     return CKV_ERR_TABLE;
 }
@@ -3287,20 +3533,6 @@ int launch_emit_feat(const Args& a, int grid, int waves, size_t lds, hipStream_t
         return CKV_ERR_ARG;
     }
     const int feat = (a.prof_bins > 0 ? kFeatProfile : 0) | (a.grazing_exact ? kFeatExact : 0);
-    if constexpr (PREC == 0) {
-        if (waves > emit_threads(0, 0) / kWave) {
-            if (feat == 0) return launch_emit<PREC, TS, kFeatNarrow>(a, grid, waves, lds, st);
-            set_error("the FP64 kernel runs 16 waves per workgroup only without other features");
-            return CKV_ERR_ARG;
-        }
-    }
-    if constexpr (PREC == 1) {
-        if (waves <= emit_threads(1, kFeatWide) / kWave) {
-            if (feat == 0) return launch_emit<PREC, TS, kFeatWide>(a, grid, waves, lds, st);
-            if (feat == kFeatProfile)
-                return launch_emit<PREC, TS, kFeatProfile | kFeatWide>(a, grid, waves, lds, st);
-        }
-    }
     switch (feat) {
         case 0: return launch_emit<PREC, TS, 0>(a, grid, waves, lds, st);
         case kFeatProfile: return launch_emit<PREC, TS, kFeatProfile>(a, grid, waves, lds, st);
@@ -3333,16 +3565,15 @@ int launch_run(RunPlan& p)
     int waves = 0;
     size_t lds = 0;
     int cap = p.emit_waves;
-    if (p.params.precision == 1 && (p.params.grazing_exact || p.params.earth_radius_m > 0.0))
-        cap = std::min(cap, emit_threads(1, kFeatExact) / kWave);
-    // the narrow FP64 build: plain runs (no profile, exact or curved path, node tables)
-    const bool narrow_ok = p.params.precision == 0 && p.prof_bins == 0 && !p.params.grazing_exact &&
-                           p.params.earth_radius_m <= 0.0 && p.atmo->h_nodes.empty();
+    if (p.params.grazing_exact || p.params.earth_radius_m > 0.0)
+        cap = std::min(cap, emit_threads(p.params.precision, kFeatExact) / kWave);
+    const bool many_nodes_ok = p.params.precision == 0 && p.params.waves_per_group == kMaxEmitWaves &&
+                               p.prof_bins == 0 && !p.params.grazing_exact &&
+                               p.params.earth_radius_m <= 0.0 && p.atmo->h_nodes.empty();
     if (int rc = emit_config(p.params.precision, a.n_tel, p.prof_bins, p.atmo, p.tile_segs, cap, &waves,
-                             &lds, narrow_ok))
+                             &lds, many_nodes_ok))
         return rc;
-    if (p.params.precision == 0 && waves > kMaxEmitWaves / 2)
-        a.lds_entries = lds_entries(0, a.n_nodes, true);
+    set_sectors(a, p.atmo, p.arr->rmax, p.arr->dmax);
     if (p.prof_bins > 0) {
         // the profile accumulates by atomics: clear it (a kernel, so the run stays capturable)
         const int64_t m = (int64_t)a.n_showers * p.prof_bins;
@@ -3443,18 +3674,19 @@ int launch_soft(RunPlan& p, const SoftPlan& sp, int mode)
         e.cell_off = ar->soft.d_cell_off;
         e.cell_list = ar->soft.d_cell_list;
         e.cell_ent = reinterpret_cast<const uint2*>(ar->soft.d_cell_ent);
-        e.lds_entries = lds_entries(1, e.n_nodes, true);
+        set_sectors(e, p.atmo, ar->screen_rmax, ar->dmax);
         e.nb_frozen = sp.n_b_frozen;
         e.list_ids = sp.ids;
         e.list_cap = sp.ids_cap;
         e.list_count = sp.ids_count;
         const size_t tab = (table_bytes(1, e.n_nodes, true) + 15) & ~(size_t)15;
-        const size_t per = wave_bytes(1, kSoftTS, e.n_tel, 0) + kScreenWaveBytes;
-        for (int wv = kMaxEmitWaves; wv >= 1 && !e_waves; wv /= 2)
-            if (tab + tel_bytes(e.n_tel) + (size_t)wv * per <= 160 * 1024) {
-                e_waves = wv;
-                e_lds = tab + tel_bytes(e.n_tel) + (size_t)wv * per;
-            }
+        const size_t per = wave_bytes(1, kSoftTS, e.n_tel, 0) + kScreenBuf * sizeof(uint64_t);
+        if (tab + tel_bytes(e.n_tel) + limit_wave_bytes(1, kSoftTS, e.n_tel, 0) + kLimitScreenBytes <= 160 * 1024)
+            for (int wv = kMaxEmitWaves; wv >= 1 && !e_waves; wv /= 2)
+                if (tel_bytes(e.n_tel) + (size_t)wv * per <= 160 * 1024) {
+                    e_waves = wv;
+                    e_lds = tel_bytes(e.n_tel) + (size_t)wv * per;
+                }
         if (!e_waves || e.n_nodes - 1 < 2) {
             set_error("soft response: tables too large for the screening pass");
             return CKV_ERR_TABLE;

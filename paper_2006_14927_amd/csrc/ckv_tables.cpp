@@ -79,10 +79,13 @@ void psi_range(ckv_atmo* a)
 {
     a->psi_min = a->psi_max = a->psi[0];
     a->psi_falls = true;
+    a->psi_slope = 0.0;
     for (size_t i = 1; i < a->psi.size(); ++i) {
         a->psi_min = std::min(a->psi_min, a->psi[i]);
         a->psi_max = std::max(a->psi_max, a->psi[i]);
         if (!(a->psi[i] <= a->psi[i - 1])) a->psi_falls = false;
+        const double width = a->h_nodes.empty() ? a->step : a->h_nodes[i] - a->h_nodes[i - 1];
+        a->psi_slope = std::max(a->psi_slope, std::fabs(a->psi[i] - a->psi[i - 1]) / width);
     }
 }
 
