@@ -146,7 +146,9 @@ size_t workspace_layout(int64_t n_segments, int32_t n_showers, int32_t n_tel, in
     // of order, so a smaller run array could be filled by later tiles and cut the
     // written prefix short)
     const int64_t run_blocks = stage_blocks * kStageBlock / kRunBlock + n_waves + 2;
-    const int64_t run_cap = run_blocks * kRunBlock;
+    // (the last two hold the bunch kernel's claim counters)
+    static_assert(kTileClasses * kClaimStride <= 2 * kRunBlock, "claim counters fit two run blocks");
+    const int64_t run_cap = (run_blocks - 2) * kRunBlock;
     size_t off = 0;
     auto take = [&](size_t bytes) { size_t o = off; off = align256(off + bytes); return o; };
     size_t o_ctrl = take(sizeof(int64_t) * kCtrlSlots);
@@ -157,7 +159,7 @@ size_t workspace_layout(int64_t n_segments, int32_t n_showers, int32_t n_tel, in
     size_t o_roff = take(sizeof(int64_t) * (size_t)max_tiles);
     size_t o_rn = take(sizeof(int32_t) * (size_t)max_tiles);
     size_t o_th = take(sizeof(int32_t) * (size_t)max_tiles);
-    size_t o_runs = take(sizeof(int64_t) * (size_t)run_cap);
+    size_t o_runs = take(sizeof(int64_t) * (size_t)(run_blocks * kRunBlock));
     size_t o_bsum = take(sizeof(int32_t) * (size_t)max_blocks * n_tel);
     size_t o_bh = take(sizeof(int64_t) * (size_t)max_blocks);
     size_t o_st = take(sizeof(int32_t) * (size_t)n_showers * n_tel);
@@ -170,6 +172,7 @@ size_t workspace_layout(int64_t n_segments, int32_t n_showers, int32_t n_tel, in
         plan->max_row_blocks = max_blocks;
         plan->stage_slots = stage_blocks * kStageBlock;
         plan->run_cap = run_cap;
+        plan->claims = (int64_t*)(b + o_runs) + run_cap;
         plan->ctrl = (int64_t*)(b + o_ctrl);
         plan->ws_result = (ckv_result*)(b + o_res);
         plan->tiles_before = (int64_t*)(b + o_tb);
@@ -400,7 +403,10 @@ static int array_create(const double* x_m, const double* y_m, const double* r_m,
         tel[4 * k + 2] = r_m[k];
         tel[4 * k + 3] = r_m[k] * r_m[k];
     }
-    if ((rc = upload(tel.data(), tel.size(), &arr->d_tel)) || (rc = upload_grid(&arr->hit)) ||
+    std::vector<uint32_t> reach;
+    build_reach(arr, &arr->reach, &reach);
+    if ((!reach.empty() && (rc = upload(reach.data(), reach.size(), &arr->reach.d_data))) ||
+        (rc = upload(tel.data(), tel.size(), &arr->d_tel)) || (rc = upload_grid(&arr->hit)) ||
         (sigma > 0.0 && (rc = upload_grid(&arr->soft))) ||
         (sigma > 0.0 && (rc = upload(tel_screen.data(), tel_screen.size(), &arr->d_tel_screen)))) {
         ckv_array_destroy(arr);
@@ -426,6 +432,7 @@ int ckv_array_create_soft(const double* x_m, const double* y_m, const double* r_
 int ckv_array_destroy(ckv_array* arr)
 {
     if (!arr) return CKV_OK;
+    if (arr->reach.d_data) (void)hipFree(arr->reach.d_data);
     if (arr->d_tel) (void)hipFree(arr->d_tel);
     if (arr->d_tel_screen) (void)hipFree(arr->d_tel_screen);
     free_grid(&arr->hit);

@@ -55,10 +55,14 @@ static_assert(sizeof(StageEntry) == 48, "staging entry is 48 bytes");
 constexpr int kRunTelShift = 40;
 constexpr int64_t kRunValueMask = ((int64_t)1 << kRunTelShift) - 1;
 
+// Claim counters of the bunch kernel: tiles claimed past each wave's first, one counter
+// per tile class, each on a 256-byte line of its own.
+constexpr int kTileClasses = 16;
+constexpr int kClaimStride = 32;
+
 // Control block in the workspace (zeroed by the first kernel of a run).  The
 // counters every wave claims from (tiles, staging blocks, run blocks) sit on cache lines of their own: same-line atomics from all waves would
 // serialise in one L2 channel.
-constexpr int kTileClasses = 16;
 enum CtrlSlot {
     kTileCounter = 0,   // next tile to claim (the soft tile kernels)
     kBlockCounter = 32, // next staging block to claim
@@ -74,10 +78,7 @@ enum CtrlSlot {
     kCutBlocks,         // row blocks holding them
     kRecords,           // their crossings
     kDrop0,             // CKV_N_DROP drop counters follow
-    // the bunch kernel's claim counters, kTileClasses of them on lines of their own: tiles
-    // claimed past each wave's first
-    kClaimCounter = 128,
-    kCtrlSlots = kClaimCounter + 32 * kTileClasses
+    kCtrlSlots = kDrop0 + CKV_N_DROP + 4
 };
 
 }  // namespace ckv
@@ -118,12 +119,25 @@ struct ckv_grid {
     uint32_t* d_cell_ent = nullptr;
 };
 
+// Sphere centres near a ground point, for the bunch kernel's step setup: a uniform grid
+// over the ground; per level l and cell, the spheres whose centre is within
+// kReachMin * 2^(l/2) of some point of the cell.  One device buffer: a record
+// {offset, count} per level and cell, then the lists (uint16, each padded to a multiple
+// of kReachPad with 0xFFFF).
+struct ckv_reach {
+    double gx0 = 0, gy0 = 0, inv_cell = 0;
+    int32_t nx = 0, ny = 0;
+    uint32_t* d_data = nullptr;      // null: no grid (few spheres)
+    size_t list_at = 0;              // 32-bit words before the lists
+};
+
 struct ckv_array {
     int device = 0;
     int32_t n_tel = 0;
     std::vector<double> x, y, r;
     double rmax = 0, dmax = 0;       // largest radius, largest distance of a centre from the origin
     double* d_tel = nullptr;         // device, n_tel x 4: X, Y, R, R^2
+    ckv_reach reach;                 // centres near a ground point
     ckv_grid hit;                    // radii R (sphere crossings)
     ckv_grid soft;                   // radii sqrt(R^2 + 2 R sigma z_cut) + margin (soft response)
     double soft_sigma = 0;           // 0: no soft grid
@@ -146,6 +160,14 @@ void psi_range(ckv_atmo* a);
 // depth at the nodes of a (after build_atmo_tables), the same interpolation as eta
 void build_depth_table(const double* alt, const double* depth, int64_t n, ckv_atmo* a);
 int build_array_grid(const ckv_array* arr, const std::vector<double>& radius, ckv_grid* g);
+// data of the reach grid; empty for at most kReachMinTel spheres
+void build_reach(const ckv_array* arr, ckv_reach* g, std::vector<uint32_t>* data);
+constexpr int kReachLevels = 7;      // up to 768 m
+constexpr double kReachMin = 96.0;
+constexpr int kReachPad = 4;
+// a step tests up to this many spheres one by one (16 double rounds of the wave) sooner
+// than it looks its ground point up (two dependent reads) and tests the 4-12 near it
+constexpr int kReachMinTel = 32;
 constexpr double kSoftZCut = 40.0;   // Phi(-40) underflows to exactly 0 in FP64
 // margin of the soft response's screening spheres over the cut radius [m]
 constexpr double kScreenMargin = 0.01;
@@ -194,6 +216,7 @@ struct RunPlan {
     int32_t* tile_run_n;        // max_tiles: runs of the tile
     int32_t* tile_hits;         // max_tiles: crossings of the tile
     int64_t* runs;              // run_cap
+    int64_t* claims;            // the bunch kernel's claim counters (kTileClasses lines)
     int32_t* block_sums;        // n_tel x max_row_blocks (telescope-major)
     int64_t* block_hits;        // max_row_blocks: crossings per row block
     int32_t* shower_tel;        // n_showers x n_tel

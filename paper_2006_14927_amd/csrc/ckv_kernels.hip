@@ -118,6 +118,13 @@ struct Args {
     // slope with altitude (0 where psi is not non-increasing), largest and smallest value
     double sec_rmax, sec_dmax, sec_slope, sec_psi_max, sec_psi_min;
     int32_t sec_falls;          // psi non-increasing with altitude at every node
+    // sphere centres near a ground point (ckv_reach; reach_rec NULL: none)
+    const uint2* reach_rec;
+    const uint2* reach_list;
+    double reach_x0, reach_y0, reach_inv;
+    int32_t reach_nx, reach_ny;
+    int64_t* claims;            // claim counters, kClaimStride apart
+    int32_t static_blocks;      // staging and run blocks dealt to the waves beforehand
 };
 
 // Memory accesses whose address space is explicit.  Where one access may go to LDS
@@ -1088,8 +1095,6 @@ __device__ __forceinline__ TileSetup tile_setup(const Args& a, int64_t g0, int n
             const double kA = cone ? dh0 * st.w : 0.0, kz = dh0 * dh0;
             const double rl = cone ? -(t * st.len + rc) : 0.0;
             constexpr int G = kWave / TS;
-            const int nh = (a.n_tel + G - 1) / G;
-            const int k_first = (lane / TS) * nh, k_last = a.n_tel - 1;
             auto passes = [&](int k) {
                 const double dx = tel_sh[3 * k] - px, dy = tel_sh[3 * k + 1] - py;
                 const double A = fma(dx, du, fma(dy, dv, kA));
@@ -1114,11 +1119,51 @@ __device__ __forceinline__ TileSetup tile_setup(const Args& a, int64_t g0, int n
                 if (np > kWave && lane < np - kWave) pairs[lane] = pairs[kWave + lane];
                 np = np > kWave ? np - kWave : 0;
             };
-            for (int i = 0; i < nh; ++i) {
-                const int k = min(k_first + i, k_last);
-                const bool p = passes(k);
-                if (__ballot(p)) push(p, k);
-                if (np >= kWave || (i + 1 == nh && np > 0)) windows();
+            // spheres near the cone's ground ellipse: a centre d from G, the axis's ground
+            // point, has n >= d w and A <= dh0 / w + d sin(zeta_a), so passing takes
+            // d (w - t sin(zeta_a)) <= t dh0 / w + rc
+            uint2 near{0u, 0u};
+            bool far = a.reach_rec == nullptr;
+            if (!far) {
+                bool above = false;
+                if (cone) {
+                    const double iw = rcp64(st.w), s_a = sqrt(fmax(0.0, (1.0 - st.w) * (1.0 + st.w)));
+                    const double room = st.w - t * s_a;
+                    const float r = (float)(fma(t * dh0, iw, rc) * rcp64(room)) * 1.0001f;
+                    const int lv = max(0, (int)ceilf(2.0f * __log2f(r * (float)(1.0 / kReachMin)) + 1e-3f));
+                    above = !(room > 1e-3) || !(r < (float)kReachMin * 8.0f) || lv >= kReachLevels;
+                    const double fx = (fma(dh0 * iw, du, px) - a.reach_x0) * a.reach_inv;
+                    const double fy = (fma(dh0 * iw, dv, py) - a.reach_y0) * a.reach_inv;
+                    // (a ground point outside the grid is farther than any level's radius)
+                    if (!above && fx >= 0.0 && fy >= 0.0 && fx < (double)a.reach_nx && fy < (double)a.reach_ny)
+                        near = a.reach_rec[(lv * a.reach_nx + (int)fx) * a.reach_ny + (int)fy];
+                }
+                far = __ballot(above) != 0ull;
+            }
+            if (far) {
+                // some step of the tile reaches beyond the lists: all spheres, TS steps at a
+                // time against one sphere per group of lanes
+                const int nh = (a.n_tel + G - 1) / G;
+                const int k_first = (lane / TS) * nh, k_last = a.n_tel - 1;
+                for (int i = 0; i < nh; ++i) {
+                    const int k = min(k_first + i, k_last);
+                    const bool p = passes(k);
+                    if (__ballot(p)) push(p, k);
+                    if (np >= kWave) windows();
+                }
+            } else {
+                const int n4 = ((int)near.y + kReachPad - 1) / kReachPad;
+                for (int i = lane / TS; __ballot(i < n4); i += G) {
+                    uint2 four{0xFFFFFFFFu, 0xFFFFFFFFu};
+                    if (i < n4) four = a.reach_list[near.x / kReachPad + i];
+#pragma unroll
+                    for (int q = 0; q < kReachPad; ++q) {
+                        const int k = (int)(((q < 2 ? four.x : four.y) >> (16 * (q & 1))) & 0xFFFFu);
+                        const bool p = k != 0xFFFF && passes(k);
+                        if (__ballot(p)) push(p, k);
+                        if (np >= kWave) windows();
+                    }
+                }
             }
             while (np > 0) windows();
             wave_lds_sync();
@@ -1299,10 +1344,10 @@ __global__ void __launch_bounds__(emit_threads(PREC, FEAT)) emit_kernel(Args a)
     const double w_graze = __builtin_bit_cast(double, scalar64(__builtin_bit_cast(int64_t,
                                SCREEN ? a.w_min - 1e-6 : a.w_min)));
 
-    int64_t blk = -1;          // current staging block; -1: none yet, -2: staging full
+    int64_t blk = -1;          // current staging block; -1: none, -2: staging full
     int blk_fill = 0;
     bool lost = false;         // a crossing of this wave found no slot (tile marked)
-    int64_t rblk = -1;         // current run block; -1: none yet
+    int64_t rblk = -1;         // current run block; -1: none
     int rfill = 0;
     const int64_t n_tiles = a.ctrl[kNumTiles];
 
@@ -1396,13 +1441,17 @@ __global__ void __launch_bounds__(emit_threads(PREC, FEAT)) emit_kernel(Args a)
     const int n_cls = min(kTileClasses, (int)gridDim.x), cls = (int)blockIdx.x % n_cls;
     const int cls_groups = ((int)gridDim.x - cls + n_cls - 1) / n_cls;
     const int cls_waves = cls_groups * (int)(blockDim.x / kWave);
-    int64_t t_next = cls + (int64_t)n_cls * scalar64(wave * cls_groups + (int)blockIdx.x / n_cls);
+    const int64_t t_first = cls + (int64_t)n_cls * scalar64(wave * cls_groups + (int)blockIdx.x / n_cls);
     for (bool first_tile = true;; first_tile = false) {
-        int64_t t = t_next;
-        if (!first_tile) {
+        int64_t t = t_first;
+        if (first_tile) {
+            // a wave with a first tile has a staging and a run block of its own from the
+            // start (all waves' first claims would queue at the counters: 50 us of a launch)
+            if (t < a.static_blocks && t < n_tiles) blk = rblk = t;
+        } else {
             int64_t i = 0;
             if (lane == 0)
-                i = (int64_t)atomicAdd((unsigned long long*)&a.ctrl[kClaimCounter + 32 * cls], 1ull);
+                i = (int64_t)atomicAdd((unsigned long long*)&a.claims[kClaimStride * cls], 1ull);
             t = cls + n_cls * (cls_waves + scalar64(i));
         }
         if (t >= n_tiles) break;
@@ -2011,6 +2060,8 @@ __global__ void __launch_bounds__(1024) init_kernel(Args a)
     __shared__ int64_t sh_t[1024], sh_b[1024];
     __shared__ int err;
     for (int q = threadIdx.x; q < kCtrlSlots; q += blockDim.x) a.ctrl[q] = 0;
+    if (a.claims)
+        for (int q = threadIdx.x; q < kTileClasses; q += blockDim.x) a.claims[kClaimStride * q] = 0;
     if (threadIdx.x == 0) err = 0;
     __syncthreads();
     const int64_t TS = a.tile_segs;
@@ -2063,6 +2114,9 @@ __global__ void __launch_bounds__(1024) init_kernel(Args a)
         a.ctrl[kNumTiles] = err ? 0 : run_t;
         a.ctrl[kNumRowBlocks] = err ? 0 : run_b;
         a.ctrl[kFirstLost] = err ? 0 : run_t;      // no lost tile yet
+        const int64_t dealt = err ? 0 : min(run_t, (int64_t)a.static_blocks);
+        a.ctrl[kBlockCounter] = dealt;
+        a.ctrl[kRunCounter] = dealt;
         if (a.result) {
             // the bunch path's finalize fills the rest; the soft entry points report
             // the error word only
@@ -3449,6 +3503,16 @@ Args make_args(const RunPlan& p)
         a.cell_off = ar->hit.d_cell_off;
         a.cell_list = ar->hit.d_cell_list;
         a.cell_ent = reinterpret_cast<const uint2*>(ar->hit.d_cell_ent);
+        const ckv_reach& rg = ar->reach;
+        if (rg.d_data) {
+            a.reach_rec = reinterpret_cast<const uint2*>(rg.d_data);
+            a.reach_list = reinterpret_cast<const uint2*>(rg.d_data + rg.list_at);
+            a.reach_x0 = rg.gx0;
+            a.reach_y0 = rg.gy0;
+            a.reach_inv = rg.inv_cell;
+            a.reach_nx = rg.nx;
+            a.reach_ny = rg.ny;
+        }
     }
     a.bunch_size = p.params.bunch_size;
     a.k_ft = p.k_ft;
@@ -3464,6 +3528,7 @@ Args make_args(const RunPlan& p)
     a.cur_step = p.cursor.step;
     a.cur_shower = p.cursor.shower;
     a.ctrl = p.ctrl;
+    a.claims = p.claims;
     a.tiles_before = p.tiles_before;
     a.blocks_before = p.blocks_before;
     a.shower_first = p.shower_first;
@@ -3590,8 +3655,6 @@ int launch_run(RunPlan& p)
 {
     Args a = make_args(p);
     hipStream_t st = p.stream;
-    init_kernel<<<1, 1024, 0, st>>>(a);
-    if (int rc = check_launch("init")) return rc;
     int waves = 0;
     size_t lds = 0;
     int cap = p.emit_waves;
@@ -3604,6 +3667,15 @@ int launch_run(RunPlan& p)
                              &lds, many_nodes_ok))
         return rc;
     set_sectors(a, p.atmo, p.arr->rmax, p.arr->dmax);
+    // a block per wave of the launch, as far as the workspace holds them beside the claims'
+    // (a grid of whole class rounds: the waves' first tiles are then 0 .. waves - 1, each
+    // block with an owner that leaves its fill)
+    a.static_blocks = p.emit_grid % kTileClasses != 0
+                          ? 0
+                          : (int32_t)std::min<int64_t>((int64_t)p.emit_grid * waves,
+                                                       std::min(a.stage_blocks, p.run_cap / kRunBlock));
+    init_kernel<<<1, 1024, 0, st>>>(a);
+    if (int rc = check_launch("init")) return rc;
     if (p.prof_bins > 0) {
         // the profile accumulates by atomics: clear it (a kernel, so the run stays capturable)
         const int64_t m = (int64_t)a.n_showers * p.prof_bins;

@@ -196,6 +196,59 @@ int build_array_grid(const ckv_array* arr, const std::vector<double>& radius, ck
     return CKV_OK;
 }
 
+void build_reach(const ckv_array* arr, ckv_reach* g, std::vector<uint32_t>* data)
+{
+    const int32_t n = arr->n_tel;
+    data->clear();
+    if (n <= kReachMinTel) return;
+    auto radius = [](int l) { return kReachMin * std::pow(2.0, 0.5 * l); };
+    const double top = radius(kReachLevels - 1);
+    const auto mx = std::minmax_element(arr->x.begin(), arr->x.end());
+    const auto my = std::minmax_element(arr->y.begin(), arr->y.end());
+    const double extent = std::max(*mx.second - *mx.first, *my.second - *my.first) + 2.0 * top;
+    // centres too far apart for a grid of this kind: the step setup tests them all
+    if (!(extent < 1e6)) return;
+    const double cell = std::max(64.0, extent / 128.0), margin = 0.01 + 1e-9 * extent;
+    g->gx0 = *mx.first - top - margin;
+    g->gy0 = *my.first - top - margin;
+    g->inv_cell = 1.0 / cell;
+    g->nx = (int32_t)std::floor((*mx.second + top + margin - g->gx0) / cell) + 1;
+    g->ny = (int32_t)std::floor((*my.second + top + margin - g->gy0) / cell) + 1;
+    const size_t n_cells = (size_t)g->nx * g->ny;
+    std::vector<std::vector<uint16_t>> lists(kReachLevels * n_cells);
+    for (int l = 0; l < kReachLevels; ++l) {
+        const double reach = radius(l) + margin;
+        for (int32_t k = 0; k < n; ++k) {
+            const int32_t x0 = std::max(0, (int32_t)std::floor((arr->x[k] - reach - g->gx0) / cell));
+            const int32_t x1 = std::min(g->nx - 1, (int32_t)std::floor((arr->x[k] + reach - g->gx0) / cell));
+            const int32_t y0 = std::max(0, (int32_t)std::floor((arr->y[k] - reach - g->gy0) / cell));
+            const int32_t y1 = std::min(g->ny - 1, (int32_t)std::floor((arr->y[k] + reach - g->gy0) / cell));
+            for (int32_t ix = x0; ix <= x1; ++ix)
+                for (int32_t iy = y0; iy <= y1; ++iy) {
+                    const double cx = g->gx0 + ix * cell, cy = g->gy0 + iy * cell;
+                    const double dx = std::max({cx - arr->x[k], 0.0, arr->x[k] - (cx + cell)});
+                    const double dy = std::max({cy - arr->y[k], 0.0, arr->y[k] - (cy + cell)});
+                    if (dx * dx + dy * dy <= reach * reach)
+                        lists[l * n_cells + (size_t)ix * g->ny + iy].push_back((uint16_t)k);
+                }
+        }
+    }
+    std::vector<uint16_t> flat;
+    data->resize(2 * lists.size());
+    for (size_t c = 0; c < lists.size(); ++c) {
+        (*data)[2 * c] = (uint32_t)flat.size();
+        (*data)[2 * c + 1] = (uint32_t)lists[c].size();
+        flat.insert(flat.end(), lists[c].begin(), lists[c].end());
+        while (flat.size() % kReachPad) flat.push_back(0xFFFF);
+    }
+    // (8-byte reads of the lists: kReachPad entries, from an even word)
+    static_assert(kReachPad * sizeof(uint16_t) == 8, "one 8-byte read per kReachPad entries");
+    g->list_at = data->size();
+    const size_t words = flat.size() / 2;
+    data->resize(g->list_at + words);
+    if (words) std::memcpy(data->data() + g->list_at, flat.data(), words * sizeof(uint32_t));
+}
+
 // ---------------------------------------------------------------------------
 // Parameterised atmosphere (differentiation pattern):
 //   log eta(h) = log eta0 - sum_l overlap([0, h], layer l) / H_l + Lambda(h),
