@@ -124,7 +124,8 @@ struct Args {
     double reach_x0, reach_y0, reach_inv;
     int32_t reach_nx, reach_ny;
     int64_t* claims;            // claim counters, kClaimStride apart
-    int32_t static_blocks;      // staging and run blocks dealt to the waves beforehand
+    int32_t grid_waves;         // waves of the bunch kernel's launch
+    int32_t static_blocks;      // staging and run blocks dealt to them beforehand
 };
 
 // Memory accesses whose address space is explicit.  Where one access may go to LDS
@@ -136,6 +137,15 @@ using LdsF64 = __attribute__((address_space(3))) double;
 using HbmF64 = __attribute__((address_space(1))) double;
 using LdsF32x4 = __attribute__((address_space(3))) f32x4;
 using HbmF32x4 = __attribute__((address_space(1))) f32x4;
+
+// The launch's argument block at the address the kernel passes to a called function:
+// wave-uniform and read-only, so the function reads it with scalar loads.
+__device__ __forceinline__ const Args& args_from(uint64_t at)
+{
+    const uint64_t u = ((uint64_t)(uint32_t)__builtin_amdgcn_readfirstlane((int)(at >> 32)) << 32) |
+                       (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)at);
+    return *(const Args*)reinterpret_cast<const __attribute__((address_space(4))) Args*>(u);
+}
 
 __device__ __forceinline__ const LdsF64* as_lds(const double* p) { return (const LdsF64*)p; }
 __device__ __forceinline__ const HbmF64* as_hbm(const double* p) { return (const HbmF64*)p; }
@@ -615,6 +625,32 @@ __device__ __forceinline__ int propagate_curved(const Args& a, double xe, double
     return -1;
 }
 
+// The two slow propagations as called functions: their loops over the cells then keep
+// their constants in scalar registers of their own (inline, the bunch kernel's spilled
+// ones came back by lane reads in every cell: 24 % more instructions).
+struct SlowRay {
+    int status;
+    double xg, yg, T, uo, vo;    // uo, vo: curved; flat: uo holds n_e
+};
+
+static __device__ __noinline__ SlowRay propagate_curved_call(uint64_t args_at, double xe, double ye, double ze, double he,
+                                                             double u, double v, double w)
+{
+    SlowRay r;
+    r.status = propagate_curved(args_from(args_at), xe, ye, ze, he, u, v, w, r.xg, r.yg, r.T, r.uo, r.vo);
+    return r;
+}
+
+static __device__ __noinline__ SlowRay propagate_exact_call(uint64_t args_at, double xe, double ye, double he, double u,
+                                                            double v, double w)
+{
+    SlowRay r;
+    r.status = -1;
+    r.vo = 0.0;
+    propagate_exact(args_from(args_at), xe, ye, he, u, v, w, r.xg, r.yg, r.T, r.uo);
+    return r;
+}
+
 // Depth bin of an emission altitude h_obs <= h < h_top, given its table cell c
 // and fraction f (x = (h - h_obs) / step, c = floor(x), f = x - c): the depth
 // table read like the index and binned by floor(X * (1/width)), in FP64
@@ -637,7 +673,7 @@ struct alignas(16) StepEntry<1> {
     double x0, y0, h0, t0, u, v, w, cos_t, ds, inv_bc;
     double photons;  // FP64: the longitudinal profile sums it
     float sb1x, sb1y, sb1z, sb2x, sb2y, sb2z;
-    int32_t sidx;   // index of the step inside the tile
+    int32_t sidx;   // lane of the step in its unit (modulo the tile size: step in the tile)
     uint32_t ctr1;  // counter word 1 of the step's random numbers
 };
 static_assert(sizeof(StepEntry<1>) == 128, "step entry size");
@@ -647,6 +683,7 @@ struct alignas(16) StepEntry<0> {
     double x0, y0, h0, t0, u, v, w, cos_t, ds, inv_bc;
     double sb1x, sb1y, sb1z, sb2x, sb2y, sb2z, photons;
     int32_t sidx;
+    uint32_t ctr1;
 };
 static_assert(sizeof(StepEntry<0>) == 144, "step entry size");
 
@@ -685,16 +722,19 @@ __host__ __device__ inline size_t table_bytes(int prec, int n_nodes, bool part)
     return (size_t)n * (prec == 0 ? kNode64 * sizeof(double) : kCell32 * sizeof(float));
 }
 
+// Steps with bunches in the pass that a wave keeps records of at a time.
+__host__ __device__ constexpr int stash_steps(int tile_segs) { return tile_segs > 32 ? tile_segs : 32; }
+
 __host__ __device__ inline size_t wave_bytes(int prec, int tile_segs, int n_tel, int prof_bins)
 {
-    size_t b = (size_t)tile_segs * (prec == 0 ? sizeof(StepEntry<0>) : sizeof(StepEntry<1>));
-    b += (size_t)tile_segs * (kSectorWords * sizeof(uint32_t) + sizeof(StepPass));
+    size_t b = (size_t)stash_steps(tile_segs) *
+               ((prec == 0 ? sizeof(StepEntry<0>) : sizeof(StepEntry<1>)) + sizeof(StepPass));
+    b += (size_t)kWave * kSectorWords * sizeof(uint32_t);
     b += (size_t)kQueue * (sizeof(uint32_t) + sizeof(uint8_t));  // queue (tile setup: pairs)
     b += kWave * sizeof(int32_t);                       // flag row
-    if (prec == 0) b += (size_t)tile_segs * sizeof(uint32_t);   // counter words (FP64 path)
     b += (size_t)kWcCount * sizeof(int64_t);            // counters
     b += ((size_t)n_tel * sizeof(int32_t) + 15) & ~(size_t)15;   // telescope counters
-    b += (size_t)prof_bins * (sizeof(double) + sizeof(uint32_t));  // profile of the tile
+    if (prof_bins) b += 2 * sizeof(int64_t) + (size_t)prof_bins * (sizeof(double) + sizeof(uint32_t));
     return (b + 15) & ~(size_t)15;
 }
 
@@ -836,29 +876,29 @@ __device__ __forceinline__ bool annulus_holds_centre(const double* tel, int n_te
 // A wave's area in the bunch kernel's LDS.
 template <int PREC, int TS>
 struct WaveArea {
-    StepEntry<PREC>* stash;    // steps of the tile with bunches in the pass, compacted
-    uint32_t* masks;           // kSectorWords per step of the tile
+    StepEntry<PREC>* stash;    // steps with bunches in the pass, compacted
     StepPass* pass;            // compacted like the stash
+    uint32_t* masks;           // kSectorWords per step of the unit
     uint32_t* qk;              // waiting bunches: bunch in its step ...
-    uint8_t* qs;               // ... and stash entry; tile setup: (sphere << 8) | step pairs
+    uint8_t* qs;               // ... and stash entry; setup: (sphere << 8) | step pairs
     int32_t* flags;
-    uint32_t* sctr;            // FP64 path: counter word per step of the tile
     int64_t* wcnt;
     int32_t* tcount;
-    double* hph;               // profile of the current tile: photons (FP64) and bunches
+    int64_t* prof;             // profile: shower of the bins below (-1: none), their bunches
+    double* hph;               // photons (FP64) and bunches per depth bin
     uint32_t* hbu;
     __device__ __forceinline__ WaveArea(unsigned char* at, int n_tel, int prof_bins)
     {
         auto take = [&](size_t b) { unsigned char* q = at; at += b; return q; };
-        stash = reinterpret_cast<StepEntry<PREC>*>(take(TS * sizeof(StepEntry<PREC>)));
-        masks = reinterpret_cast<uint32_t*>(take(TS * kSectorWords * sizeof(uint32_t)));
-        pass = reinterpret_cast<StepPass*>(take(TS * sizeof(StepPass)));
+        stash = reinterpret_cast<StepEntry<PREC>*>(take(stash_steps(TS) * sizeof(StepEntry<PREC>)));
+        pass = reinterpret_cast<StepPass*>(take(stash_steps(TS) * sizeof(StepPass)));
+        masks = reinterpret_cast<uint32_t*>(take(kWave * kSectorWords * sizeof(uint32_t)));
         qk = reinterpret_cast<uint32_t*>(take(kQueue * sizeof(uint32_t)));
         qs = take(kQueue);
         flags = reinterpret_cast<int32_t*>(take(kWave * sizeof(int32_t)));
-        sctr = reinterpret_cast<uint32_t*>(take(PREC == 0 ? TS * sizeof(uint32_t) : 0));
         wcnt = reinterpret_cast<int64_t*>(take(kWcCount * sizeof(int64_t)));
         tcount = reinterpret_cast<int32_t*>(take(((size_t)n_tel * sizeof(int32_t) + 15) & ~(size_t)15));
+        prof = reinterpret_cast<int64_t*>(take(prof_bins ? 2 * sizeof(int64_t) : 0));
         hph = reinterpret_cast<double*>(take(prof_bins * sizeof(double)));
         hbu = reinterpret_cast<uint32_t*>(at);
     }
@@ -974,13 +1014,14 @@ __device__ __forceinline__ bool light_cone(const Args& a, const Setup& st, doubl
     return dh0 - st.len * w > a.sec_rmax + base + 1.0;
 }
 
-// What the windows need of a step (in its stash entry's room during the tile setup).
-struct alignas(16) ConeStep {
+// What the windows need of a step (in the stash's room during the setup).
+struct ConeStep {
     double px, py;
     float b1x, b1y, b1z, b2x, b2y, b2z;
     float u, v, w, dh0, t, ict, len, base;
 };
-static_assert(sizeof(ConeStep) <= sizeof(StepEntry<1>), "cone steps share the stash's room");
+static_assert(kWave * sizeof(ConeStep) <= stash_steps(32) * (sizeof(StepEntry<1>) + sizeof(StepPass)),
+              "cone steps share the room of the stash and the pass");
 
 // Sectors of step c's azimuths whose light may reach sphere (X, Y, R^2), or-ed into its
 // mask words.  FP32: its errors are inside light_cone's margin and the 2e-5 turns here.
@@ -1014,36 +1055,144 @@ __device__ __forceinline__ void add_window(const ConeStep& c, double X, double Y
     }
 }
 
-// Step setups of a tile: the bunch counts, which steps' light can reach a sphere and at
-// which azimuths, the records of the steps that stay and the step-level counters.
-// Lane l sets up step l mod TS (the lanes past TS repeat it and share the search over
-// the spheres).  Called by the whole wave.
+// Longitudinal profile: the wave's bins to their shower's row.  Called by the whole wave.
+template <typename Area>
+__device__ __forceinline__ void flush_profile(const Args& a, const Area& wa, int lane)
+{
+    const int64_t s = wa.prof[0];
+    for (int kk = lane; kk < a.prof_bins; kk += kWave) {
+        const uint32_t c = wa.hbu[kk];
+        if (c) {
+            atomicAdd(&a.prof_ph[s * a.prof_bins + kk], wa.hph[kk]);
+            atomicAdd((unsigned long long*)&a.prof_bu[s * a.prof_bins + kk], (unsigned long long)c);
+            wa.hph[kk] = 0.0;
+            wa.hbu[kk] = 0u;
+        }
+    }
+    wave_lds_sync();
+    if (lane == 0) wa.prof[1] = 0;
+}
+
+// A step's bunches into the depth bins, one step per lane.  The depth at a bunch's emission
+// point is monotonic along the step and sub-step k holds bunch k, so a range of sub-steps
+// whose ends lie in one bin (with 1e-6 m to spare, far above the rounding of a bunch's
+// altitude) is counted at once; only a bunch whose sub-step holds a bin's edge, or an end
+// of the table, takes its random number.  20 g/cm^2 bins hold 95 % of the steps whole.
+template <typename Area>
+__device__ __forceinline__ void profile_step(const Args& a, const Setup& st, int32_t nb, uint32_t ctr1,
+                                             uint32_t shower_id, const Area& wa)
+{
+    auto depth = [&](double h) {
+        const double x = (h - a.h_obs) * a.inv_step;
+        const int c = max(0, min((int)x, a.n_nodes - 2));
+        const double f = x - (double)c;
+        return a.depth[c] + f * (a.depth[c + 1] - a.depth[c]);
+    };
+    auto bin = [&](double X) { return max(0, min((int)floor(X * a.inv_bin), a.prof_bins - 1)); };
+    constexpr double slack = 1e-6;
+    constexpr int kOutside = -1, kMixed = -2;
+    // bin of all of sub-steps [ka, kb), kOutside (none of them counted) or kMixed
+    auto bin_of = [&](int32_t ka, int32_t kb) {
+        const double ha = st.h0 - ((double)ka * st.ds) * st.w, hb = st.h0 - ((double)kb * st.ds) * st.w;
+        const double up = fmax(ha, hb) + slack, down = fmin(ha, hb) - slack;
+        if (up < a.h_obs || down >= a.h_top) return kOutside;
+        if (down < a.h_obs || up >= a.h_top) return kMixed;
+        const int b = bin(depth(up) * (1.0 - 1e-13));
+        return b == bin(depth(down) * (1.0 + 1e-13)) ? b : kMixed;
+    };
+    auto add = [&](int b, int32_t n) {
+        if (b < 0) return;
+        atomicAdd(&wa.hph[b], (double)n * st.photons);
+        atomicAdd(&wa.hbu[b], (uint32_t)n);
+    };
+    int32_t k = 0;
+    while (k < nb) {
+        int b = bin_of(k, nb);
+        int32_t end = nb;
+        if (b == kMixed) {
+            // the longest range from k in one bin: first where a linear depth puts the
+            // edge, then by halving
+            int32_t lo = k, hi = nb;
+            const double Xk = depth(fmax(fmin(st.h0 - ((double)k * st.ds) * st.w, a.h_top), a.h_obs));
+            const double Xe = depth(fmax(fmin(st.h0 - ((double)nb * st.ds) * st.w, a.h_top), a.h_obs));
+            const double edge = (floor(Xk * a.inv_bin) + (Xe > Xk ? 1.0 : 0.0)) / a.inv_bin;
+            const double part = Xe != Xk ? (edge - Xk) / (Xe - Xk) : 0.5;
+            int32_t mid = k + (int32_t)(fmin(fmax(part, 0.0), 1.0) * (double)(nb - k));
+            for (int probe = 0; hi - lo > 1; ++probe) {
+                mid = max(lo + 1, min(mid, hi - 1));
+                const int bm = bin_of(k, mid);
+                if (bm != kMixed) { lo = mid; b = bm; } else { hi = mid; }
+                mid = probe == 0 ? (bm != kMixed ? lo + 1 : hi - 1) : lo + (hi - lo) / 2;
+            }
+            end = lo;
+        }
+        if (end > k) add(b, end - k);
+        k = end;
+        if (k < nb) {
+            // bunch k by its own emission point, as the bunch loop computes it
+            uint32_t r[4];
+            philox4x32_10((uint32_t)k, ctr1, shower_id, 0u, a.key0, a.key1, r);
+            const double u0 = fma((double)r[0], 2.3283064365386963e-10, 1.1641532182693481e-10);
+            const double s_along = ((double)k + u0) * st.ds;
+            double he;
+            {
+#pragma clang fp contract(off)
+                he = st.h0 - s_along * st.w;
+            }
+            const double xcell = (he - a.h_obs) * a.inv_step;
+            const int ci = min((int)xcell, a.n_nodes - 2);
+            if (he >= a.h_obs && he < a.h_top) add(profile_bin(a, ci, xcell - (double)ci), 1);
+            ++k;
+        }
+    }
+}
+
+// Step setups of a unit, 1 or 64 / TS consecutive tiles (h_all), one step per lane: the
+// bunch counts, which steps' light can reach a sphere and at which azimuths, the records
+// of the steps that stay and the step-level counters.  With one tile the lanes past its
+// steps repeat them and share the search over the spheres.  It covers the unit's tiles
+// from h_first on, as many whole ones as the stash has room for; the caller comes back
+// for the rest.  Called by the whole wave.
 struct TileSetup {
-    int32_t total;      // bunches in the pass
-    int32_t excl;       // first of this lane's step
-    bool in_pass;       // this lane's step has bunches in the pass
-    bool direct;        // every bunch in the pass is taken, whatever its azimuth
+    int32_t excl, incl;      // bunches of the pass before this lane's step, and through it
+    int32_t shower;          // of this lane's tile
+    bool in_pass;            // this lane's step has bunches in the pass
+    bool masked;             // and they are taken by azimuth
+    int32_t h_end;           // tiles h_first .. h_end - 1 are covered
 };
 
 template <int PREC, int TS, int FEAT>
-__device__ __forceinline__ TileSetup tile_setup(const Args& a, int64_t g0, int nseg, int64_t seg_id0,
-                                                uint32_t shower_id, int lane, uint64_t lt_mask,
-                                                const WaveArea<PREC, TS>& wa, const double* tel_sh)
+__device__ __forceinline__ TileSetup tile_setup(const Args& a, int64_t t0, int h_first, int h_all, int lane,
+                                                uint64_t lt_mask, const WaveArea<PREC, TS>& wa,
+                                                const double* tel_sh)
 {
     constexpr bool SCREEN = (FEAT & kFeatScreen) != 0;
     constexpr bool PROF = (FEAT & kFeatProfile) != 0;
     constexpr bool CURVED = (FEAT & kFeatCurved) != 0;
     using T = typename std::conditional<PREC == 0, double, float>::type;
     using Entry = StepEntry<PREC>;
-    const int l = lane & (TS - 1);
-    const bool own = lane < TS;
+    // this lane's tile, its shower and its step
+    const int l = lane & (TS * h_all - 1), h = l / TS;
+    const bool own = lane == l;
+    const bool covered = h >= h_first;
+    const int64_t t = t0 + (covered ? h : h_first);
+    int s = 0;
+    for (int hi = a.n_showers; hi - s > 1;) {     // tiles_before[s] <= t < tiles_before[hi]
+        const int mid = (s + hi) >> 1;
+        if (a.tiles_before[mid] <= t) s = mid; else hi = mid;
+    }
+    const int64_t seg0 = a.seg_offsets[s], seg1 = a.seg_offsets[s + 1];
+    const int64_t g = a.shower_first[s] + (t - a.tiles_before[s]) * (int64_t)TS + (l & (TS - 1));
+    const uint32_t shower_id = a.shower_ids ? a.shower_ids[s] : (uint32_t)s;
     int64_t nb = 0;
     int status = -2;   // -2: no step in this lane
     Setup st;
-    if (l < nseg) {
+    uint32_t ctr1 = 0;
+    if (covered && g < seg1) {
         // screening: the frozen count loaded with the step's inputs, not after them
-        const int64_t f = SCREEN ? a.nb_frozen[g0 + l] : 0;
-        step_setup(a, g0 + l, st);
+        const int64_t f = SCREEN ? a.nb_frozen[g] : 0;
+        ctr1 = a.step_id ? a.step_id[g] : (uint32_t)((a.seg_id_base ? a.seg_id_base[s] : 0) + (g - seg0));
+        step_setup(a, g, st);
         status = st.status;
         if (st.status < 0) nb = st.nb;
         if (SCREEN && st.status < 0) {
@@ -1058,11 +1207,17 @@ __device__ __forceinline__ TileSetup tile_setup(const Args& a, int64_t g0, int n
             }
         }
     }
-    const int64_t total_all = scalar64(wave_last(wave_incl_scan(own ? nb : 0)));
-    if (total_all >= ((int64_t)1 << 30)) {
+    const int l_first = l & ~(TS - 1), l_last = l | (TS - 1);
+    int64_t tile_nb;
+    {
+        const int64_t n = own ? nb : 0, c = wave_incl_scan(n);
+        tile_nb = __shfl(c, l_last) - __shfl(c - n, l_first);
+    }
+    const bool over = tile_nb >= ((int64_t)1 << 30);
+    if (over) {
         // bunch offsets inside a tile are 32-bit: refuse such a tile
-        if (lane == 0 && a.result) atomicOr(&a.result->error, 2);
         nb = 0;
+        tile_nb = 0;
         status = status == -1 ? -3 : status;
     }
     const bool emits = status == -1;
@@ -1074,9 +1229,9 @@ __device__ __forceinline__ TileSetup tile_setup(const Args& a, int64_t g0, int n
         double px = 0.0, py = 0.0, base = 0.0;
         if (live) cone = light_cone<CURVED, SCREEN>(a, st, px, py, base);
         if (__ballot(cone)) {
-            for (int q = lane; q < TS * kSectorWords; q += kWave) wa.masks[q] = 0u;
+            for (int q = lane; q < TS * h_all * kSectorWords; q += kWave) wa.masks[q] = 0u;
             const double ict = cone ? rcp64(st.cos_t) : 0.0;
-            const double t = cone ? st.sin_t * ict : 0.0;
+            const double tn = cone ? st.sin_t * ict : 0.0;
             const double dh0 = cone ? st.h0 - a.h_obs : 0.0;
             ConeStep* cs = reinterpret_cast<ConeStep*>(wa.stash);
             if (cone && own) {
@@ -1086,28 +1241,22 @@ __device__ __forceinline__ TileSetup tile_setup(const Args& a, int64_t g0, int n
                 c.b2x = (float)st.b2x; c.b2y = (float)st.b2y; c.b2z = (float)st.b2z;
                 c.u = (float)st.u; c.v = (float)st.v; c.w = (float)st.w;
                 c.dh0 = (float)dh0;
-                c.t = (float)t; c.ict = (float)ict; c.len = (float)st.len; c.base = (float)base * 1.00001f;
+                c.t = (float)tn; c.ict = (float)ict; c.len = (float)st.len; c.base = (float)base * 1.00001f;
             }
             wave_lds_sync();
             uint32_t* pairs = wa.qk;
             const double du = cone ? st.u : 0.0, dv = cone ? st.v : 0.0;
             const double rc = cone ? (a.sec_rmax + base) * ict : -1.0;
             const double kA = cone ? dh0 * st.w : 0.0, kz = dh0 * dh0;
-            const double rl = cone ? -(t * st.len + rc) : 0.0;
-            constexpr int G = kWave / TS;
+            const double rl = cone ? -(tn * st.len + rc) : 0.0;
             auto passes = [&](int k) {
                 const double dx = tel_sh[3 * k] - px, dy = tel_sh[3 * k + 1] - py;
                 const double A = fma(dx, du, fma(dy, dv, kA));
                 const double n2 = fma(-A, A, fma(dx, dx, fma(dy, dy, kz)));
-                const double hi = fma(t, A, rc), lo = fmax(fma(t, A, rl), 0.0);
+                const double hi = fma(tn, A, rc), lo = fmax(fma(tn, A, rl), 0.0);
                 return cone && fma(-hi, hi, n2) <= 0.0 && fma(-lo, lo, n2) >= 0.0;
             };
             int np = 0;
-            auto push = [&](bool p, int k) {
-                const uint64_t m = __ballot(p);
-                if (p) pairs[np + __popcll(m & lt_mask)] = ((uint32_t)k << 8) | (uint32_t)l;
-                np += __popcll(m);
-            };
             auto windows = [&]() {
                 wave_lds_sync();
                 if (lane < np) {
@@ -1128,8 +1277,8 @@ __device__ __forceinline__ TileSetup tile_setup(const Args& a, int64_t g0, int n
                 bool above = false;
                 if (cone) {
                     const double iw = rcp64(st.w), s_a = sqrt(fmax(0.0, (1.0 - st.w) * (1.0 + st.w)));
-                    const double room = st.w - t * s_a;
-                    const float r = (float)(fma(t * dh0, iw, rc) * rcp64(room)) * 1.0001f;
+                    const double room = st.w - tn * s_a;
+                    const float r = (float)(fma(tn * dh0, iw, rc) * rcp64(room)) * 1.0001f;
                     const int lv = max(0, (int)ceilf(2.0f * __log2f(r * (float)(1.0 / kReachMin)) + 1e-3f));
                     above = !(room > 1e-3) || !(r < (float)kReachMin * 8.0f) || lv >= kReachLevels;
                     const double fx = (fma(dh0 * iw, du, px) - a.reach_x0) * a.reach_inv;
@@ -1140,29 +1289,29 @@ __device__ __forceinline__ TileSetup tile_setup(const Args& a, int64_t g0, int n
                 }
                 far = __ballot(above) != 0ull;
             }
-            if (far) {
-                // some step of the tile reaches beyond the lists: all spheres, TS steps at a
-                // time against one sphere per group of lanes
-                const int nh = (a.n_tel + G - 1) / G;
-                const int k_first = (lane / TS) * nh, k_last = a.n_tel - 1;
-                for (int i = 0; i < nh; ++i) {
-                    const int k = min(k_first + i, k_last);
-                    const bool p = passes(k);
-                    if (__ballot(p)) push(p, k);
-                    if (np >= kWave) windows();
-                }
-            } else {
-                const int n4 = ((int)near.y + kReachPad - 1) / kReachPad;
-                for (int i = lane / TS; __ballot(i < n4); i += G) {
-                    uint2 four{0xFFFFFFFFu, 0xFFFFFFFFu};
-                    if (i < n4) four = a.reach_list[near.x / kReachPad + i];
+            // candidates 4 at a time: the lane's next list entries, or, when some step of the
+            // unit reaches beyond the lists, all spheres in order
+            const int n4 = far ? (a.n_tel + kReachPad - 1) / kReachPad : ((int)near.y + kReachPad - 1) / kReachPad;
+            const int groups = kWave / (TS * h_all);
+            for (int i = lane / (TS * h_all); __ballot(i < n4); i += groups) {
+                uint2 four{0xFFFFFFFFu, 0xFFFFFFFFu};
+                if (!far && i < n4) four = a.reach_list[near.x / kReachPad + i];
+                uint32_t p4 = 0;
 #pragma unroll
-                    for (int q = 0; q < kReachPad; ++q) {
-                        const int k = (int)(((q < 2 ? four.x : four.y) >> (16 * (q & 1))) & 0xFFFFu);
-                        const bool p = k != 0xFFFF && passes(k);
-                        if (__ballot(p)) push(p, k);
-                        if (np >= kWave) windows();
-                    }
+                for (int q = 0; q < kReachPad; ++q) {
+                    int k = (int)(((q < 2 ? four.x : four.y) >> (16 * (q & 1))) & 0xFFFFu);
+                    if (far) k = kReachPad * i + q;
+                    if (i < n4 && k < a.n_tel && passes(k)) p4 |= 1u << q;
+                }
+                while (__ballot(p4 != 0u)) {
+                    const int q = p4 ? __builtin_ctz(p4) : 0;
+                    const int k = far ? kReachPad * i + q
+                                      : (int)(((q < 2 ? four.x : four.y) >> (16 * (q & 1))) & 0xFFFFu);
+                    const uint64_t m = __ballot(p4 != 0u);
+                    if (p4) pairs[np + __popcll(m & lt_mask)] = ((uint32_t)k << 8) | (uint32_t)l;
+                    np += __popcll(m);
+                    p4 &= p4 - 1;
+                    if (np >= kWave) windows();
                 }
             }
             while (np > 0) windows();
@@ -1177,26 +1326,40 @@ __device__ __forceinline__ TileSetup tile_setup(const Args& a, int64_t g0, int n
             wave_lds_sync();
         }
     }
-    const bool direct = __ballot(live && cone && (PROF || seen)) == 0ull;
-    // steps the bunch loop's first pass walks: all that emit when the profile counts them
-    const bool in_pass = own && live && (PROF || seen);
-    if (in_pass && !cone && !direct) {
+    // ---- the tiles covered now: whole ones, while their steps in the pass fit the stash and
+    // their bunches 30 bits (the profile's bins are one shower's)
+    bool in_pass = own && live && seen;
+    int h_end = h_first;
+    {
+        const uint64_t stay = __ballot(in_pass);
+        int64_t sum = 0;
+        int n = 0;
+        for (; h_end < h_all; ++h_end) {
+            const int l0 = h_end * TS;
+            n += __popcll((stay >> l0) & (~0ull >> (64 - TS)));
+            sum += scalar64(__shfl(tile_nb, l0));
+            if (h_end > h_first && (n > stash_steps(TS) || sum >= ((int64_t)1 << 30))) break;
+            if (PROF && __shfl(s, l0) != __shfl(s, h_first * TS)) break;
+        }
+    }
+    const bool now = own && covered && h < h_end;
+    in_pass = in_pass && now;
+    if (over && now && lane == l_first && a.result) atomicOr(&a.result->error, 2);
+    const bool masked = in_pass && cone;
+    const uint64_t tile_masked = (__ballot(masked) >> l_first) & (~0ull >> (64 - TS));
+    if (in_pass && !cone && tile_masked) {
         // no bound for this step: every azimuth
 #pragma unroll
-        for (int q = 0; q < kSectorWords; ++q) wa.masks[kSectorWords * l + q] = 0xFFFFFFFFu;
+        for (int q = 0; q < kSectorWords; ++q) wa.masks[kSectorWords * lane + q] = 0xFFFFFFFFu;
     }
-    const int64_t nbp = in_pass ? nb : 0;
-    const int64_t incl = wave_incl_scan(nbp);
-    const int32_t total = __builtin_amdgcn_readfirstlane((int)wave_last(incl));
-    const int excl = (int)(incl - nbp);      // first bunch of this lane's step
+    const int32_t nbp = in_pass ? (int32_t)nb : 0;
+    const int32_t incl = (int32_t)wave_incl_scan((int64_t)nbp);
+    const int32_t excl = incl - nbp;      // first bunch of this lane's step
     const uint64_t pass_mask = __ballot(in_pass);
     if (in_pass) {
         const int at = __popcll(pass_mask & lt_mask);
         Entry& e = wa.stash[at];
-        const int64_t g = g0 + lane;
-        const uint32_t ctr1 = a.step_id ? a.step_id[g] : (uint32_t)(seg_id0 + lane);
-        if constexpr (PREC == 1) e.ctr1 = ctr1;
-        else wa.sctr[lane] = ctr1;
+        e.ctr1 = ctr1;
         // Philox: the first round's word 0 is the same for all bunches of the step, and
         // with it the second round's product of that word
         const uint32_t w0 = __umulhi(0xCD9E8D57u, shower_id) ^ ctr1 ^ a.key0;
@@ -1225,38 +1388,47 @@ __device__ __forceinline__ TileSetup tile_setup(const Args& a, int64_t g0, int n
         e.photons = st.photons;
         e.sidx = lane;
     }
+    const int64_t total_now = scalar64(wave_last(wave_incl_scan(now ? nb : 0)));
     {
-        const int n_emit = __popcll(__ballot(own && emits));
-        const int d_mass = __popcll(__ballot(own && status == CKV_DROP_MASS));
-        const int d_thr = __popcll(__ballot(own && status == CKV_DROP_THRESHOLD));
-        const int d_nf = __popcll(__ballot(own && status == CKV_DROP_NONFINITE));
+        const int n_emit = __popcll(__ballot(now && emits));
+        const int d_mass = __popcll(__ballot(now && status == CKV_DROP_MASS));
+        const int d_thr = __popcll(__ballot(now && status == CKV_DROP_THRESHOLD));
+        const int d_nf = __popcll(__ballot(now && status == CKV_DROP_NONFINITE));
         if (lane == 0) {
-            if (total_all < ((int64_t)1 << 30)) wa.wcnt[kWcBunches] += total_all;
+            wa.wcnt[kWcBunches] += total_now;
             wa.wcnt[kWcEmitting] += n_emit;
             wa.wcnt[kWcDrop0 + CKV_DROP_MASS] += d_mass;
             wa.wcnt[kWcDrop0 + CKV_DROP_THRESHOLD] += d_thr;
             wa.wcnt[kWcDrop0 + CKV_DROP_NONFINITE] += d_nf;
         }
     }
-    return TileSetup{total, excl, in_pass, direct};
+    if constexpr (PROF) {
+        // the bins hold one shower's bunches, fewer than 2^32 of them
+        const int s_now = __builtin_amdgcn_readlane(s, h_first * TS);
+        if (wa.prof[0] >= 0 && (wa.prof[0] != s_now || wa.prof[1] + total_now >= ((int64_t)1 << 32)))
+            flush_profile(a, wa, lane);
+        wave_lds_sync();
+        if (lane == 0) {
+            wa.prof[0] = s_now;
+            wa.prof[1] += total_now;
+        }
+        if (now && live) profile_step(a, st, (int32_t)nb, ctr1, shower_id, wa);
+    }
+    return TileSetup{excl, incl, s, in_pass, masked, h_end};
 }
 
 // The same as a called function: its step setup's registers and the step arrays'
-// pointers then take no room in the bunch loop.
+// pointers then take no room in the bunch loop (inlined: 400 -> 474 us, 2e6 steps).
 template <int PREC, int TS, int FEAT>
-__device__ __noinline__ TileSetup tile_setup_call(uint64_t args_at, int64_t g0, int nseg, int64_t seg_id0,
-                                                  uint32_t shower_id, int lane, uint64_t lt_mask,
-                                                  uint32_t area_at, uint32_t tel_at)
+__device__ __noinline__ TileSetup tile_setup_call(uint64_t args_at, int64_t t0, int h_first, int h_all, int lane,
+                                                  uint64_t lt_mask, uint32_t area_at, uint32_t tel_at)
 {
     extern __shared__ __align__(16) unsigned char lds[];
-    // the launch's argument block, at the address the kernel passes: wave-uniform and
-    // read-only, so the setup reads it with scalar loads
-    const uint64_t at_u = ((uint64_t)(uint32_t)__builtin_amdgcn_readfirstlane((int)(args_at >> 32)) << 32) |
-                          (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)args_at);
-    const Args& a = *(const Args*)reinterpret_cast<const __attribute__((address_space(4))) Args*>(at_u);
-    const WaveArea<PREC, TS> wa(lds + __builtin_amdgcn_readfirstlane((int)area_at), a.n_tel,
-                                (FEAT & kFeatProfile) != 0 ? a.prof_bins : 0);
-    return tile_setup<PREC, TS, FEAT>(a, g0, nseg, seg_id0, shower_id, lane, lt_mask, wa,
+    const Args& a = args_from(args_at);
+    const WaveArea<PREC, TS> wa(lds + __builtin_amdgcn_readfirstlane((int)area_at),
+                                (FEAT & kFeatScreen) != 0 ? 0 : a.n_tel, (FEAT & kFeatProfile) != 0 ? a.prof_bins : 0);
+    return tile_setup<PREC, TS, FEAT>(a, scalar64(t0), __builtin_amdgcn_readfirstlane(h_first),
+                                      __builtin_amdgcn_readfirstlane(h_all), lane, lt_mask, wa,
                                       reinterpret_cast<const double*>(
                                           lds + __builtin_amdgcn_readfirstlane((int)tel_at)));
 }
@@ -1275,6 +1447,21 @@ __device__ __forceinline__ void flush_list(const Args& a, const uint64_t* buf, i
     for (int q = lane; q < n; q += kWave)
         if (base + q >= 0 && base + q < a.list_cap) a.list_ids[base + q] = buf[q];
     wave_lds_sync();
+}
+
+// Tiles are worked on in units that a wave sets up together: 64 steps' worth of tiles, then
+// the last two rounds of the grid's waves tile by tile, so that the launch ends evenly.
+struct Units {
+    int64_t wide;      // units of kWave / tile_segs tiles
+    int64_t count;
+};
+
+__device__ __forceinline__ Units units_of(int64_t n_tiles, int grid_waves, int tile_segs)
+{
+    const int per = kWave / tile_segs;
+    const int64_t left = n_tiles - 2 * (int64_t)grid_waves;
+    const int64_t wide = left > 0 ? left / per : 0;
+    return Units{wide, wide + (n_tiles - wide * per)};
 }
 
 template <int PREC, int TS, int FEAT>
@@ -1306,23 +1493,23 @@ __global__ void __launch_bounds__(emit_threads(PREC, FEAT)) emit_kernel(Args a)
         tel_sh[3 * q + 2] = a.tel[4 * q + 3];
     }
     const int prof_bins = PROF ? a.prof_bins : 0;
-    const size_t wv_bytes = wave_bytes(PREC, TS, a.n_tel, prof_bins);
+    const int n_count = SCREEN ? 0 : a.n_tel;      // spheres counted per tile
+    const size_t wv_bytes = wave_bytes(PREC, TS, n_count, prof_bins);
     const size_t wv_stride = wv_bytes + (SCREEN ? kScreenBuf * sizeof(uint64_t) : 0);
     unsigned char* wbase = lds + srch_bytes + tel_bytes(a.n_tel) + (size_t)wave * wv_stride;
-    const WaveArea<PREC, TS> wa(wbase, a.n_tel, prof_bins);
+    const WaveArea<PREC, TS> wa(wbase, n_count, prof_bins);
     // screening: ids on their way to the list
     uint64_t* const buf = reinterpret_cast<uint64_t*>(wbase + wv_bytes);
     int buf_n = 0;
     Entry* const stash = wa.stash;
     int32_t* const flags = wa.flags;
-    uint32_t* const sctr = wa.sctr;
     int64_t* const wcnt = wa.wcnt;
     int32_t* const tcount = wa.tcount;
-    double* const hph = wa.hph;
-    uint32_t* const hbu = wa.hbu;
-    for (int k = lane; k < a.n_tel; k += kWave) tcount[k] = 0;
-    if (PROF)
-        for (int k = lane; k < prof_bins; k += kWave) { hph[k] = 0.0; hbu[k] = 0u; }
+    for (int k = lane; k < n_count; k += kWave) tcount[k] = 0;
+    if (PROF) {
+        for (int k = lane; k < prof_bins; k += kWave) { wa.hph[k] = 0.0; wa.hbu[k] = 0u; }
+        if (lane < 2) wa.prof[lane] = lane == 0 ? -1 : 0;
+    }
     if (lane < kWcCount) wcnt[lane] = 0;
     flags[lane] = 0;
     __syncthreads();
@@ -1434,61 +1621,55 @@ __global__ void __launch_bounds__(emit_threads(PREC, FEAT)) emit_kernel(Args a)
         return ctw * ix.inv_w * inv_c;
     };
 
-    // Tiles are dealt in kTileClasses interleaved classes, one per group of workgroups, each
-    // with its claim counter on its own cache line: all waves' claims on one address came
-    // 13 ns apart, which bounded the kernel once a tile took less (62 500 tiles: 0.83 ms).
-    // Each wave's first tile goes by its place in the grid, a workgroup's first wave first.
+    // Units of tiles are dealt in kTileClasses interleaved classes, one per group of
+    // workgroups, each with its claim counter on its own cache line: all waves' claims on
+    // one address came 13 ns apart, which bounded the kernel once a tile took less (62 500
+    // tiles: 0.83 ms).  Each wave's first unit goes by its place in the grid, a workgroup's
+    // first wave first.
     const int n_cls = min(kTileClasses, (int)gridDim.x), cls = (int)blockIdx.x % n_cls;
     const int cls_groups = ((int)gridDim.x - cls + n_cls - 1) / n_cls;
     const int cls_waves = cls_groups * (int)(blockDim.x / kWave);
-    const int64_t t_first = cls + (int64_t)n_cls * scalar64(wave * cls_groups + (int)blockIdx.x / n_cls);
-    for (bool first_tile = true;; first_tile = false) {
-        int64_t t = t_first;
-        if (first_tile) {
-            // a wave with a first tile has a staging and a run block of its own from the
-            // start (all waves' first claims would queue at the counters: 50 us of a launch)
-            if (t < a.static_blocks && t < n_tiles) blk = rblk = t;
-        } else {
-            int64_t i = 0;
-            if (lane == 0)
-                i = (int64_t)atomicAdd((unsigned long long*)&a.claims[kClaimStride * cls], 1ull);
-            t = cls + n_cls * (cls_waves + scalar64(i));
+    const Units units = units_of(n_tiles, a.grid_waves, TS);
+    int64_t unit = cls + (int64_t)n_cls * scalar64(wave * cls_groups + (int)blockIdx.x / n_cls);
+    // a wave with a first unit has a staging and a run block of its own from the start (all
+    // waves' first claims would queue at the counters: 50 us of a launch)
+    if (unit < a.static_blocks && unit < units.count) blk = rblk = unit;
+    while (unit < units.count) {
+        int64_t claimed = 0;
+        const bool wide = unit < units.wide;
+        const int64_t t0 = wide ? unit * (kWave / TS) : unit + units.wide * (kWave / TS - 1);
+        const int h_all = wide ? kWave / TS : 1;
+        TileSetup ts_;
+        ts_.h_end = 0;
+        for (int h = 0; h < h_all; ++h) {
+        // ---- step setups of the unit (called out of line, with the arguments where the
+        // launch put them, the kernel argument segment, rather than a private copy)
+        if (h >= ts_.h_end) {
+            ts_ = tile_setup_call<PREC, TS, FEAT>((uint64_t)__builtin_amdgcn_kernarg_segment_ptr(), t0, h, h_all, lane,
+                                                  lt_mask, (uint32_t)(wbase - lds),
+                                                  (uint32_t)(reinterpret_cast<unsigned char*>(tel_sh) - lds));
+            ts_.h_end = __builtin_amdgcn_readfirstlane(ts_.h_end);
+            wave_lds_sync();
         }
-        if (t >= n_tiles) break;
-        // shower of the tile
-        int lo = 0, hi = a.n_showers;   // tiles_before[lo] <= t < tiles_before[hi]
-        while (hi - lo > 1) {
-            int mid = (lo + hi) >> 1;
-            if (a.tiles_before[mid] <= t) lo = mid; else hi = mid;
-        }
-        const int s = lo;
-        const int64_t g0 = a.shower_first[s] + (t - a.tiles_before[s]) * (int64_t)TS;
-        const int64_t gend = min(g0 + (int64_t)TS, a.seg_offsets[s + 1]);
-        const int nseg = (int)(gend - g0);
+        const int64_t t = t0 + h;
+        const int s = __builtin_amdgcn_readlane(ts_.shower, h * TS);
         const uint32_t shower_id = a.shower_ids ? a.shower_ids[s] : (uint32_t)s;
-        const int64_t seg_id0 = (a.seg_id_base ? a.seg_id_base[s] : 0) + (g0 - a.seg_offsets[s]);
         const double t_ref = a.t_ref[s];
         int32_t thits = 0;         // crossings of this tile (wave-uniform)
-
-        // ---- step setups (called out of line, with the arguments where the launch put
-        // them, the kernel argument segment, rather than a private copy)
-        const TileSetup ts_ = tile_setup_call<PREC, TS, FEAT>(
-            (uint64_t)__builtin_amdgcn_kernarg_segment_ptr(), g0, nseg, seg_id0, shower_id, lane, lt_mask,
-            (uint32_t)(wbase - lds), (uint32_t)(reinterpret_cast<unsigned char*>(tel_sh) - lds));
-        const int32_t total = __builtin_amdgcn_readfirstlane(ts_.total);
         const bool in_pass = ts_.in_pass;
-        const bool direct = ts_.direct;
         const int excl = ts_.excl;
-        wave_lds_sync();
+        const int c_end = __builtin_amdgcn_readlane(ts_.incl, h * TS + TS - 1);
+        // every bunch of the tile is taken, whatever its azimuth
+        const bool direct = ((__ballot(ts_.masked) >> (h * TS)) & (~0ull >> (64 - TS))) == 0ull;
 
         // ---- bunches of the tile.  First pass, one bunch per lane: its azimuth's draw
         // against its step's sectors; the bunches that may reach a sphere wait in the
         // queue until 64 are there, in (step, bunch) order.
-        int c0 = 0, qn = 0;
+        int c0 = __builtin_amdgcn_readlane(excl, h * TS), qn = 0;
         for (;;) {
-            while (qn < kWave && c0 < total) {
+            while (qn < kWave && c0 < c_end) {
                 const int32_t j = c0 + lane;
-                const bool active = j < total;
+                const bool active = j < c_end;
                 // step of bunch j: the pass's steps starting at or before c0, plus those
                 // starting inside this chunk at or before j (flag row)
                 const int cnt0 = __popcll(__ballot(in_pass && excl <= c0));
@@ -1502,50 +1683,7 @@ __global__ void __launch_bounds__(emit_threads(PREC, FEAT)) emit_kernel(Args a)
                 uint32_t kr0 = a.key0 + opaque, kr1 = a.key1 + opaque;
                 bool take = active;
                 int32_t k = 0;
-                if (PROF) {
-                    // longitudinal profile: every bunch's emission altitude
-                    int pbin = -1;     // depth bin of the bunch, -1: not counted
-                    if (active) {
-                        const Entry& e = stash[si];
-                        k = j - wa.pass[si].boff;
-                        uint32_t c_1;
-                        if constexpr (PREC == 1) c_1 = e.ctr1;
-                        else c_1 = sctr[e.sidx];
-                        uint32_t r[4];
-                        philox4x32_10((uint32_t)k, c_1, shower_id, 0u, kr0, kr1, r);
-                        const double u0 = fma((double)r[0], 2.3283064365386963e-10, 1.1641532182693481e-10);
-                        const double s_along = ((double)k + u0) * e.ds;
-                        double he;
-                        {
-                            // rounded as the FP64 definition rounds it
-#pragma clang fp contract(off)
-                            he = e.h0 - s_along * e.w;
-                        }
-                        const double xcell = (he - a.h_obs) * a.inv_step;
-                        const int ci = min((int)xcell, a.n_nodes - 2);
-                        if (he >= a.h_obs && he < a.h_top) pbin = profile_bin(a, ci, xcell - (double)ci);
-                        if (!direct) {
-                            const uint32_t w = wa.masks[kSectorWords * e.sidx + (int)(r[1] >> 29)];
-                            take = ((w >> ((r[1] >> 24) & 31u)) & 1u) != 0;
-                        }
-                    }
-                    // runs of lanes with the same step and bin (bunches of a step are
-                    // consecutive lanes and their depth is monotonic in k): the first lane
-                    // of each run adds the whole run, so LDS atomics do not collide
-                    const bool member = pbin >= 0;
-                    const int key = member ? (si << 8) | pbin : -1;     // pbin < 256
-                    // the previous lane's key (DPP wave shift right by one; lane 0 gets -2)
-                    const int key_prev = __builtin_amdgcn_update_dpp(-2, key, 0x138, 0xf, 0xf, false);
-                    const bool head = member && key_prev != key;
-                    const uint64_t mem_mask = __ballot(member), head_mask = __ballot(head);
-                    if (head) {
-                        const uint64_t after = lane == kWave - 1 ? 0ull : (~0ull << (lane + 1));
-                        const uint64_t ends = (~mem_mask | head_mask) & after;
-                        const int len = (ends ? __builtin_ctzll(ends) : kWave) - lane;
-                        atomicAdd(&hph[pbin], (double)len * stash[si].photons);
-                        atomicAdd(&hbu[pbin], (uint32_t)len);
-                    }
-                } else if (active) {
+                if (active) {
                     const StepPass sp = wa.pass[si];
                     k = j - sp.boff;
                     if (!direct) {
@@ -1627,9 +1765,7 @@ __global__ void __launch_bounds__(emit_threads(PREC, FEAT)) emit_kernel(Args a)
                 const Entry& e = stash[si];
                 // Philox4x32-10 with counter (k, step index in shower, shower id, 0)
                 uint32_t c_0 = (uint32_t)k, c_2 = shower_id, c_3 = 0u;
-                uint32_t c_1;
-                if constexpr (PREC == 1) c_1 = e.ctr1;
-                else c_1 = sctr[e.sidx];
+                uint32_t c_1 = e.ctr1;
 #pragma unroll
                 for (int rr = 0; rr < 10; ++rr) {
                     const uint64_t p0 = (uint64_t)0xD2511F53u * c_0;
@@ -1734,17 +1870,19 @@ __global__ void __launch_bounds__(emit_threads(PREC, FEAT)) emit_kernel(Args a)
                     }
                     double T_x = 0.0;
                     if (CURVED) {
-                        const int stc = propagate_curved(a, xe, ye, ze, he, pu, pv, pw, xg, yg, T_x,
-                                                         uod, vod);
-                        if (stc >= 0) {
-                            drop_why = stc;
+                        const SlowRay r = propagate_curved_call((uint64_t)__builtin_amdgcn_kernarg_segment_ptr(), xe,
+                                                                ye, ze, he, pu, pv, pw);
+                        xg = r.xg; yg = r.yg; T_x = r.T; uod = r.uo; vod = r.vo;
+                        if (r.status >= 0) {
+                            drop_why = r.status;
                             alive = false;
                         }
                     } else {
-                        double ne_x;
-                        propagate_exact(a, xe, ye, he, pu, pv, pw, xg, yg, T_x, ne_x);
-                        uod = pu * ne_x / a.n_obs;
-                        vod = pv * ne_x / a.n_obs;
+                        const SlowRay r = propagate_exact_call((uint64_t)__builtin_amdgcn_kernarg_segment_ptr(), xe,
+                                                               ye, he, pu, pv, pw);
+                        xg = r.xg; yg = r.yg; T_x = r.T;
+                        uod = pu * r.uo / a.n_obs;
+                        vod = pv * r.uo / a.n_obs;
                     }
                     t_rec = (te - t_ref) + T_x;
                 }
@@ -1861,7 +1999,8 @@ __global__ void __launch_bounds__(emit_threads(PREC, FEAT)) emit_kernel(Args a)
                 // candidates of the soft response: gathered in the wave's buffer, which goes
                 // to the list when full (one atomic on the list's count for each 256 or so:
                 // claims of all waves come 13 ns apart)
-                const uint64_t step = (uint64_t)(g0 + stash[active ? si : 0].sidx);
+                const uint64_t step = (uint64_t)(a.shower_first[s] + (t - a.tiles_before[s]) * (int64_t)TS +
+                                                 (stash[active ? si : 0].sidx & (TS - 1)));
                 bool cand = my_next != INT_MAX || screen_all;
                 if (sweep)
                     for (int kb = 0; kb < a.n_tel; kb += 32) {
@@ -1890,7 +2029,7 @@ __global__ void __launch_bounds__(emit_threads(PREC, FEAT)) emit_kernel(Args a)
                 if (sweep || __ballot(my_next != INT_MAX)) {
                     if (sweep ? alive : my_next != INT_MAX) {
                         const Entry& er = stash[si];
-                        sidx_rec = er.sidx;
+                        sidx_rec = er.sidx & (TS - 1);
                         photons = (float)er.photons;
                         if (PREC == 0) {
                             lam = (float)rcp64(a.inv_l1 - fma((double)r2_rec, 2.3283064365386963e-10,
@@ -1971,6 +2110,10 @@ __global__ void __launch_bounds__(emit_threads(PREC, FEAT)) emit_kernel(Args a)
                 }
             }
         }
+        // the next unit's claim, on its way during the rest (claimed any earlier, the launch
+        // ends unevenly: shells at 70 degrees 398 -> 480 us)
+        if (h + 1 == h_all && lane == 0)
+            claimed = (int64_t)atomicAdd((unsigned long long*)&a.claims[kClaimStride * cls], 1ull);
         // ---- per-telescope crossings of this tile as runs (ascending telescope)
         wave_lds_sync();
         if (!SCREEN && t < a.max_tiles) {
@@ -2018,18 +2161,9 @@ __global__ void __launch_bounds__(emit_threads(PREC, FEAT)) emit_kernel(Args a)
             }
             if (lane == 0) wcnt[kWcHits] += thits;
         }
-        // ---- profile of this tile into its shower's row
-        for (int kk = lane; PROF && kk < a.prof_bins; kk += kWave) {
-            const uint32_t c = hbu[kk];
-            if (c) {
-                const int64_t g = (int64_t)s * a.prof_bins + kk;
-                atomicAdd(&a.prof_ph[g], hph[kk]);
-                atomicAdd((unsigned long long*)&a.prof_bu[g], (unsigned long long)c);
-                hph[kk] = 0.0;
-                hbu[kk] = 0u;
-            }
-        }
         wave_lds_sync();
+        }
+        unit = cls + n_cls * (cls_waves + scalar64(claimed));
     }
 
     if (SCREEN) flush_list(a, buf, buf_n, lane);
@@ -2039,6 +2173,35 @@ __global__ void __launch_bounds__(emit_threads(PREC, FEAT)) emit_kernel(Args a)
     // the end of every launch)
     if (blk >= 0 && lane == 0) a.stage_fill[blk] = blk_fill;
     __syncthreads();
+    if (PROF) {
+        // the waves' bins, summed over waves that end on the same shower
+        const int nw = (int)(blockDim.x / kWave);
+        for (int kk = threadIdx.x; kk < prof_bins; kk += blockDim.x) {
+            double ph = 0.0;
+            unsigned long long bu = 0;
+            for (int w = 0; w < nw; ++w) {
+                const WaveArea<PREC, TS> ww(lds + srch_bytes + tel_bytes(a.n_tel) + (size_t)w * wv_stride, a.n_tel,
+                                            prof_bins);
+                ph += ww.hph[kk];
+                bu += ww.hbu[kk];
+                const int64_t s = ww.prof[0];
+                bool last = w + 1 == nw;
+                if (!last) {
+                    const WaveArea<PREC, TS> wn(lds + srch_bytes + tel_bytes(a.n_tel) + (size_t)(w + 1) * wv_stride,
+                                                a.n_tel, prof_bins);
+                    last = wn.prof[0] != s;
+                }
+                if (last) {
+                    if (bu) {
+                        atomicAdd(&a.prof_ph[s * prof_bins + kk], ph);
+                        atomicAdd((unsigned long long*)&a.prof_bu[s * prof_bins + kk], bu);
+                    }
+                    ph = 0.0;
+                    bu = 0;
+                }
+            }
+        }
+    }
     if (wave == 0 && lane < kWcCount) {
         const unsigned char* w0 = reinterpret_cast<const unsigned char*>(wcnt);
         int64_t v = 0;
@@ -2114,7 +2277,10 @@ __global__ void __launch_bounds__(1024) init_kernel(Args a)
         a.ctrl[kNumTiles] = err ? 0 : run_t;
         a.ctrl[kNumRowBlocks] = err ? 0 : run_b;
         a.ctrl[kFirstLost] = err ? 0 : run_t;      // no lost tile yet
-        const int64_t dealt = err ? 0 : min(run_t, (int64_t)a.static_blocks);
+        int64_t dealt = 0;
+        if (!err && a.static_blocks > 0) {
+            dealt = min(units_of(run_t, a.grid_waves, a.tile_segs).count, (int64_t)a.static_blocks);
+        }
         a.ctrl[kBlockCounter] = dealt;
         a.ctrl[kRunCounter] = dealt;
         if (a.result) {
@@ -3667,6 +3833,7 @@ int launch_run(RunPlan& p)
                              &lds, many_nodes_ok))
         return rc;
     set_sectors(a, p.atmo, p.arr->rmax, p.arr->dmax);
+    a.grid_waves = p.emit_grid * waves;
     // a block per wave of the launch, as far as the workspace holds them beside the claims'
     // (a grid of whole class rounds: the waves' first tiles are then 0 .. waves - 1, each
     // block with an owner that leaves its fill)
@@ -3782,7 +3949,7 @@ int launch_soft(RunPlan& p, const SoftPlan& sp, int mode)
         e.list_cap = sp.ids_cap;
         e.list_count = sp.ids_count;
         const size_t tab = (table_bytes(1, e.n_nodes, true) + 15) & ~(size_t)15;
-        const size_t per = wave_bytes(1, kSoftTS, e.n_tel, 0) + kScreenBuf * sizeof(uint64_t);
+        const size_t per = wave_bytes(1, kSoftTS, 0, 0) + kScreenBuf * sizeof(uint64_t);
         if (tab + tel_bytes(e.n_tel) + limit_wave_bytes(1, kSoftTS, e.n_tel, 0) + kLimitScreenBytes <= 160 * 1024)
             for (int wv = kMaxEmitWaves; wv >= 1 && !e_waves; wv /= 2)
                 if (tel_bytes(e.n_tel) + (size_t)wv * per <= 160 * 1024) {
@@ -3821,6 +3988,7 @@ int launch_soft(RunPlan& p, const SoftPlan& sp, int mode)
         allow_lds((const void*)soft_kernel<0>, 160 * 1024);
         if (s.ids_count) {
             allow_lds((const void*)emit_kernel<1, kSoftTS, kFeatScreen>, 160 * 1024);
+            e.grid_waves = p.emit_grid * e_waves;
             emit_kernel<1, kSoftTS, kFeatScreen><<<p.emit_grid, e_waves * kWave, e_lds, st>>>(e);
             if (int rc = check_launch("screen")) return rc;
             size_t lds_c = (size_t)a.n_tel * 4 * sizeof(double) +
