@@ -162,7 +162,7 @@ void build_depth_table(const double* alt, const double* depth, int64_t n, ckv_at
 int build_array_grid(const ckv_array* arr, const std::vector<double>& radius, ckv_grid* g);
 // data of the reach grid; empty for at most kReachMinTel spheres
 void build_reach(const ckv_array* arr, ckv_reach* g, std::vector<uint32_t>* data);
-constexpr int kReachLevels = 7;      // up to 768 m
+constexpr int kReachLevels = 6;      // up to 543 m
 constexpr double kReachMin = 96.0;
 constexpr int kReachPad = 4;
 // a step tests up to this many spheres one by one (16 double rounds of the wave) sooner

@@ -3,7 +3,6 @@
 // computed at initialisation so that lookups need no search).
 #include <algorithm>
 #include <cmath>
-#include <cstring>
 
 #include "ckv_internal.h"
 
@@ -161,36 +160,43 @@ int build_array_grid(const ckv_array* arr, const std::vector<double>& radius, ck
     g->ny = ny;
     g->level_cells = nx * ny;
     const size_t n_cells = (size_t)nx * ny;
-    g->cell_off.assign(kGridLevels * n_cells + 1, 0);
-    std::vector<std::vector<uint16_t>> lists(kGridLevels * n_cells);
-    for (int lv = 0; lv < kGridLevels; ++lv)
-        for (int32_t k = 0; k < n; ++k) {
-            double reach = radius[k] / kGridWLevel[lv] + margin;
-            int32_t ix0 = std::max(0, (int32_t)std::floor((arr->x[k] - reach - xmin) / cell));
-            int32_t ix1 = std::min(nx - 1, (int32_t)std::floor((arr->x[k] + reach - xmin) / cell));
-            int32_t iy0 = std::max(0, (int32_t)std::floor((arr->y[k] - reach - ymin) / cell));
-            int32_t iy1 = std::min(ny - 1, (int32_t)std::floor((arr->y[k] + reach - ymin) / cell));
-            for (int32_t ix = ix0; ix <= ix1; ++ix)
+    const size_t n_lists = kGridLevels * n_cells;
+    // each (level, sphere)'s cells, by the distance from the centre to the cell rectangle;
+    // once to count, once to fill (lists ascend by sphere)
+    auto each = [&](auto&& visit) {
+        std::vector<double> dy2(ny);
+        for (int lv = 0; lv < kGridLevels; ++lv)
+            for (int32_t k = 0; k < n; ++k) {
+                double reach = radius[k] / kGridWLevel[lv] + margin;
+                int32_t ix0 = std::max(0, (int32_t)std::floor((arr->x[k] - reach - xmin) / cell));
+                int32_t ix1 = std::min(nx - 1, (int32_t)std::floor((arr->x[k] + reach - xmin) / cell));
+                int32_t iy0 = std::max(0, (int32_t)std::floor((arr->y[k] - reach - ymin) / cell));
+                int32_t iy1 = std::min(ny - 1, (int32_t)std::floor((arr->y[k] + reach - ymin) / cell));
                 for (int32_t iy = iy0; iy <= iy1; ++iy) {
-                    // distance from the centre to the cell rectangle
-                    double cx0 = xmin + ix * cell, cy0 = ymin + iy * cell;
-                    double dx = std::max({cx0 - arr->x[k], 0.0, arr->x[k] - (cx0 + cell)});
+                    double cy0 = ymin + iy * cell;
                     double dy = std::max({cy0 - arr->y[k], 0.0, arr->y[k] - (cy0 + cell)});
-                    if (dx * dx + dy * dy <= reach * reach)
-                        lists[lv * n_cells + (size_t)ix * ny + iy].push_back((uint16_t)k);
+                    dy2[iy] = dy * dy;
                 }
-        }
-    g->cell_list.clear();
-    for (size_t c = 0; c < lists.size(); ++c) {
-        g->cell_off[c] = (int32_t)g->cell_list.size();
-        g->cell_list.insert(g->cell_list.end(), lists[c].begin(), lists[c].end());
-    }
-    g->cell_off[lists.size()] = (int32_t)g->cell_list.size();
-    g->cell_ent.assign(2 * lists.size(), 0u);
-    for (size_t c = 0; c < lists.size(); ++c) {
-        const uint32_t cnt = (uint32_t)lists[c].size();
+                for (int32_t ix = ix0; ix <= ix1; ++ix) {
+                    double cx0 = xmin + ix * cell;
+                    double dx = std::max({cx0 - arr->x[k], 0.0, arr->x[k] - (cx0 + cell)});
+                    const size_t row = lv * n_cells + (size_t)ix * ny;
+                    for (int32_t iy = iy0; iy <= iy1; ++iy)
+                        if (dx * dx + dy2[iy] <= reach * reach) visit(row + iy, (uint16_t)k);
+                }
+            }
+    };
+    g->cell_off.assign(n_lists + 1, 0);
+    each([&](size_t c, uint16_t) { ++g->cell_off[c + 1]; });
+    for (size_t c = 0; c < n_lists; ++c) g->cell_off[c + 1] += g->cell_off[c];
+    g->cell_list.resize(g->cell_off[n_lists]);
+    std::vector<int32_t> at(g->cell_off.begin(), g->cell_off.end() - 1);
+    each([&](size_t c, uint16_t k) { g->cell_list[at[c]++] = k; });
+    g->cell_ent.assign(2 * n_lists, 0u);
+    for (size_t c = 0; c < n_lists; ++c) {
+        const uint32_t cnt = (uint32_t)(g->cell_off[c + 1] - g->cell_off[c]);
         g->cell_ent[2 * c] = (uint32_t)g->cell_off[c];
-        g->cell_ent[2 * c + 1] = cnt | ((cnt ? (uint32_t)lists[c][0] : 0u) << 16);
+        g->cell_ent[2 * c + 1] = cnt | ((cnt ? (uint32_t)g->cell_list[g->cell_off[c]] : 0u) << 16);
     }
     if (g->cell_list.empty()) g->cell_list.push_back(0);
     return CKV_OK;
@@ -208,45 +214,54 @@ void build_reach(const ckv_array* arr, ckv_reach* g, std::vector<uint32_t>* data
     const double extent = std::max(*mx.second - *mx.first, *my.second - *my.first) + 2.0 * top;
     // centres too far apart for a grid of this kind: the step setup tests them all
     if (!(extent < 1e6)) return;
-    const double cell = std::max(64.0, extent / 128.0), margin = 0.01 + 1e-9 * extent;
+    const double cell = std::max(80.0, extent / 96.0), margin = 0.01 + 1e-9 * extent;
     g->gx0 = *mx.first - top - margin;
     g->gy0 = *my.first - top - margin;
     g->inv_cell = 1.0 / cell;
     g->nx = (int32_t)std::floor((*mx.second + top + margin - g->gx0) / cell) + 1;
     g->ny = (int32_t)std::floor((*my.second + top + margin - g->gy0) / cell) + 1;
     const size_t n_cells = (size_t)g->nx * g->ny;
-    std::vector<std::vector<uint16_t>> lists(kReachLevels * n_cells);
-    for (int l = 0; l < kReachLevels; ++l) {
-        const double reach = radius(l) + margin;
-        for (int32_t k = 0; k < n; ++k) {
-            const int32_t x0 = std::max(0, (int32_t)std::floor((arr->x[k] - reach - g->gx0) / cell));
-            const int32_t x1 = std::min(g->nx - 1, (int32_t)std::floor((arr->x[k] + reach - g->gx0) / cell));
-            const int32_t y0 = std::max(0, (int32_t)std::floor((arr->y[k] - reach - g->gy0) / cell));
-            const int32_t y1 = std::min(g->ny - 1, (int32_t)std::floor((arr->y[k] + reach - g->gy0) / cell));
-            for (int32_t ix = x0; ix <= x1; ++ix)
+    // each (level, sphere)'s cells, row by row; once to count, once to fill
+    auto each = [&](auto&& visit) {
+        std::vector<double> dy2(g->ny);
+        for (int l = 0; l < kReachLevels; ++l) {
+            const double reach = radius(l) + margin;
+            for (int32_t k = 0; k < n; ++k) {
+                const double X = arr->x[k] - g->gx0, Y = arr->y[k] - g->gy0;
+                const int32_t x0 = std::max(0, (int32_t)std::floor((X - reach) / cell));
+                const int32_t x1 = std::min(g->nx - 1, (int32_t)std::floor((X + reach) / cell));
+                const int32_t y0 = std::max(0, (int32_t)std::floor((Y - reach) / cell));
+                const int32_t y1 = std::min(g->ny - 1, (int32_t)std::floor((Y + reach) / cell));
                 for (int32_t iy = y0; iy <= y1; ++iy) {
-                    const double cx = g->gx0 + ix * cell, cy = g->gy0 + iy * cell;
-                    const double dx = std::max({cx - arr->x[k], 0.0, arr->x[k] - (cx + cell)});
-                    const double dy = std::max({cy - arr->y[k], 0.0, arr->y[k] - (cy + cell)});
-                    if (dx * dx + dy * dy <= reach * reach)
-                        lists[l * n_cells + (size_t)ix * g->ny + iy].push_back((uint16_t)k);
+                    const double dy = std::max({iy * cell - Y, 0.0, Y - (iy + 1) * cell});
+                    dy2[iy] = dy * dy;
                 }
+                for (int32_t ix = x0; ix <= x1; ++ix) {
+                    const double dx = std::max({ix * cell - X, 0.0, X - (ix + 1) * cell});
+                    const double left = reach * reach - dx * dx;
+                    const size_t row = l * n_cells + (size_t)ix * g->ny;
+                    for (int32_t iy = y0; iy <= y1; ++iy)
+                        if (dy2[iy] <= left) visit(row + iy, (uint16_t)k);
+                }
+            }
         }
-    }
-    std::vector<uint16_t> flat;
-    data->resize(2 * lists.size());
-    for (size_t c = 0; c < lists.size(); ++c) {
-        (*data)[2 * c] = (uint32_t)flat.size();
-        (*data)[2 * c + 1] = (uint32_t)lists[c].size();
-        flat.insert(flat.end(), lists[c].begin(), lists[c].end());
-        while (flat.size() % kReachPad) flat.push_back(0xFFFF);
+    };
+    const size_t n_lists = kReachLevels * n_cells;
+    data->assign(2 * n_lists, 0u);
+    each([&](size_t c, uint16_t) { ++(*data)[2 * c + 1]; });
+    uint32_t total = 0;
+    for (size_t c = 0; c < n_lists; ++c) {
+        (*data)[2 * c] = total;
+        total += ((*data)[2 * c + 1] + kReachPad - 1) / kReachPad * kReachPad;
     }
     // (8-byte reads of the lists: kReachPad entries, from an even word)
     static_assert(kReachPad * sizeof(uint16_t) == 8, "one 8-byte read per kReachPad entries");
-    g->list_at = data->size();
-    const size_t words = flat.size() / 2;
-    data->resize(g->list_at + words);
-    if (words) std::memcpy(data->data() + g->list_at, flat.data(), words * sizeof(uint32_t));
+    g->list_at = 2 * n_lists;
+    data->resize(g->list_at + total / 2, 0xFFFFFFFFu);
+    uint16_t* list = reinterpret_cast<uint16_t*>(data->data() + g->list_at);
+    std::vector<uint32_t> at(n_lists);
+    for (size_t c = 0; c < n_lists; ++c) at[c] = (*data)[2 * c];
+    each([&](size_t c, uint16_t k) { list[at[c]++] = k; });
 }
 
 // ---------------------------------------------------------------------------
