@@ -2331,67 +2331,147 @@ __device__ __forceinline__ int run_tile(int64_t incl, int64_t q, int m)
     return lo;
 }
 
-// Adds the runs of tiles [t0, t1) into acc[telescope] (LDS) with the whole
-// workgroup.  Each wave takes groups of kRowBlock / waves tiles: its lanes load
-// the group's run counts and offsets in one round, then walk the group's runs in
-// flat order (a run per lane), so the loads of different tiles are not chained.
-__device__ __forceinline__ void add_runs(const Args& a, int64_t t0, int64_t t1, int32_t* acc)
-{
-    const int lane = lane_id(), wave = threadIdx.x / kWave, nw = blockDim.x / kWave;
-    int g = kRowBlock / nw;                         // tiles per group: a power of two
-    if (g < 1) g = 1;
-    for (int64_t base = t0 + (int64_t)wave * g; base < t1; base += (int64_t)nw * g) {
-        const int64_t t = base + lane;
-        const bool mine = lane < g && t < t1;
-        const int n = mine ? a.tile_run_n[t] : 0;
-        const int64_t off = mine ? a.tile_run_off[t] : 0;
-        const int64_t incl = wave_incl_scan((int64_t)n);
-        const int64_t total = wave_last(incl);
-        // the whole wave runs every round (the shuffles read every lane)
-        for (int64_t q0 = 0; q0 < total; q0 += kWave) {
-            const int64_t q = q0 + lane;
-            const int j = run_tile(incl, q, g);
-            const int64_t off_j = __shfl(off, j), first_j = __shfl(incl, j) - __shfl((int64_t)n, j);
-            if (q < total) {
-                const int64_t r = a.runs[off_j + (q - first_j)];
-                atomicAdd(&acc[(int)(r >> kRunTelShift)], (int32_t)(r & kRunValueMask));
-            }
-        }
-    }
-}
+// A: per row block, one workgroup: each run's count becomes the crossings of its telescope
+// in the block's earlier tiles, and the block's crossings per telescope (block_sums,
+// telescope-major: block_sums[k * max_row_blocks + b]) and in all (block_hits) are kept.
+// The block's runs go into a dense tiles x telescopes count matrix in LDS, each
+// telescope's column is scanned, and each run takes its entry: nothing is serial over the
+// block's tiles but one register sum per column, and the runs are read once (sums and
+// prefixes in kernels of their own: 17.6 us on the TeV shower, now 11).
+constexpr int kPrefixDenseTel = 512;           // 128 KB of LDS
 
-// A: per row block: crossings per telescope (block_sums, telescope-major:
-// block_sums[k * max_row_blocks + b]) and in all (block_hits).
-__global__ void __launch_bounds__(256) block_sum_kernel(Args a)
+__global__ void __launch_bounds__(1024) block_prefix_dense_kernel(Args a)
 {
-    extern __shared__ int32_t acc[];               // n_tel
-    __shared__ unsigned long long tot;
+    extern __shared__ int32_t mat[];               // kRowBlock x n_tel, row = tile
+    __shared__ int64_t s_incl[kRowBlock], s_off[kRowBlock];
+    const int tid = threadIdx.x, nt = a.n_tel;
     const int64_t nblk = a.ctrl[kNumRowBlocks];
     for (int64_t b = blockIdx.x; b < nblk; b += gridDim.x) {
-        for (int k = threadIdx.x; k < a.n_tel; k += blockDim.x) acc[k] = 0;
-        if (threadIdx.x == 0) tot = 0;
-        __syncthreads();
         int s;
         int64_t t0, t1;
         block_tiles(a, b, s, t0, t1);
-        add_runs(a, t0, t1, acc);
-        for (int64_t t = t0 + threadIdx.x; t < t1; t += blockDim.x)
-            atomicAdd(&tot, (unsigned long long)a.tile_hits[t]);
+        const int ntl = (int)(t1 - t0);
+        if (tid < kWave) {
+            // lane l: tile t0 + l; inclusive run counts over the block's tiles
+            const bool mine = tid < ntl;
+            const int n = mine ? a.tile_run_n[t0 + tid] : 0;
+            s_off[tid] = mine ? a.tile_run_off[t0 + tid] : 0;
+            const int64_t hits = mine ? (int64_t)a.tile_hits[t0 + tid] : 0;
+            s_incl[tid] = wave_incl_scan((int64_t)n);
+            const int64_t sum = wave_last(wave_incl_scan(hits));
+            if (tid == 0) a.block_hits[b] = sum;
+        }
+        for (int q = tid; q < ntl * nt; q += blockDim.x) mat[q] = 0;
         __syncthreads();
-        for (int k = threadIdx.x; k < a.n_tel; k += blockDim.x)
-            a.block_sums[(int64_t)k * a.max_row_blocks + b] = acc[k];
-        if (threadIdx.x == 0) a.block_hits[b] = (int64_t)tot;
+        const int64_t total = s_incl[kRowBlock - 1];
+        // the block's runs in flat order: run q's tile is the first whose inclusive
+        // count passes q
+        auto run_at = [&](int64_t q, int& j) {
+            j = 0;
+            for (int step = kRowBlock / 2; step > 0; step >>= 1)
+                if (s_incl[j + step - 1] <= q) j += step;
+            return s_off[j] + (q - (j ? s_incl[j - 1] : 0));
+        };
+        for (int64_t q = tid; q < total; q += blockDim.x) {
+            int j;
+            const int64_t r = a.runs[run_at(q, j)];
+            mat[j * nt + (int)(r >> kRunTelShift)] = (int32_t)(r & kRunValueMask);
+        }
         __syncthreads();
+        // exclusive scan down each telescope's column
+        for (int k = tid; k < nt; k += blockDim.x) {
+            int32_t acc = 0;
+            for (int j = 0; j < ntl; ++j) {
+                const int32_t v = mat[j * nt + k];
+                mat[j * nt + k] = acc;
+                acc += v;
+            }
+            a.block_sums[(int64_t)k * a.max_row_blocks + b] = acc;
+        }
+        __syncthreads();
+        for (int64_t q = tid; q < total; q += blockDim.x) {
+            int j;
+            const int64_t g = run_at(q, j);
+            const int tel = (int)(a.runs[g] >> kRunTelShift);
+            a.runs[g] = ((int64_t)tel << kRunTelShift) | mat[j * nt + tel];
+        }
+        __syncthreads();
+    }
+}
+
+// The same for more telescopes: per row block, one wave.  The block's runs are gathered
+// into LDS when they fit (one load round per tile list), walked tile by tile there, and
+// written back.
+constexpr int kPrefixLdsRuns = 4096;
+
+__global__ void __launch_bounds__(64) block_prefix_kernel(Args a)
+{
+    extern __shared__ int32_t ctr[];               // n_tel counters, then the run buffer
+    int64_t* buf = reinterpret_cast<int64_t*>(ctr + ((a.n_tel + 1) & ~1));
+    const int lane = lane_id();
+    const int64_t nblk = a.ctrl[kNumRowBlocks];
+    for (int64_t b = blockIdx.x; b < nblk; b += gridDim.x) {
+        int s;
+        int64_t t0, t1;
+        block_tiles(a, b, s, t0, t1);
+        for (int k = lane; k < a.n_tel; k += kWave) ctr[k] = 0;
+        // lane l: tile t0 + l (a block has at most 64 tiles)
+        const int64_t tl = t0 + lane;
+        const int n = tl < t1 ? a.tile_run_n[tl] : 0;
+        const int64_t off = tl < t1 ? a.tile_run_off[tl] : 0;
+        const int64_t hits = wave_last(wave_incl_scan(tl < t1 ? (int64_t)a.tile_hits[tl] : 0));
+        if (lane == 0) a.block_hits[b] = hits;
+        const int64_t incl = wave_incl_scan((int64_t)n);
+        const int64_t total = wave_last(incl);
+        const int my0 = (int)(incl - n);
+        const bool in_lds = total <= kPrefixLdsRuns;
+        // the block's runs into LDS in flat order, a run per lane (the loads of
+        // different tiles are not chained)
+        if (in_lds)
+            for (int64_t q0 = 0; q0 < total; q0 += kWave) {
+                const int64_t q = q0 + lane;
+                const int j = run_tile(incl, q, kWave);
+                const int64_t off_j = __shfl(off, j), first_j = __shfl(incl, j) - __shfl((int64_t)n, j);
+                if (q < total) buf[q] = a.runs[off_j + (q - first_j)];
+            }
+        wave_lds_sync();
+        for (int64_t t = t0; t < t1; ++t) {
+            // the tile's count, offset and first slot from its lane (a uniform lane
+            // index: a register read, not an LDS round trip)
+            const int j = (int)(t - t0);
+            const int nj = __builtin_amdgcn_readlane(n, j);
+            const int64_t offj = (int64_t)(((uint64_t)(uint32_t)__builtin_amdgcn_readlane((int)(off >> 32), j) << 32) |
+                                           (uint32_t)__builtin_amdgcn_readlane((int)off, j));
+            const int bj = __builtin_amdgcn_readlane(my0, j);
+            for (int i = lane; i < nj; i += kWave) {
+                const int64_t r = in_lds ? buf[bj + i] : a.runs[offj + i];
+                const int tel = (int)(r >> kRunTelShift);
+                const int32_t v = ctr[tel];
+                const int64_t w = ((int64_t)tel << kRunTelShift) | v;
+                if (in_lds) buf[bj + i] = w; else a.runs[offj + i] = w;
+                ctr[tel] = v + (int32_t)(r & kRunValueMask);
+            }
+            wave_lds_sync();
+        }
+        if (in_lds)
+            for (int64_t q0 = 0; q0 < total; q0 += kWave) {
+                const int64_t q = q0 + lane;
+                const int j = run_tile(incl, q, kWave);
+                const int64_t off_j = __shfl(off, j), first_j = __shfl(incl, j) - __shfl((int64_t)n, j);
+                if (q < total) a.runs[off_j + (q - first_j)] = buf[q];
+            }
+        for (int k = lane; k < a.n_tel; k += kWave) a.block_sums[(int64_t)k * a.max_row_blocks + b] = ctr[k];
+        wave_lds_sync();
     }
 }
 
 // B: the written prefix.  Without a lost tile and with every crossing within the
 // capacity it is the whole run.  Otherwise it ends at the first tile that is
 // lost or whose crossings would pass the capacity; the row block holding that
-// tile gets its sums again over the tiles before it.  One workgroup.
-__global__ void __launch_bounds__(1024) cutoff_kernel(Args a)
+// tile gets its sums again over the tiles before it (acc: n_tel counters in LDS).
+// Called by a whole workgroup of 1024 threads.
+__device__ __forceinline__ void find_cutoff(const Args& a, int32_t* acc)
 {
-    extern __shared__ int32_t acc[];               // n_tel
     __shared__ int64_t part[1024];
     __shared__ int first_thread;
     __shared__ int64_t cut_tile, cut_block, cut_records, blk_b, blk_before;
@@ -2458,9 +2538,17 @@ __global__ void __launch_bounds__(1024) cutoff_kernel(Args a)
     int s;
     int64_t t0, t1;
     block_tiles(a, b, s, t0, t1);
-    for (int k = threadIdx.x; k < a.n_tel; k += blockDim.x) acc[k] = 0;
+    for (int k = threadIdx.x; k < a.n_tel; k += blockDim.x)
+        acc[k] = a.block_sums[(int64_t)k * a.max_row_blocks + b];
     __syncthreads();
-    add_runs(a, t0, min(t1, cut_tile), acc);
+    // a telescope's first run at or past the cut holds its crossings before the cut
+    for (int64_t t = max(t0, cut_tile) + threadIdx.x; t < t1; t += blockDim.x) {
+        const int64_t off = a.tile_run_off[t];
+        for (int i = 0; i < a.tile_run_n[t]; ++i) {
+            const int64_t r = a.runs[off + i];
+            atomicMin(&acc[(int)(r >> kRunTelShift)], (int32_t)(r & kRunValueMask));
+        }
+    }
     __syncthreads();
     for (int k = threadIdx.x; k < a.n_tel; k += blockDim.x)
         a.block_sums[(int64_t)k * a.max_row_blocks + b] = acc[k];
@@ -2471,17 +2559,21 @@ __global__ void __launch_bounds__(1024) cutoff_kernel(Args a)
     }
 }
 
+__global__ void __launch_bounds__(1024) cutoff_kernel(Args a)
+{
+    extern __shared__ int32_t acc[];
+    find_cutoff(a, acc);
+}
+
 // C: per (shower, telescope), one wave: exclusive scan over the shower's row
 // blocks below the cut, 8 x 64 blocks per round
-__global__ void __launch_bounds__(256) rowblock_scan_kernel(Args a)
+__device__ __forceinline__ void scan_row_blocks(const Args& a, int64_t wave0, int64_t waves)
 {
     const int lane = lane_id();
     const int64_t nst = (int64_t)a.n_showers * a.n_tel;
-    const int64_t waves = (int64_t)gridDim.x * (blockDim.x / kWave);
     const bool have_tiles = a.ctrl[kNumTiles] > 0;
     const int64_t cutb = a.ctrl[kCutBlocks];
-    for (int64_t q = blockIdx.x * (int64_t)(blockDim.x / kWave) + threadIdx.x / kWave; q < nst;
-         q += waves) {
+    for (int64_t q = wave0; q < nst; q += waves) {
         const int s = (int)(q / a.n_tel), k = (int)(q % a.n_tel);
         int64_t run = 0;
         if (have_tiles) {
@@ -2513,154 +2605,45 @@ __global__ void __launch_bounds__(256) rowblock_scan_kernel(Args a)
     }
 }
 
-// D: per row block below the cut, one wave: each run's count becomes the
-// crossings of its (shower, telescope) in earlier tiles.  The block's runs are
-// gathered into LDS when they fit (one load round per tile list), walked tile by
-// tile there, and written back.
-constexpr int kPrefixLdsRuns = 4096;
-
-__global__ void __launch_bounds__(64) tile_prefix_kernel(Args a)
+__global__ void __launch_bounds__(256) rowblock_scan_kernel(Args a)
 {
-    extern __shared__ int32_t ctr[];               // n_tel counters, then the run buffer
-    int64_t* buf = reinterpret_cast<int64_t*>(ctr + ((a.n_tel + 1) & ~1));
-    const int lane = lane_id();
-    const int64_t cutb = a.ctrl[kCutBlocks], cut = a.ctrl[kCutTile];
-    for (int64_t b = blockIdx.x; b < cutb; b += gridDim.x) {
-        int s;
-        int64_t t0, t1;
-        block_tiles(a, b, s, t0, t1);
-        t1 = min(t1, cut);
-        for (int k = lane; k < a.n_tel; k += kWave) ctr[k] = a.block_sums[(int64_t)k * a.max_row_blocks + b];
-        // lane l: tile t0 + l (a block has at most 64 tiles)
-        const int64_t tl = t0 + lane;
-        const int n = tl < t1 ? a.tile_run_n[tl] : 0;
-        const int64_t off = tl < t1 ? a.tile_run_off[tl] : 0;
-        const int64_t incl = wave_incl_scan((int64_t)n);
-        const int64_t total = wave_last(incl);
-        const int my0 = (int)(incl - n);
-        const bool in_lds = total <= kPrefixLdsRuns;
-        // the block's runs into LDS in flat order, a run per lane (the loads of
-        // different tiles are not chained)
-        if (in_lds)
-            for (int64_t q0 = 0; q0 < total; q0 += kWave) {
-                const int64_t q = q0 + lane;
-                const int j = run_tile(incl, q, kWave);
-                const int64_t off_j = __shfl(off, j), first_j = __shfl(incl, j) - __shfl((int64_t)n, j);
-                if (q < total) buf[q] = a.runs[off_j + (q - first_j)];
-            }
-        wave_lds_sync();
-        for (int64_t t = t0; t < t1; ++t) {
-            // the tile's count, offset and first slot from its lane (a uniform lane
-            // index: a register read, not an LDS round trip)
-            const int j = (int)(t - t0);
-            const int nj = __builtin_amdgcn_readlane(n, j);
-            const int64_t offj = (int64_t)(((uint64_t)(uint32_t)__builtin_amdgcn_readlane((int)(off >> 32), j) << 32) |
-                                           (uint32_t)__builtin_amdgcn_readlane((int)off, j));
-            const int bj = __builtin_amdgcn_readlane(my0, j);
-            for (int i = lane; i < nj; i += kWave) {
-                const int64_t r = in_lds ? buf[bj + i] : a.runs[offj + i];
-                const int tel = (int)(r >> kRunTelShift);
-                const int32_t v = ctr[tel];
-                const int64_t w = ((int64_t)tel << kRunTelShift) | v;
-                if (in_lds) buf[bj + i] = w; else a.runs[offj + i] = w;
-                ctr[tel] = v + (int32_t)(r & kRunValueMask);
-            }
-            wave_lds_sync();
-        }
-        if (in_lds)
-            for (int64_t q0 = 0; q0 < total; q0 += kWave) {
-                const int64_t q = q0 + lane;
-                const int j = run_tile(incl, q, kWave);
-                const int64_t off_j = __shfl(off, j), first_j = __shfl(incl, j) - __shfl((int64_t)n, j);
-                if (q < total) a.runs[off_j + (q - first_j)] = buf[q];
-            }
-        wave_lds_sync();
-    }
+    const int64_t per = blockDim.x / kWave;
+    scan_row_blocks(a, blockIdx.x * per + threadIdx.x / kWave, (int64_t)gridDim.x * per);
 }
 
-// D, for at most kPrefixDenseTel telescopes: per row block, one workgroup.  The
-// block's runs go into a dense tiles x telescopes count matrix in LDS, each
-// telescope's column is scanned from the crossings of earlier blocks, and each run
-// takes its entry.  Nothing is serial over the block's tiles but one register sum
-// per column, so the block costs a few memory round trips instead of a chain of
-// LDS round trips per tile.
-constexpr int kPrefixDenseTel = 128;
+// D: CSR offsets over (shower, telescope) and the run report.  Each thread takes up to
+// kCsrPer consecutive entries, so 256 showers x 100 telescopes are four rounds of one
+// scan.  Called by a whole workgroup of 1024 threads.
+constexpr int kCsrPer = 8;
 
-__global__ void __launch_bounds__(256) tile_prefix_dense_kernel(Args a)
+__device__ __forceinline__ void write_offsets(const Args& a)
 {
-    extern __shared__ int32_t mat[];               // kRowBlock x n_tel, row = tile
-    __shared__ int64_t s_incl[kRowBlock], s_off[kRowBlock];
-    const int tid = threadIdx.x, nt = a.n_tel;
-    const int64_t cutb = a.ctrl[kCutBlocks], cut = a.ctrl[kCutTile];
-    for (int64_t b = blockIdx.x; b < cutb; b += gridDim.x) {
-        int s;
-        int64_t t0, t1;
-        block_tiles(a, b, s, t0, t1);
-        t1 = min(t1, cut);
-        const int ntl = (int)(t1 - t0);
-        if (tid < kWave) {
-            // lane l: tile t0 + l; inclusive run counts over the block's tiles
-            const bool mine = tid < ntl;
-            const int n = mine ? a.tile_run_n[t0 + tid] : 0;
-            s_off[tid] = mine ? a.tile_run_off[t0 + tid] : 0;
-            s_incl[tid] = wave_incl_scan((int64_t)n);
-        }
-        for (int q = tid; q < ntl * nt; q += blockDim.x) mat[q] = 0;
-        __syncthreads();
-        const int64_t total = s_incl[kRowBlock - 1];
-        // the block's runs in flat order: run q's tile is the first whose inclusive
-        // count passes q
-        for (int64_t q = tid; q < total; q += blockDim.x) {
-            int j = 0;
-            for (int step = kRowBlock / 2; step > 0; step >>= 1)
-                if (s_incl[j + step - 1] <= q) j += step;
-            const int64_t first = j ? s_incl[j - 1] : 0;
-            const int64_t r = a.runs[s_off[j] + (q - first)];
-            mat[j * nt + (int)(r >> kRunTelShift)] = (int32_t)(r & kRunValueMask);
-        }
-        __syncthreads();
-        // exclusive scan down each telescope's column
-        for (int k = tid; k < nt; k += blockDim.x) {
-            int32_t acc = a.block_sums[(int64_t)k * a.max_row_blocks + b];
-            for (int j = 0; j < ntl; ++j) {
-                const int32_t v = mat[j * nt + k];
-                mat[j * nt + k] = acc;
-                acc += v;
-            }
-        }
-        __syncthreads();
-        for (int64_t q = tid; q < total; q += blockDim.x) {
-            int j = 0;
-            for (int step = kRowBlock / 2; step > 0; step >>= 1)
-                if (s_incl[j + step - 1] <= q) j += step;
-            const int64_t first = j ? s_incl[j - 1] : 0;
-            const int64_t g = s_off[j] + (q - first);
-            const int tel = (int)(a.runs[g] >> kRunTelShift);
-            a.runs[g] = ((int64_t)tel << kRunTelShift) | mat[j * nt + tel];
-        }
-        __syncthreads();
-    }
-}
-
-// E: CSR offsets over (shower, telescope) and the run report
-__global__ void __launch_bounds__(1024) csr_kernel(Args a)
-{
-    __shared__ int64_t sh[1024];
+    __shared__ int64_t sums[1024 / kWave];
+    const int lane = lane_id(), wave = threadIdx.x / kWave, nw = blockDim.x / kWave;
     const int64_t nst = (int64_t)a.n_showers * a.n_tel;
     int64_t run = 0;
-    for (int64_t base = 0; base < nst; base += blockDim.x) {
-        const int64_t q = base + threadIdx.x;
-        const int64_t x = q < nst ? (int64_t)a.shower_tel[q] : 0;
-        sh[threadIdx.x] = x;
-        __syncthreads();
-        for (int d = 1; d < (int)blockDim.x; d <<= 1) {
-            int64_t y = (int)threadIdx.x >= d ? sh[threadIdx.x - d] : 0;
-            __syncthreads();
-            sh[threadIdx.x] += y;
-            __syncthreads();
+    for (int64_t base = 0; base < nst; base += (int64_t)blockDim.x * kCsrPer) {
+        const int64_t q0 = base + (int64_t)threadIdx.x * kCsrPer;
+        int64_t x[kCsrPer], mine = 0;
+#pragma unroll
+        for (int i = 0; i < kCsrPer; ++i) {
+            x[i] = q0 + i < nst ? (int64_t)a.shower_tel[q0 + i] : 0;
+            mine += x[i];
         }
-        if (q < nst) a.tel_offsets[q] = run + sh[threadIdx.x] - x;
-        run += sh[blockDim.x - 1];
+        const int64_t incl = wave_incl_scan(mine);
+        if (lane == kWave - 1) sums[wave] = incl;
+        __syncthreads();
+        int64_t at = run + incl - mine, all = 0;
+        for (int w = 0; w < nw; ++w) {
+            if (w < wave) at += sums[w];
+            all += sums[w];
+        }
+#pragma unroll
+        for (int i = 0; i < kCsrPer; ++i) {
+            if (q0 + i < nst) a.tel_offsets[q0 + i] = at;
+            at += x[i];
+        }
+        run += all;
         __syncthreads();
     }
     if (threadIdx.x == 0) {
@@ -2686,9 +2669,31 @@ __global__ void __launch_bounds__(1024) csr_kernel(Args a)
     }
 }
 
-// F: scatter the staged records of the written tiles to their final slots.  A
+__global__ void __launch_bounds__(1024) csr_kernel(Args a) { write_offsets(a); }
+
+// Cutoff, row-block scan and offsets in one workgroup, for at most kFinishPairs (shower,
+// telescope) pairs (8 columns a wave) and kFinishBlocks row blocks (130 000 steps): 6.7 us
+// instead of three launches of 4.7 and their gaps.  With 977 row blocks and 100 spheres
+// its columns take 82 us against 17 in three kernels.
+constexpr int kFinishPairs = 128;
+constexpr int kFinishBlocks = 64;
+
+__global__ void __launch_bounds__(1024) finish_kernel(Args a)
+{
+    extern __shared__ int32_t acc[];               // n_tel
+    find_cutoff(a, acc);
+    __threadfence_block();
+    __syncthreads();
+    scan_row_blocks(a, threadIdx.x / kWave, blockDim.x / kWave);
+    __threadfence_block();
+    __syncthreads();
+    write_offsets(a);
+}
+
+// E: scatter the staged records of the written tiles to their final slots.  A
 // slot's place is its (shower, telescope) offset, plus its telescope's crossings
-// in earlier tiles of the shower (its run's value), plus its rank in the tile.
+// in earlier row blocks of the shower and in earlier tiles of its block (its run's
+// value), plus its rank in the tile.
 // Each thread takes kScatterSlots slots a round and issues the loads that do not
 // depend on one another together: the block fills, then the entries (record and
 // placement at once), then the tile's run list, the shower's offset and the
@@ -2732,7 +2737,9 @@ __device__ __forceinline__ void scatter_tile(const Args& a, ScatterSlot& x, cons
         x.shower = find_shower(before, a.n_showers, tile);
         x.off = a.tile_run_off[tile];
         x.n = a.tile_run_n[tile];
-        x.base = a.tel_offsets[(int64_t)x.shower * a.n_tel + x.tel];
+        const int64_t b = a.blocks_before[x.shower] + (tile - before[x.shower]) / kRowBlock;
+        x.base = a.tel_offsets[(int64_t)x.shower * a.n_tel + x.tel] +
+                 a.block_sums[(int64_t)x.tel * a.max_row_blocks + b];
     }
     x.len = x.n;
 }
@@ -3858,22 +3865,28 @@ int launch_run(RunPlan& p)
     if (p.params.event_end) (void)hipEventRecord((hipEvent_t)p.params.event_end, st);
     const int fin_grid = 1024;
     const size_t tel_lds = (size_t)a.n_tel * sizeof(int32_t);
-    block_sum_kernel<<<fin_grid, 256, tel_lds, st>>>(a);
-    if (int rc2 = check_launch("block_sum")) return rc2;
-    cutoff_kernel<<<1, 1024, tel_lds, st>>>(a);
-    if (int rc2 = check_launch("cutoff")) return rc2;
-    rowblock_scan_kernel<<<fin_grid, 256, 0, st>>>(a);
-    if (int rc2 = check_launch("rowblock_scan")) return rc2;
     if (a.n_tel <= kPrefixDenseTel) {
-        tile_prefix_dense_kernel<<<fin_grid, 256, (size_t)kRowBlock * a.n_tel * sizeof(int32_t), st>>>(a);
+        // (256 threads for up to 128 telescopes: several workgroups share a compute unit)
+        allow_lds((const void*)block_prefix_dense_kernel, kRowBlock * kPrefixDenseTel * sizeof(int32_t));
+        block_prefix_dense_kernel<<<fin_grid, a.n_tel <= 128 ? 256 : 1024,
+                                    (size_t)kRowBlock * a.n_tel * sizeof(int32_t), st>>>(a);
     } else {
         const size_t prefix_lds = (size_t)((a.n_tel + 1) & ~1) * sizeof(int32_t) +
                                   (size_t)kPrefixLdsRuns * sizeof(int64_t);
-        tile_prefix_kernel<<<fin_grid, kWave, prefix_lds, st>>>(a);
+        block_prefix_kernel<<<fin_grid, kWave, prefix_lds, st>>>(a);
     }
-    if (int rc2 = check_launch("tile_prefix")) return rc2;
-    csr_kernel<<<1, 1024, 0, st>>>(a);
-    if (int rc2 = check_launch("csr")) return rc2;
+    if (int rc2 = check_launch("block_prefix")) return rc2;
+    if ((int64_t)a.n_showers * a.n_tel <= kFinishPairs && a.max_row_blocks <= kFinishBlocks) {
+        finish_kernel<<<1, 1024, tel_lds, st>>>(a);
+        if (int rc2 = check_launch("finish")) return rc2;
+    } else {
+        cutoff_kernel<<<1, 1024, tel_lds, st>>>(a);
+        if (int rc2 = check_launch("cutoff")) return rc2;
+        rowblock_scan_kernel<<<fin_grid, 256, 0, st>>>(a);
+        if (int rc2 = check_launch("rowblock_scan")) return rc2;
+        csr_kernel<<<1, 1024, 0, st>>>(a);
+        if (int rc2 = check_launch("csr")) return rc2;
+    }
     scatter_kernel<<<4096, 256, 0, st>>>(a);
     return check_launch("scatter");
 }

@@ -455,3 +455,28 @@ def test_step_ids_keep_bunches_when_steps_are_reordered(precision):
         np.testing.assert_array_equal(ids[sl][order], one["ids"][o[t]:o[t + 1]])
         np.testing.assert_array_equal(rec[sl][order].view(np.uint32),
                                       one["rec"][o[t]:o[t + 1]].view(np.uint32))
+
+
+@pytest.mark.parametrize("n_tel", [31, 33, 127, 512, 513])
+def test_finalize_forms_by_sphere_count(n_tel):
+    """Sphere counts on both sides of the switches of the step setup (all spheres or the
+    lists near its ground point) and of the finalize (one workgroup or three kernels,
+    dense counts or tile walk), whole and cut short by a full output: offsets and ids
+    are the oracle's, and a run resumed at the cursor gives the rest."""
+    import dataclasses
+    wl = synth.single_tev(3000)
+    wl = dataclasses.replace(wl, tels=synth.telescopes_disk(n_tel, disk_radius=100.0 * np.sqrt(n_tel)))
+    cfg = oracle.Config.from_workload(wl)
+    r = oracle.run(cfg, wl.segs, nthreads=8)
+    g = gpu_run(wl, ckv.CKV_FP64, capacity=len(r.seg) + 8)
+    np.testing.assert_array_equal(g["offsets"], r.offsets)
+    np.testing.assert_array_equal(g["ids"][:, 0], r.seg)
+    np.testing.assert_array_equal(g["ids"][:, 1], r.k)
+    # the steps before the cursor, complete and in order
+    cut = gpu_run(wl, ckv.CKV_FP64, capacity=len(r.seg) // 3)
+    res = cut["result"]
+    assert res["overflow"] == 1 and 0 < res["resume_step"] < wl.segs.n
+    first = r.seg < res["resume_step"]
+    assert res["n_records"] == first.sum()
+    np.testing.assert_array_equal(cut["ids"][:, 0], r.seg[first])
+    np.testing.assert_array_equal(cut["ids"][:, 1], r.k[first])
