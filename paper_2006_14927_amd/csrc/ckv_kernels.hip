@@ -731,7 +731,6 @@ __host__ __device__ inline size_t wave_bytes(int prec, int tile_segs, int n_tel,
                ((prec == 0 ? sizeof(StepEntry<0>) : sizeof(StepEntry<1>)) + sizeof(StepPass));
     b += (size_t)kWave * kSectorWords * sizeof(uint32_t);
     b += (size_t)kQueue * (sizeof(uint32_t) + sizeof(uint8_t));  // queue (tile setup: pairs)
-    b += kWave * sizeof(int32_t);                       // flag row
     b += (size_t)kWcCount * sizeof(int64_t);            // counters
     b += ((size_t)n_tel * sizeof(int32_t) + 15) & ~(size_t)15;   // telescope counters
     if (prof_bins) b += 2 * sizeof(int64_t) + (size_t)prof_bins * (sizeof(double) + sizeof(uint32_t));
@@ -881,7 +880,6 @@ struct WaveArea {
     uint32_t* masks;           // kSectorWords per step of the unit
     uint32_t* qk;              // waiting bunches: bunch in its step ...
     uint8_t* qs;               // ... and stash entry; setup: (sphere << 8) | step pairs
-    int32_t* flags;
     int64_t* wcnt;
     int32_t* tcount;
     int64_t* prof;             // profile: shower of the bins below (-1: none), their bunches
@@ -895,7 +893,6 @@ struct WaveArea {
         masks = reinterpret_cast<uint32_t*>(take(kWave * kSectorWords * sizeof(uint32_t)));
         qk = reinterpret_cast<uint32_t*>(take(kQueue * sizeof(uint32_t)));
         qs = take(kQueue);
-        flags = reinterpret_cast<int32_t*>(take(kWave * sizeof(int32_t)));
         wcnt = reinterpret_cast<int64_t*>(take(kWcCount * sizeof(int64_t)));
         tcount = reinterpret_cast<int32_t*>(take(((size_t)n_tel * sizeof(int32_t) + 15) & ~(size_t)15));
         prof = reinterpret_cast<int64_t*>(take(prof_bins ? 2 * sizeof(int64_t) : 0));
@@ -1502,7 +1499,6 @@ __global__ void __launch_bounds__(emit_threads(PREC, FEAT)) emit_kernel(Args a)
     uint64_t* const buf = reinterpret_cast<uint64_t*>(wbase + wv_bytes);
     int buf_n = 0;
     Entry* const stash = wa.stash;
-    int32_t* const flags = wa.flags;
     int64_t* const wcnt = wa.wcnt;
     int32_t* const tcount = wa.tcount;
     for (int k = lane; k < n_count; k += kWave) tcount[k] = 0;
@@ -1511,7 +1507,6 @@ __global__ void __launch_bounds__(emit_threads(PREC, FEAT)) emit_kernel(Args a)
         if (lane < 2) wa.prof[lane] = lane == 0 ? -1 : 0;
     }
     if (lane < kWcCount) wcnt[lane] = 0;
-    flags[lane] = 0;
     __syncthreads();
 
     const T a1 = (T)-0.5, a2 = (T)0.375, a3 = (T)-0.3125, a4 = (T)0.2734375;
@@ -1671,12 +1666,11 @@ __global__ void __launch_bounds__(emit_threads(PREC, FEAT)) emit_kernel(Args a)
                 const int32_t j = c0 + lane;
                 const bool active = j < c_end;
                 // step of bunch j: the pass's steps starting at or before c0, plus those
-                // starting inside this chunk at or before j (flag row)
+                // starting inside this chunk at or before j (one to three, by lane reads)
                 const int cnt0 = __popcll(__ballot(in_pass && excl <= c0));
-                if (in_pass && excl > c0 && excl < c0 + kWave) flags[excl - c0] = 1;
-                wave_lds_sync();
-                const uint64_t starts = __ballot(flags[lane] != 0);
-                flags[lane] = 0;
+                uint64_t starts = 0;
+                for (uint64_t in = __ballot(in_pass && excl > c0 && excl < c0 + kWave); in; in &= in - 1)
+                    starts |= 1ull << (__builtin_amdgcn_readlane(excl, __builtin_ctzll(in)) - c0);
                 const int si = cnt0 - 1 + __popcll(starts & le_mask);
                 // Philox round keys, advanced on the scalar unit inside the loop
                 const uint32_t opaque = (uint32_t)((uint64_t)(uint32_t)c0 >> 31);   // 0; keeps the schedule in the loop
@@ -2086,7 +2080,7 @@ __global__ void __launch_bounds__(emit_threads(PREC, FEAT)) emit_kernel(Args a)
                             else if (nbk >= 0) slot = nbk * kStageBlock + (below - room);
                             if (slot >= 0) {
                                 StageEntry* se = a.stage + slot;
-                                const double* tp = a.tel + 4 * kmin;
+                                const double* tp = tel_sh + 3 * kmin;
                                 float4* ef = reinterpret_cast<float4*>(se);
                                 ef[0] = make_float4((float)(xg - tp[0]), (float)(yg - tp[1]), uo, vo);
                                 ef[1] = make_float4(t_f, he_f, photons, lam);
@@ -2103,8 +2097,8 @@ __global__ void __launch_bounds__(emit_threads(PREC, FEAT)) emit_kernel(Args a)
                         } else {
                             blk_fill += nmine;
                         }
+                        // (no other turn of this chunk reads it, and a wave's LDS accesses are in order)
                         if (lane == 0) tcount[kmin] = rank0 + nmine;
-                        wave_lds_sync();
                         if (mine) advance(kb);
                     }
                 }
