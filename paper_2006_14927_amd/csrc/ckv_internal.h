@@ -69,6 +69,7 @@ enum CtrlSlot {
     kRunCounter = 64,   // next run block to claim
     kNumTiles = 96,    // tiles of this run
     kNumRowBlocks,      // row blocks of the per-telescope scan
+    kReportTiles,       // tiles of the report's size
     kHits,              // crossings found
     kBunches,           // bunches generated
     kEmitting,          // steps with light
@@ -200,6 +201,7 @@ struct RunPlan {
     hipStream_t stream;
     // derived
     int32_t tile_segs;
+    int32_t report_segs;        // tile size of the report and of a cut (a multiple of tile_segs)
     int64_t max_tiles, max_row_blocks, stage_slots;
     int32_t emit_grid, emit_waves;
     int32_t prof_bins;          // longitudinal-profile bins, 0 = no profile
@@ -224,6 +226,9 @@ struct RunPlan {
     StageEntry* stage;          // stage_slots
 };
 
+// smaller tiles for a run that leaves waves idle (see its definition); after the layout
+// and emit_grid
+void refine_tiles(int64_t n_segments, int32_t n_showers, int32_t n_tel, RunPlan* plan);
 size_t workspace_layout(int64_t n_segments, int32_t n_showers, int32_t n_tel, int64_t capacity,
                         const ckv_params* p, RunPlan* plan, void* base);
 // ckv_run after its handle-free checks: validates, lays out `workspace` and launches
@@ -237,7 +242,7 @@ int launch_count(const ckv_segments* segs, const ckv_params* p, const ckv_atmo* 
                  int64_t* n_b, hipStream_t stream);
 // waves per bunch-kernel workgroup (at most max_waves) and its LDS bytes
 int emit_config(int precision, int n_tel, int prof_bins, const ckv_atmo* atmo, int tile_segs,
-                int max_waves, int* waves, size_t* lds_bytes, bool many_nodes_ok);
+                int limit_segs, int max_waves, int* waves, size_t* lds_bytes, bool many_nodes_ok);
 
 struct SoftPlan {
     const int64_t* n_b_frozen;

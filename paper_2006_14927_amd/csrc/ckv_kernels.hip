@@ -76,6 +76,7 @@ struct Args {
     double r_obs;               // earth_r + h_obs
     uint32_t key0, key1;
     int32_t tile_segs;
+    int32_t report_segs;        // tile size of the report and of a cut (a multiple of it)
     // first step of the run (a resume cursor; step 0 of shower 0 without one)
     int64_t cur_step;
     int32_t cur_shower;
@@ -2215,11 +2216,12 @@ __global__ void __launch_bounds__(emit_threads(PREC, FEAT)) emit_kernel(Args a)
 __global__ void __launch_bounds__(1024) init_kernel(Args a)
 {
     __shared__ int64_t sh_t[1024], sh_b[1024];
+    __shared__ unsigned long long report;
     __shared__ int err;
     for (int q = threadIdx.x; q < kCtrlSlots; q += blockDim.x) a.ctrl[q] = 0;
     if (a.claims)
         for (int q = threadIdx.x; q < kTileClasses; q += blockDim.x) a.claims[kClaimStride * q] = 0;
-    if (threadIdx.x == 0) err = 0;
+    if (threadIdx.x == 0) { err = 0; report = 0; }
     __syncthreads();
     const int64_t TS = a.tile_segs;
     int64_t run_t = 0, run_b = 0;
@@ -2244,6 +2246,8 @@ __global__ void __launch_bounds__(1024) init_kernel(Args a)
             const int64_t cnt = hi >= first ? hi - first : 0;
             nt = (cnt + TS - 1) / TS;
             nbk = (nt + kRowBlock - 1) / kRowBlock;
+            if (TS != a.report_segs)
+                atomicAdd(&report, (unsigned long long)((cnt + a.report_segs - 1) / a.report_segs));
         }
         sh_t[threadIdx.x] = nt;
         sh_b[threadIdx.x] = nbk;
@@ -2270,6 +2274,7 @@ __global__ void __launch_bounds__(1024) init_kernel(Args a)
         if (run_t > a.max_tiles || run_b > a.max_row_blocks) err = 1;
         a.ctrl[kNumTiles] = err ? 0 : run_t;
         a.ctrl[kNumRowBlocks] = err ? 0 : run_b;
+        a.ctrl[kReportTiles] = err ? 0 : TS != a.report_segs ? (int64_t)report : run_t;
         a.ctrl[kFirstLost] = err ? 0 : run_t;      // no lost tile yet
         int64_t dealt = 0;
         if (!err && a.static_blocks > 0) {
@@ -2522,6 +2527,10 @@ __device__ __forceinline__ void find_cutoff(const Args& a, int32_t* acc)
         block_tiles(a, blk_b, s, t0, t1);
         int64_t cum = blk_before, t = t0;
         while (t < t1 && t < lost && cum + a.tile_hits[t] <= a.capacity) cum += a.tile_hits[t++];
+        // (a cut inside a tile of the report's size goes back to its start)
+        if (t < t1)
+            for (int64_t back = (t - a.tiles_before[s]) % (a.report_segs / a.tile_segs); back > 0; --back)
+                cum -= a.tile_hits[--t];
         cut_tile = t;
         cut_block = t > t0 ? blk_b + 1 : blk_b;
         cut_records = cum;
@@ -2648,7 +2657,7 @@ __device__ __forceinline__ void write_offsets(const Args& a)
         r->n_hits = a.ctrl[kHits];
         r->n_records = a.ctrl[kRecords];
         r->n_emitting = a.ctrl[kEmitting];
-        r->n_tiles = n_tiles;
+        r->n_tiles = a.ctrl[kReportTiles];
         for (int d = 0; d < CKV_N_DROP; ++d) r->drops[d] = a.ctrl[kDrop0 + d];
         if (cut < n_tiles) {
             const int sc = find_shower(a.tiles_before, a.n_showers, cut);
@@ -3692,6 +3701,7 @@ Args make_args(const RunPlan& p)
     a.key0 = (uint32_t)p.params.seed;
     a.key1 = (uint32_t)(p.params.seed >> 32);
     a.tile_segs = p.tile_segs;
+    a.report_segs = p.report_segs;
     a.cur_step = p.cursor.step;
     a.cur_shower = p.cursor.shower;
     a.ctrl = p.ctrl;
@@ -3746,14 +3756,14 @@ int check_launch(const char* what)
 }  // namespace
 
 int emit_config(int precision, int n_tel, int prof_bins, const ckv_atmo* atmo, int tile_segs,
-                int max_waves, int* waves, size_t* lds_bytes, bool many_nodes_ok)
+                int limit_segs, int max_waves, int* waves, size_t* lds_bytes, bool many_nodes_ok)
 {
     const size_t srch = atmo->h_nodes.empty() ? 0 : search_bytes((int)atmo->n_nodes);
     const size_t cap = 160 * 1024;
     const size_t per = wave_bytes(precision, tile_segs, n_tel, prof_bins);
     auto beside_table = [&](bool part, int wv) {
         return ((table_bytes(precision, (int)atmo->n_nodes, part) + 15) & ~(size_t)15) + srch + tel_bytes(n_tel) +
-                   (size_t)wv * limit_wave_bytes(precision, tile_segs, n_tel, prof_bins) <= cap;
+                   (size_t)wv * limit_wave_bytes(precision, limit_segs, n_tel, prof_bins) <= cap;
     };
     if (beside_table(prof_bins > 0, 1) || (many_nodes_ok && beside_table(true, kMaxEmitWaves)))
         for (int wv = kMaxEmitWaves; wv >= 1; wv /= 2) {
@@ -3807,6 +3817,10 @@ template <int PREC>
 int launch_emit_ts(const Args& a, int ts, int grid, int waves, size_t lds, hipStream_t st)
 {
     switch (ts) {
+        case 2:
+            if (a.grazing_exact && a.prof_bins == 0 && !a.hnodes && a.earth_r <= 0.0)
+                return launch_emit<PREC, 2, kFeatExact>(a, grid, waves, lds, st);
+            break;
         case 8: return launch_emit_feat<PREC, 8>(a, grid, waves, lds, st);
         case 16: return launch_emit_feat<PREC, 16>(a, grid, waves, lds, st);
         case 32: return launch_emit_feat<PREC, 32>(a, grid, waves, lds, st);
@@ -3830,8 +3844,8 @@ int launch_run(RunPlan& p)
     const bool many_nodes_ok = p.params.precision == 0 && p.params.waves_per_group == kMaxEmitWaves &&
                                p.prof_bins == 0 && !p.params.grazing_exact &&
                                p.params.earth_radius_m <= 0.0 && p.atmo->h_nodes.empty();
-    if (int rc = emit_config(p.params.precision, a.n_tel, p.prof_bins, p.atmo, p.tile_segs, cap, &waves,
-                             &lds, many_nodes_ok))
+    if (int rc = emit_config(p.params.precision, a.n_tel, p.prof_bins, p.atmo, p.tile_segs, p.report_segs, cap,
+                             &waves, &lds, many_nodes_ok))
         return rc;
     set_sectors(a, p.atmo, p.arr->rmax, p.arr->dmax);
     a.grid_waves = p.emit_grid * waves;
@@ -3888,7 +3902,7 @@ int launch_run(RunPlan& p)
 int launch_soft(RunPlan& p, const SoftPlan& sp, int mode)
 {
     Args a = make_args(p);
-    a.tile_segs = kSoftTS;          // the soft kernels walk 32-step tiles
+    a.tile_segs = a.report_segs = kSoftTS;          // the soft kernels walk 32-step tiles
     hipStream_t st = p.stream;
     const ckv_array* ar = p.arr;
     // the per-step cull's bound constants (screen_annulus), for the screening pass and
@@ -4035,7 +4049,7 @@ int launch_count(const ckv_segments* segs, const ckv_params* prm, const ckv_atmo
     p.atmo = atmo;
     p.arr = nullptr;
     p.k_ft = k_ft;
-    p.tile_segs = 1;
+    p.tile_segs = p.report_segs = 1;
     Args a = make_args(p);
     if (segs->n == 0) return CKV_OK;
     const int64_t blocks = std::min<int64_t>((segs->n + 255) / 256, 65536);

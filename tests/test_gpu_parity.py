@@ -480,3 +480,20 @@ def test_finalize_forms_by_sphere_count(n_tel):
     assert res["n_records"] == first.sum()
     np.testing.assert_array_equal(cut["ids"][:, 0], r.seg[first])
     np.testing.assert_array_equal(cut["ids"][:, 1], r.k[first])
+
+
+@pytest.mark.parametrize("n_seg,grazing", [(1, False), (300, False), (8192, False), (8193, False), (32769, False),
+                                           (40, True), (700, True)])
+def test_default_tiles_report_and_cut_as_32_step_tiles(n_seg, grazing):
+    """Short runs of default tiles work in smaller ones: the report, the records and where
+    a full output cuts the run are those of 32-step tiles."""
+    wl = synth.grazing_tracks(n_seg) if grazing else synth.vertical_gamma(n_seg)
+    full = gpu_run(wl, ckv.CKV_MIXED, tile_segments=32, grazing_exact=grazing,
+                   capacity=n_seg * (2000 if grazing else 8) + 4096)
+    assert full["result"]["overflow"] == 0
+    for cap in (full["result"]["n_records"], full["result"]["n_records"] // 2, 0):
+        a = gpu_run(wl, ckv.CKV_MIXED, tile_segments=32, grazing_exact=grazing, capacity=cap)
+        b = gpu_run(wl, ckv.CKV_MIXED, grazing_exact=grazing, capacity=cap)
+        assert a["result"] == b["result"]
+        for f in ("offsets", "rec", "ids"):
+            np.testing.assert_array_equal(a[f], b[f])
