@@ -125,6 +125,7 @@ struct Args {
     double reach_x0, reach_y0, reach_inv;
     int32_t reach_nx, reach_ny;
     int64_t* claims;            // claim counters, kClaimStride apart
+    int32_t span_tiles;         // tiles of a unit whose bunches a wave takes together
     int32_t grid_waves;         // waves of the bunch kernel's launch
     int32_t static_blocks;      // staging and run blocks dealt to them beforehand
 };
@@ -1344,8 +1345,7 @@ __device__ __forceinline__ TileSetup tile_setup(const Args& a, int64_t t0, int h
     in_pass = in_pass && now;
     if (over && now && lane == l_first && a.result) atomicOr(&a.result->error, 2);
     const bool masked = in_pass && cone;
-    const uint64_t tile_masked = (__ballot(masked) >> l_first) & (~0ull >> (64 - TS));
-    if (in_pass && !cone && tile_masked) {
+    if (__ballot(masked) != 0ull && in_pass && !cone) {
         // no bound for this step: every azimuth
 #pragma unroll
         for (int q = 0; q < kSectorWords; ++q) wa.masks[kSectorWords * lane + q] = 0xFFFFFFFFu;
@@ -1424,7 +1424,7 @@ __device__ __noinline__ TileSetup tile_setup_call(uint64_t args_at, int64_t t0, 
     extern __shared__ __align__(16) unsigned char lds[];
     const Args& a = args_from(args_at);
     const WaveArea<PREC, TS> wa(lds + __builtin_amdgcn_readfirstlane((int)area_at),
-                                (FEAT & kFeatScreen) != 0 ? 0 : a.n_tel, (FEAT & kFeatProfile) != 0 ? a.prof_bins : 0);
+                                (FEAT & kFeatScreen) != 0 ? 0 : a.n_tel * a.span_tiles, (FEAT & kFeatProfile) != 0 ? a.prof_bins : 0);
     return tile_setup<PREC, TS, FEAT>(a, scalar64(t0), __builtin_amdgcn_readfirstlane(h_first),
                                       __builtin_amdgcn_readfirstlane(h_all), lane, lt_mask, wa,
                                       reinterpret_cast<const double*>(
@@ -1491,7 +1491,7 @@ __global__ void __launch_bounds__(emit_threads(PREC, FEAT)) emit_kernel(Args a)
         tel_sh[3 * q + 2] = a.tel[4 * q + 3];
     }
     const int prof_bins = PROF ? a.prof_bins : 0;
-    const int n_count = SCREEN ? 0 : a.n_tel;      // spheres counted per tile
+    const int n_count = SCREEN ? 0 : a.n_tel * a.span_tiles;      // crossings counted per tile and sphere
     const size_t wv_bytes = wave_bytes(PREC, TS, n_count, prof_bins);
     const size_t wv_stride = wv_bytes + (SCREEN ? kScreenBuf * sizeof(uint64_t) : 0);
     unsigned char* wbase = lds + srch_bytes + tel_bytes(a.n_tel) + (size_t)wave * wv_stride;
@@ -1529,7 +1529,7 @@ __global__ void __launch_bounds__(emit_threads(PREC, FEAT)) emit_kernel(Args a)
 
     int64_t blk = -1;          // current staging block; -1: none, -2: staging full
     int blk_fill = 0;
-    bool lost = false;         // a crossing of this wave found no slot (tile marked)
+    int64_t lost = INT64_MAX;  // first tile of this wave with a crossing that found no slot
     int64_t rblk = -1;         // current run block; -1: none
     int rfill = 0;
     const int64_t n_tiles = a.ctrl[kNumTiles];
@@ -1637,7 +1637,7 @@ __global__ void __launch_bounds__(emit_threads(PREC, FEAT)) emit_kernel(Args a)
         const int h_all = wide ? kWave / TS : 1;
         TileSetup ts_;
         ts_.h_end = 0;
-        for (int h = 0; h < h_all; ++h) {
+        for (int h = 0, h_next; h < h_all; h = h_next) {
         // ---- step setups of the unit (called out of line, with the arguments where the
         // launch put them, the kernel argument segment, rather than a private copy)
         if (h >= ts_.h_end) {
@@ -1647,18 +1647,20 @@ __global__ void __launch_bounds__(emit_threads(PREC, FEAT)) emit_kernel(Args a)
             ts_.h_end = __builtin_amdgcn_readfirstlane(ts_.h_end);
             wave_lds_sync();
         }
-        const int64_t t = t0 + h;
+        // ---- a span: tiles of one shower that were set up together, their bunches taken
+        // together (a tile's fill 1.3 chunks of the second pass, two tiles' 1.8)
         const int s = __builtin_amdgcn_readlane(ts_.shower, h * TS);
+        for (h_next = h + 1; h_next < ts_.h_end && h_next < h + a.span_tiles; ++h_next)
+            if (__builtin_amdgcn_readlane(ts_.shower, h_next * TS) != s) break;
         const uint32_t shower_id = a.shower_ids ? a.shower_ids[s] : (uint32_t)s;
         const double t_ref = a.t_ref[s];
-        int32_t thits = 0;         // crossings of this tile (wave-uniform)
         const bool in_pass = ts_.in_pass;
         const int excl = ts_.excl;
-        const int c_end = __builtin_amdgcn_readlane(ts_.incl, h * TS + TS - 1);
-        // every bunch of the tile is taken, whatever its azimuth
-        const bool direct = ((__ballot(ts_.masked) >> (h * TS)) & (~0ull >> (64 - TS))) == 0ull;
+        const int c_end = __builtin_amdgcn_readlane(ts_.incl, h_next * TS - 1);
+        // every bunch is taken, whatever its azimuth
+        const bool direct = __ballot(ts_.masked) == 0ull;
 
-        // ---- bunches of the tile.  First pass, one bunch per lane: its azimuth's draw
+        // ---- bunches of the span.  First pass, one bunch per lane: its azimuth's draw
         // against its step's sectors; the bunches that may reach a sphere wait in the
         // queue until 64 are there, in (step, bunch) order.
         int c0 = __builtin_amdgcn_readlane(excl, h * TS), qn = 0;
@@ -1994,8 +1996,8 @@ __global__ void __launch_bounds__(emit_threads(PREC, FEAT)) emit_kernel(Args a)
                 // candidates of the soft response: gathered in the wave's buffer, which goes
                 // to the list when full (one atomic on the list's count for each 256 or so:
                 // claims of all waves come 13 ns apart)
-                const uint64_t step = (uint64_t)(a.shower_first[s] + (t - a.tiles_before[s]) * (int64_t)TS +
-                                                 (stash[active ? si : 0].sidx & (TS - 1)));
+                const uint64_t step = (uint64_t)(a.shower_first[s] + (t0 - a.tiles_before[s]) * (int64_t)TS +
+                                                 stash[active ? si : 0].sidx);
                 bool cand = my_next != INT_MAX || screen_all;
                 if (sweep)
                     for (int kb = 0; kb < a.n_tel; kb += 32) {
@@ -2024,7 +2026,7 @@ __global__ void __launch_bounds__(emit_threads(PREC, FEAT)) emit_kernel(Args a)
                 if (sweep || __ballot(my_next != INT_MAX)) {
                     if (sweep ? alive : my_next != INT_MAX) {
                         const Entry& er = stash[si];
-                        sidx_rec = er.sidx & (TS - 1);
+                        sidx_rec = er.sidx;
                         photons = (float)er.photons;
                         if (PREC == 0) {
                             lam = (float)rcp64(a.inv_l1 - fma((double)r2_rec, 2.3283064365386963e-10,
@@ -2048,17 +2050,45 @@ __global__ void __launch_bounds__(emit_threads(PREC, FEAT)) emit_kernel(Args a)
                         he_f = (float)he;
                     }
                 }
-                // ---- record crossings; telescopes in ascending order, lanes (bunches) in order
+                // ---- record crossings.  A turn takes lanes with one sphere each, all lanes of a
+                // sphere in the same turn, in bunch order: every crossing lane when none has
+                // another sphere to come, else those of the lowest sphere.
                 for (int kb = 0; kb < (sweep ? a.n_tel : 1); kb += 32) {
                     if (sweep) sweep_from(kb);
-                    while (__ballot(my_next != INT_MAX)) {
-                        const int kmin = wave_min_sparse(my_next, INT_MAX);
-                        const bool mine = my_next == kmin;
+                    for (;;) {
+                        const uint64_t any = __ballot(my_next != INT_MAX);
+                        if (!any) break;
+                        bool more = sweep ? (hits & (hits - 1)) != 0u : false;
+                        if (!sweep && my_next != INT_MAX && cur < cend) {
+                            // the rest of the lane's list, up to its next sphere
+                            int c = cur;
+                            while (c < cend && !more) more = crosses((int)a.cell_list[c++]);
+                            cur = more ? c - 1 : cend;
+                        }
+                        const bool last = __ballot(more && my_next != INT_MAX) == 0ull;
+                        const bool mine = my_next == (last ? my_next : wave_min_sparse(my_next, INT_MAX)) &&
+                                          my_next != INT_MAX;
                         const uint64_t mask = __ballot(mine);
                         const int nmine = __popcll(mask);
                         const int below = __popcll(mask & lt_mask);
-                        const int rank0 = tcount[kmin];
-                        thits += nmine;
+                        // rank among the turn's crossings of the same tile and sphere, then the
+                        // crossings of earlier turns
+                        const int key = mine ? (sidx_rec / TS - h) * a.n_tel + my_next : -1;
+                        int rank = 0, of_key = 0;
+                        for (uint64_t rest = mask; rest;) {
+                            const int kk = __builtin_amdgcn_readlane(key, __builtin_ctzll(rest));
+                            const uint64_t same = __ballot(key == kk);
+                            if (key == kk) {
+                                rank = __popcll(same & lt_mask);
+                                of_key = __popcll(same);
+                            }
+                            rest &= ~same;
+                        }
+                        if (mine) {
+                            const int before = tcount[key];
+                            if (rank == 0) tcount[key] = before + of_key;
+                            rank += before;
+                        }
                         // staging slots: the first `room` crossings fill the current
                         // block, the rest start a newly claimed one
                         const int room = blk >= 0 ? kStageBlock - blk_fill : 0;
@@ -2069,11 +2099,15 @@ __global__ void __launch_bounds__(emit_threads(PREC, FEAT)) emit_kernel(Args a)
                             nbk = uniform(nbk);
                             if (nbk >= a.stage_blocks) nbk = -2;
                         }
-                        if (nmine > room && nbk < 0 && !lost) {
-                            // crossings of this tile find no slot: the run's written prefix
-                            // ends before it (this wave's later tiles come after it)
-                            lost = true;
-                            if (lane == 0) atomicMin((unsigned long long*)&a.ctrl[kFirstLost], (unsigned long long)t);
+                        if (nmine > room && nbk < 0) {
+                            // crossings find no slot: the run's written prefix ends before the
+                            // first one's tile (lanes are in tile order)
+                            const uint64_t none = __ballot(mine && below >= room);
+                            const int64_t tl = t0 + __builtin_amdgcn_readlane(sidx_rec, __builtin_ctzll(none)) / TS;
+                            if (tl < lost) {
+                                lost = tl;
+                                if (lane == 0) atomicMin((unsigned long long*)&a.ctrl[kFirstLost], (unsigned long long)tl);
+                            }
                         }
                         if (mine) {
                             int64_t slot = -1;
@@ -2081,13 +2115,14 @@ __global__ void __launch_bounds__(emit_threads(PREC, FEAT)) emit_kernel(Args a)
                             else if (nbk >= 0) slot = nbk * kStageBlock + (below - room);
                             if (slot >= 0) {
                                 StageEntry* se = a.stage + slot;
-                                const double* tp = tel_sh + 3 * kmin;
+                                const double* tp = tel_sh + 3 * my_next;
                                 float4* ef = reinterpret_cast<float4*>(se);
                                 ef[0] = make_float4((float)(xg - tp[0]), (float)(yg - tp[1]), uo, vo);
                                 ef[1] = make_float4(t_f, he_f, photons, lam);
                                 uint4* eu = reinterpret_cast<uint4*>(se);
-                                eu[2] = make_uint4((uint32_t)t, (uint32_t)kmin | ((uint32_t)sidx_rec << 16),
-                                                   (uint32_t)(rank0 + below), (uint32_t)k);
+                                eu[2] = make_uint4((uint32_t)(t0 + sidx_rec / TS),
+                                                   (uint32_t)my_next | ((uint32_t)(sidx_rec & (TS - 1)) << 16),
+                                                   (uint32_t)rank, (uint32_t)k);
                             }
                         }
                         if (nmine > room) {
@@ -2098,8 +2133,6 @@ __global__ void __launch_bounds__(emit_threads(PREC, FEAT)) emit_kernel(Args a)
                         } else {
                             blk_fill += nmine;
                         }
-                        // (no other turn of this chunk reads it, and a wave's LDS accesses are in order)
-                        if (lane == 0) tcount[kmin] = rank0 + nmine;
                         if (mine) advance(kb);
                     }
                 }
@@ -2107,16 +2140,22 @@ __global__ void __launch_bounds__(emit_threads(PREC, FEAT)) emit_kernel(Args a)
         }
         // the next unit's claim, on its way during the rest (claimed any earlier, the launch
         // ends unevenly: shells at 70 degrees 398 -> 480 us)
-        if (h + 1 == h_all && lane == 0)
+        if (h_next == h_all && lane == 0)
             claimed = (int64_t)atomicAdd((unsigned long long*)&a.claims[kClaimStride * cls], 1ull);
-        // ---- per-telescope crossings of this tile as runs (ascending telescope)
+        // ---- per-telescope crossings of each tile as runs (ascending telescope)
         wave_lds_sync();
-        if (!SCREEN && t < a.max_tiles) {
+        for (int hh = h; !SCREEN && hh < h_next; ++hh) {
+            const int64_t t = t0 + hh;
+            int32_t* const tc = tcount + (hh - h) * a.n_tel;
             int nz = 0;
+            int64_t found = 0;
             for (int k0 = 0; k0 < a.n_tel; k0 += kWave) {
                 const int kk = k0 + lane;
-                nz += __popcll(__ballot(kk < a.n_tel && tcount[kk] != 0));
+                const int32_t c = kk < a.n_tel ? tc[kk] : 0;
+                nz += __popcll(__ballot(c != 0));
+                found += c;
             }
+            const int32_t thits = (int32_t)wave_last(wave_incl_scan(found));
             // run slots from the wave's current block of kRunBlock (a tile with more
             // runs than a block takes enough whole blocks of its own)
             int64_t base = 0;
@@ -2133,19 +2172,19 @@ __global__ void __launch_bounds__(emit_threads(PREC, FEAT)) emit_kernel(Args a)
                 rfill = nz > kRunBlock ? kRunBlock : rfill + nz;
             }
             const bool fits = base + nz <= a.run_cap;
-            if (!fits && !lost) {
-                lost = true;
+            if (!fits && t < lost) {
+                lost = t;
                 if (lane == 0) atomicMin((unsigned long long*)&a.ctrl[kFirstLost], (unsigned long long)t);
             }
             int done = 0;
             for (int k0 = 0; k0 < a.n_tel; k0 += kWave) {
                 const int kk = k0 + lane;
-                const int32_t c = kk < a.n_tel ? tcount[kk] : 0;
+                const int32_t c = kk < a.n_tel ? tc[kk] : 0;
                 const uint64_t m = __ballot(c != 0);
                 if (c != 0) {
                     if (fits)
                         a.runs[base + done + __popcll(m & lt_mask)] = ((int64_t)kk << kRunTelShift) | c;
-                    tcount[kk] = 0;
+                    tc[kk] = 0;
                 }
                 done += __popcll(m);
             }
@@ -2175,7 +2214,7 @@ __global__ void __launch_bounds__(emit_threads(PREC, FEAT)) emit_kernel(Args a)
             double ph = 0.0;
             unsigned long long bu = 0;
             for (int w = 0; w < nw; ++w) {
-                const WaveArea<PREC, TS> ww(lds + srch_bytes + tel_bytes(a.n_tel) + (size_t)w * wv_stride, a.n_tel,
+                const WaveArea<PREC, TS> ww(lds + srch_bytes + tel_bytes(a.n_tel) + (size_t)w * wv_stride, n_count,
                                             prof_bins);
                 ph += ww.hph[kk];
                 bu += ww.hbu[kk];
@@ -2183,7 +2222,7 @@ __global__ void __launch_bounds__(emit_threads(PREC, FEAT)) emit_kernel(Args a)
                 bool last = w + 1 == nw;
                 if (!last) {
                     const WaveArea<PREC, TS> wn(lds + srch_bytes + tel_bytes(a.n_tel) + (size_t)(w + 1) * wv_stride,
-                                                a.n_tel, prof_bins);
+                                                n_count, prof_bins);
                     last = wn.prof[0] != s;
                 }
                 if (last) {
@@ -3847,7 +3886,19 @@ int launch_run(RunPlan& p)
     if (int rc = emit_config(p.params.precision, a.n_tel, p.prof_bins, p.atmo, p.tile_segs, p.report_segs, cap,
                              &waves, &lds, many_nodes_ok))
         return rc;
+    // as many tiles taken together as their crossing counters find room for
+    const size_t fixed = (p.atmo->h_nodes.empty() ? 0 : search_bytes(a.n_nodes)) + tel_bytes(a.n_tel);
+    int span = kWave / p.tile_segs;
+    for (; span > 1; span >>= 1) {
+        const size_t tot = fixed + (size_t)waves * wave_bytes(p.params.precision, p.tile_segs, a.n_tel * span,
+                                                              p.prof_bins);
+        if (tot <= 160 * 1024) {
+            lds = tot;
+            break;
+        }
+    }
     set_sectors(a, p.atmo, p.arr->rmax, p.arr->dmax);
+    a.span_tiles = span;
     a.grid_waves = p.emit_grid * waves;
     // a block per wave of the launch, as far as the workspace holds them beside the claims'
     // (a grid of whole class rounds: the waves' first tiles are then 0 .. waves - 1, each
@@ -4009,6 +4060,7 @@ int launch_soft(RunPlan& p, const SoftPlan& sp, int mode)
         allow_lds((const void*)soft_kernel<0>, 160 * 1024);
         if (s.ids_count) {
             allow_lds((const void*)emit_kernel<1, kSoftTS, kFeatScreen>, 160 * 1024);
+            e.span_tiles = kWave / kSoftTS;
             e.grid_waves = p.emit_grid * e_waves;
             emit_kernel<1, kSoftTS, kFeatScreen><<<p.emit_grid, e_waves * kWave, e_lds, st>>>(e);
             if (int rc = check_launch("screen")) return rc;
