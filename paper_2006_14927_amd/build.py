@@ -25,6 +25,11 @@ def hipcc() -> str:
 STAMP_PATH = os.path.join(LIB_DIR, "libckv.sources")
 
 
+# Flags of single files.  ckv_kernels.hip: values that do not change in a loop stay out
+# of registers around it (why, and the times of both, beside the kernels).
+FILE_FLAGS = {"ckv_kernels.hip": ("-mllvm", "-disable-machine-licm")}
+
+
 def sources():
     return sorted(glob.glob(os.path.join(HERE, "csrc", "*.cpp")) +
                   glob.glob(os.path.join(HERE, "csrc", "*.hip")))
@@ -62,7 +67,7 @@ def build(verbose: bool = False, extra_flags=()) -> str:
               "-Wall", "-Wno-unused-function", *extra_flags]
     for src in sources():
         obj = os.path.join(LIB_DIR, os.path.basename(src) + ".o")
-        cmd = common + ["-x", "hip", "-c", src, "-o", obj]
+        cmd = common + [*FILE_FLAGS.get(os.path.basename(src), ()), "-x", "hip", "-c", src, "-o", obj]
         if verbose:
             print(" ".join(cmd), flush=True)
         r = subprocess.run(cmd, capture_output=True, text=True)

@@ -2249,6 +2249,33 @@ __global__ void __launch_bounds__(emit_threads(PREC, FEAT)) emit_kernel(Args a)
     }
 }
 
+// The builds whose lanes leave the moment series (kFeatExact, kFeatCurved) are
+// compiled by ckv_slowpath.hip, all others here.  Here the compiler must not keep
+// loop-invariant values, mostly FP64 constants, in registers around the loops (the
+// flag is with the file's name in build.py): at 128 registers (16 waves) they push
+// tile state into scratch, and the soft kernels lose waves to them.  Kept against
+// not kept: 2e6 TeV steps FP64 330 -> 288 us, mixed 298 -> 289 us; candidates of a
+// 1.6e6-step fit 165 -> 123 us (220 -> 126 registers, two -> four waves per SIMD).
+// The serial FP64 chains of the slow paths, 8 waves with registers to spare, are
+// better with them in registers: curved 378 against 386 us, grazing 894 against 908.
+#define CKV_SLOWPATH_TS(M, PREC, TS)                                               \
+    M template __global__ void emit_kernel<PREC, TS, kFeatExact>(Args);            \
+    M template __global__ void emit_kernel<PREC, TS, kFeatProfile | kFeatExact>(Args);
+#define CKV_SLOWPATH_PREC(M, PREC)                                                 \
+    M template __global__ void emit_kernel<PREC, 2, kFeatExact>(Args);             \
+    M template __global__ void emit_kernel<PREC, 32, kFeatCurved>(Args);           \
+    CKV_SLOWPATH_TS(M, PREC, 8)                                                    \
+    CKV_SLOWPATH_TS(M, PREC, 16)                                                   \
+    CKV_SLOWPATH_TS(M, PREC, 32)                                                   \
+    CKV_SLOWPATH_TS(M, PREC, 64)
+
+#ifdef CKV_SLOWPATH
+CKV_SLOWPATH_PREC(, 0)
+CKV_SLOWPATH_PREC(, 1)
+#else
+CKV_SLOWPATH_PREC(extern, 0)
+CKV_SLOWPATH_PREC(extern, 1)
+
 // --------------------------------------------------------------------------
 // init: control block, shower validation, tile and row-block counts
 // --------------------------------------------------------------------------
@@ -4108,5 +4135,7 @@ int launch_count(const ckv_segments* segs, const ckv_params* prm, const ckv_atmo
     count_kernel<<<(unsigned)blocks, 256, 0, stream>>>(a, n_b);
     return check_launch("count");
 }
+
+#endif  // CKV_SLOWPATH
 
 }  // namespace ckv
