@@ -192,7 +192,9 @@ typedef struct {
     double w_min;          /* bunches with w <= w_min are dropped (0 <= w_min < 1) */
     uint64_t seed;         /* Philox key */
     int32_t precision;     /* CKV_FP64 or CKV_MIXED */
-    int32_t tile_segments; /* steps per emit tile: 8, 16, 32 or 64; 0 = default (32) */
+    int32_t tile_segments; /* steps per emit tile: 8, 16, 32 or 64; 0 = default (32; with
+                              grid 0 as well, short runs work in smaller tiles inside:
+                              n_tiles, the cut and a resume stay those of 32) */
     int32_t grid;          /* bunch-kernel workgroups, 0 = one per compute unit */
     int32_t waves_per_group; /* bunch-kernel waves per workgroup: 1, 2, 4, 8 or 16 (with
                               grazing_exact or earth_radius_m: <= 8); 0 = the most that fit the LDS; a value that does not
@@ -389,9 +391,9 @@ int ckv_array_create_soft(const double* x_m, const double* y_m, const double* r_
 /* Bunch list of the soft response.  With a list, ckv_soft_forward first screens
    every bunch with the mixed-precision path against spheres of the cut radius
    sqrt(R^2 + 2 R sigma 40) plus 1 cm (far above that path's errors), lists the
-   candidates and recomputes only those in FP64 for S and A.  Steps whose light
-   provably lands too far from every sphere centre (a bound on the ground ring of
-   the step's cone, refraction included) are not screened.  The list thus holds
+   candidates and recomputes only those in FP64 for S and A.  Azimuths of a step's
+   cone whose light provably lands too far from every sphere centre (a bound on the
+   ground ring, refraction included) are not screened.  The list thus holds
    every bunch with z >= -40 at some sphere (the ones that enter S, A and the
    gradient) and a few just outside.  Ids are (global step index << 24) | bunch
    index k, in no particular order.  ckv_soft_backward then recomputes only the

@@ -168,6 +168,20 @@ __device__ __forceinline__ void hbm_add(double* p, double v)
 // wave helpers
 // --------------------------------------------------------------------------
 __device__ __forceinline__ int lane_id() { return __lane_id(); }
+// bits of m at lanes below this one, and at this lane and below.  The builds of
+// ckv_slowpath.hip, which keep loop invariants in registers, keep the lane's masks there
+// (grazing 3000 steps 874 us, 930 with the counts below).
+#ifdef CKV_SLOWPATH
+__device__ __forceinline__ uint64_t lt_mask() { return lane_id() == 0 ? 0ull : (~0ull >> (64 - lane_id())); }
+__device__ __forceinline__ int lanes_below(uint64_t m) { return __popcll(m & lt_mask()); }
+__device__ __forceinline__ int lanes_upto(uint64_t m) { return __popcll(m & (lt_mask() | (1ull << lane_id()))); }
+#else
+__device__ __forceinline__ int lanes_below(uint64_t m)
+{
+    return (int)__builtin_amdgcn_mbcnt_hi((uint32_t)(m >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)m, 0u));
+}
+__device__ __forceinline__ int lanes_upto(uint64_t m) { return lanes_below(m >> 1) + (int)(m & 1); }
+#endif
 
 // x of the lane the DPP control CTRL names as source, in the rows ROWS enables; 0
 // where there is no source or the row is masked off
@@ -939,7 +953,8 @@ static_assert(kPairs * sizeof(uint32_t) <= kQueue * sizeof(uint32_t), "pairs sha
 // On the 20 degree TeV shower (100 spheres) 19 % of the bunches are in steps with some
 // window and 1.7 % lie in one (1.0 % cross), so 81 % of the bunches cost nothing and 98 %
 // no propagation: 3083 VALU instructions per 32-step tile against 9570 with every bunch
-// propagated; mixed kernel 1150 -> 550 us, FP64 2036 -> 580 us (2e6 steps); spherical
+// propagated; mixed kernel 1150 -> 550 us, FP64 2036 -> 580 us (2e6 steps; with the setup
+// and the chunks shared by tiles, below, 1730 instructions, 268 and 264 us); spherical
 // shells at 70 degrees, where a propagated bunch walks 250 cells, 3608 -> 360 us (1e5
 // steps).  A bitmask of 256 sectors (2.9 m of a 120 m ring) takes any number of windows at
 // one LDS read per bunch.
@@ -1162,7 +1177,7 @@ struct TileSetup {
 
 template <int PREC, int TS, int FEAT>
 __device__ __forceinline__ TileSetup tile_setup(const Args& a, int64_t t0, int h_first, int h_all, int lane,
-                                                uint64_t lt_mask, const WaveArea<PREC, TS>& wa,
+                                                const WaveArea<PREC, TS>& wa,
                                                 const double* tel_sh)
 {
     constexpr bool SCREEN = (FEAT & kFeatScreen) != 0;
@@ -1307,7 +1322,7 @@ __device__ __forceinline__ TileSetup tile_setup(const Args& a, int64_t t0, int h
                     const int k = far ? kReachPad * i + q
                                       : (int)(((q < 2 ? four.x : four.y) >> (16 * (q & 1))) & 0xFFFFu);
                     const uint64_t m = __ballot(p4 != 0u);
-                    if (p4) pairs[np + __popcll(m & lt_mask)] = ((uint32_t)k << 8) | (uint32_t)l;
+                    if (p4) pairs[np + lanes_below(m)] = ((uint32_t)k << 8) | (uint32_t)l;
                     np += __popcll(m);
                     p4 &= p4 - 1;
                     if (np >= kWave) windows();
@@ -1355,7 +1370,7 @@ __device__ __forceinline__ TileSetup tile_setup(const Args& a, int64_t t0, int h
     const int32_t excl = incl - nbp;      // first bunch of this lane's step
     const uint64_t pass_mask = __ballot(in_pass);
     if (in_pass) {
-        const int at = __popcll(pass_mask & lt_mask);
+        const int at = lanes_below(pass_mask);
         Entry& e = wa.stash[at];
         e.ctr1 = ctr1;
         // Philox: the first round's word 0 is the same for all bunches of the step, and
@@ -1415,20 +1430,30 @@ __device__ __forceinline__ TileSetup tile_setup(const Args& a, int64_t t0, int h
     return TileSetup{excl, incl, s, in_pass, masked, h_end};
 }
 
-// The same as a called function: its step setup's registers and the step arrays'
-// pointers then take no room in the bunch loop (inlined: 400 -> 474 us, 2e6 steps).
+// The same with the arguments where the launch put them, the kernel argument segment,
+// and the wave's places in LDS as offsets: the bunch loop's copies of them then take no
+// registers here, nor these there.
 template <int PREC, int TS, int FEAT>
-__device__ __noinline__ TileSetup tile_setup_call(uint64_t args_at, int64_t t0, int h_first, int h_all, int lane,
-                                                  uint64_t lt_mask, uint32_t area_at, uint32_t tel_at)
+__device__ __forceinline__ TileSetup tile_setup_at(uint64_t args_at, int64_t t0, int h_first, int h_all, int lane,
+                                                   uint32_t area_at, uint32_t tel_at)
 {
     extern __shared__ __align__(16) unsigned char lds[];
     const Args& a = args_from(args_at);
     const WaveArea<PREC, TS> wa(lds + __builtin_amdgcn_readfirstlane((int)area_at),
                                 (FEAT & kFeatScreen) != 0 ? 0 : a.n_tel * a.span_tiles, (FEAT & kFeatProfile) != 0 ? a.prof_bins : 0);
     return tile_setup<PREC, TS, FEAT>(a, scalar64(t0), __builtin_amdgcn_readfirstlane(h_first),
-                                      __builtin_amdgcn_readfirstlane(h_all), lane, lt_mask, wa,
+                                      __builtin_amdgcn_readfirstlane(h_all), lane, wa,
                                       reinterpret_cast<const double*>(
                                           lds + __builtin_amdgcn_readfirstlane((int)tel_at)));
+}
+
+// As a called function, for the builds that keep loop invariants in registers
+// (kFeatExact, kFeatCurved): the step setup's then take no room in the bunch loop.
+template <int PREC, int TS, int FEAT>
+__device__ __noinline__ TileSetup tile_setup_call(uint64_t args_at, int64_t t0, int h_first, int h_all, int lane,
+                                                  uint32_t area_at, uint32_t tel_at)
+{
+    return tile_setup_at<PREC, TS, FEAT>(args_at, t0, h_first, h_all, lane, area_at, tel_at);
 }
 
 // Screening pass: the n ids of a wave's buffer to the list; one atomic claims exactly
@@ -1476,7 +1501,9 @@ __global__ void __launch_bounds__(emit_threads(PREC, FEAT)) emit_kernel(Args a)
     extern __shared__ __align__(16) unsigned char lds[];
 
     const int lane = lane_id();
-    const int wave = threadIdx.x / kWave;
+    // scalar, so that the wave's LDS addresses take no lane registers (the slow-path builds
+    // have those to spare)
+    const int wave = SLOWPATH ? (int)threadIdx.x / kWave : __builtin_amdgcn_readfirstlane((int)threadIdx.x / kWave);
 
     // node tables: altitudes and inverse widths
     double* hn_lds = reinterpret_cast<double*>(lds);
@@ -1512,8 +1539,6 @@ __global__ void __launch_bounds__(emit_threads(PREC, FEAT)) emit_kernel(Args a)
 
     const T a1 = (T)-0.5, a2 = (T)0.375, a3 = (T)-0.3125, a4 = (T)0.2734375;
     const double inv_c = 1.0 / kSpeedOfLight;
-    const uint64_t lt_mask = (lane == 0) ? 0ull : (~0ull >> (64 - lane));
-    const uint64_t le_mask = lt_mask | (1ull << lane);
     const float step32 = __builtin_bit_cast(
         float, __builtin_amdgcn_readfirstlane(__builtin_bit_cast(int, (float)a.step)));
     // n - 1 at the observation level, for the observed direction
@@ -1638,12 +1663,18 @@ __global__ void __launch_bounds__(emit_threads(PREC, FEAT)) emit_kernel(Args a)
         TileSetup ts_;
         ts_.h_end = 0;
         for (int h = 0, h_next; h < h_all; h = h_next) {
-        // ---- step setups of the unit (called out of line, with the arguments where the
-        // launch put them, the kernel argument segment, rather than a private copy)
+        // ---- step setups of the unit.  A call saves 40 registers a lane to scratch, more HBM
+        // traffic than all else; inlined, 2e6 steps take 280 against 286 us, FP64 268 against
+        // 282 (268 and 264 with the wave index scalar and the lane masks counted).  Where
+        // loop invariants are kept in registers the call is the better one.
         if (h >= ts_.h_end) {
-            ts_ = tile_setup_call<PREC, TS, FEAT>((uint64_t)__builtin_amdgcn_kernarg_segment_ptr(), t0, h, h_all, lane,
-                                                  lt_mask, (uint32_t)(wbase - lds),
-                                                  (uint32_t)(reinterpret_cast<unsigned char*>(tel_sh) - lds));
+            const uint64_t args_at = (uint64_t)__builtin_amdgcn_kernarg_segment_ptr();
+            const uint32_t area_at = (uint32_t)(wbase - lds);
+            const uint32_t tel_at = (uint32_t)(reinterpret_cast<unsigned char*>(tel_sh) - lds);
+            if constexpr (SLOWPATH)
+                ts_ = tile_setup_call<PREC, TS, FEAT>(args_at, t0, h, h_all, lane, area_at, tel_at);
+            else
+                ts_ = tile_setup_at<PREC, TS, FEAT>(args_at, t0, h, h_all, lane, area_at, tel_at);
             ts_.h_end = __builtin_amdgcn_readfirstlane(ts_.h_end);
             wave_lds_sync();
         }
@@ -1674,7 +1705,7 @@ __global__ void __launch_bounds__(emit_threads(PREC, FEAT)) emit_kernel(Args a)
                 uint64_t starts = 0;
                 for (uint64_t in = __ballot(in_pass && excl > c0 && excl < c0 + kWave); in; in &= in - 1)
                     starts |= 1ull << (__builtin_amdgcn_readlane(excl, __builtin_ctzll(in)) - c0);
-                const int si = cnt0 - 1 + __popcll(starts & le_mask);
+                const int si = cnt0 - 1 + lanes_upto(starts);
                 // Philox round keys, advanced on the scalar unit inside the loop
                 const uint32_t opaque = (uint32_t)((uint64_t)(uint32_t)c0 >> 31);   // 0; keeps the schedule in the loop
                 uint32_t kr0 = a.key0 + opaque, kr1 = a.key1 + opaque;
@@ -1722,7 +1753,7 @@ __global__ void __launch_bounds__(emit_threads(PREC, FEAT)) emit_kernel(Args a)
                 }
                 const uint64_t m = __ballot(take);
                 if (take) {
-                    const int at = qn + __popcll(m & lt_mask);
+                    const int at = qn + lanes_below(m);
                     wa.qk[at] = (uint32_t)k;
                     wa.qs[at] = (uint8_t)si;
                 }
@@ -2013,7 +2044,7 @@ __global__ void __launch_bounds__(emit_threads(PREC, FEAT)) emit_kernel(Args a)
                     flush_list(a, buf, buf_n, lane);
                     buf_n = 0;
                 }
-                if (cand) buf[buf_n + __popcll(m & lt_mask)] = (step << kSoftIdBits) | (uint64_t)(uint32_t)k;
+                if (cand) buf[buf_n + lanes_below(m)] = (step << kSoftIdBits) | (uint64_t)(uint32_t)k;
                 buf_n += __popcll(m);
             } else {
                 // ---- the records of the crossing bunches.  About one chunk in five holds
@@ -2070,7 +2101,7 @@ __global__ void __launch_bounds__(emit_threads(PREC, FEAT)) emit_kernel(Args a)
                                           my_next != INT_MAX;
                         const uint64_t mask = __ballot(mine);
                         const int nmine = __popcll(mask);
-                        const int below = __popcll(mask & lt_mask);
+                        const int below = lanes_below(mask);
                         // rank among the turn's crossings of the same tile and sphere, then the
                         // crossings of earlier turns
                         const int key = mine ? (sidx_rec / TS - h) * a.n_tel + my_next : -1;
@@ -2079,7 +2110,7 @@ __global__ void __launch_bounds__(emit_threads(PREC, FEAT)) emit_kernel(Args a)
                             const int kk = __builtin_amdgcn_readlane(key, __builtin_ctzll(rest));
                             const uint64_t same = __ballot(key == kk);
                             if (key == kk) {
-                                rank = __popcll(same & lt_mask);
+                                rank = lanes_below(same);
                                 of_key = __popcll(same);
                             }
                             rest &= ~same;
@@ -2183,7 +2214,7 @@ __global__ void __launch_bounds__(emit_threads(PREC, FEAT)) emit_kernel(Args a)
                 const uint64_t m = __ballot(c != 0);
                 if (c != 0) {
                     if (fits)
-                        a.runs[base + done + __popcll(m & lt_mask)] = ((int64_t)kk << kRunTelShift) | c;
+                        a.runs[base + done + lanes_below(m)] = ((int64_t)kk << kRunTelShift) | c;
                     tc[kk] = 0;
                 }
                 done += __popcll(m);
@@ -2950,11 +2981,9 @@ struct alignas(16) SoftStep {
 static_assert(sizeof(SoftStep) % 16 == 0, "soft step entry alignment");
 
 constexpr int kSoftTS = 32;
-// forward: 8 waves (<= 256 VGPRs, two waves per SIMD); adjoint: 4 waves, whose
-// reverse sweep needs more registers than two waves per SIMD leave
-// 8 waves for both: the adjoint at 4 waves keeps 288 registers (one wave per SIMD);
-// built for 8 it gets 256 (two per SIMD) at the cost of a few spills, which is faster
-__host__ __device__ constexpr int soft_max_waves(int mode) { return mode == 0 ? 8 : 8; }
+// 8 waves for both directions, two per SIMD: the forward keeps 143 registers, the
+// adjoint 198
+__host__ __device__ constexpr int soft_max_waves(int) { return 8; }
 // adjoint bins (dL/dpsi_i, dL/dP_j(h_i)) of the lowest kSoftBinNodes nodes live in
 // LDS (h_obs + 51 km on a 50 m grid); the rare contributions above go to HBM
 constexpr int kSoftBinNodes = 1024;
@@ -3304,7 +3333,7 @@ __global__ void __launch_bounds__(soft_max_waves(MODE) * kWave) soft_kernel(Args
     // after the screening pass) does the work (the same decision in every thread)
     if (sa.skip_if_listed && soft_list_complete(sa)) return;
     const int lane = lane_id();
-    const int wave = threadIdx.x / kWave;
+    const int wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x / kWave);
     const int N = a.n_nodes;
     const int NB = soft_bin_nodes(N);
     double* bins = reinterpret_cast<double*>(lds);                 // MODE 1: 6 x NB
@@ -3336,8 +3365,6 @@ __global__ void __launch_bounds__(soft_max_waves(MODE) * kWave) soft_kernel(Args
         else hbm_add(j == 0 ? &sa.g_psi[i] : &sa.g_P[(size_t)(j - 1) * N + i], v);
     };
 
-    const uint64_t lt_mask = (lane == 0) ? 0ull : (~0ull >> (64 - lane));
-    const uint64_t le_mask = lt_mask | (1ull << lane);
     const double inv_nobs = 1.0 / a.n_obs;
     const double half_inv_nobs3 = 0.5 * inv_nobs * inv_nobs * inv_nobs;
     double g_psi0 = 0.0;
@@ -3373,7 +3400,7 @@ __global__ void __launch_bounds__(soft_max_waves(MODE) * kWave) soft_kernel(Args
             if (emits) nb = nbf;
         }
         // the tile limit on the frozen counts, then the cull of the steps whose
-        // bunches can weight no sphere (screen_annulus, as in the screening pass)
+        // bunches can weight no sphere (screen_annulus)
         if (wave_last(wave_incl_scan(nb)) >= ((int64_t)1 << 30)) {
             if (lane == 0 && a.result) atomicOr(&a.result->error, 2);
             continue;
@@ -3397,7 +3424,7 @@ __global__ void __launch_bounds__(soft_max_waves(MODE) * kWave) soft_kernel(Args
             st.boff = excl;
             st.sidx = lane;
             st.ctr1 = a.step_id ? a.step_id[g0 + lane] : (uint32_t)(seg_id0 + lane);
-            stash[__popcll(emit_mask & lt_mask)] = st;
+            stash[lanes_below(emit_mask)] = st;
         }
         wave_lds_sync();
 
@@ -3409,7 +3436,7 @@ __global__ void __launch_bounds__(soft_max_waves(MODE) * kWave) soft_kernel(Args
             wave_lds_sync();
             const uint64_t starts = __ballot(flags[lane] != 0);
             flags[lane] = 0;
-            const int si = cnt0 - 1 + __popcll(starts & le_mask);
+            const int si = cnt0 - 1 + lanes_upto(starts);
             if (active) {
                 SoftStep& e = stash[si];
                 const int32_t k = j - e.boff;
@@ -3436,7 +3463,7 @@ __global__ void __launch_bounds__(soft_max_waves(MODE) * kWave) soft_kernel(Args
             }
         } else if (emits) {
             // ---- reverse through the step setup (index at the step midpoint)
-            const SoftStep& es = stash[__popcll(emit_mask & lt_mask)];
+            const SoftStep& es = stash[lanes_below(emit_mask)];
             soft_step_reverse(es, es.g_cos, es.g_sin, es.g_phot, add_bin);
         }
         wave_lds_sync();
@@ -3540,6 +3567,9 @@ __device__ __forceinline__ void stage_showers(const Args& a, ShowerRec* shr)
     }
 }
 
+// Bound like soft_cand_kernel below, at two waves per SIMD: 7.0e7 VALU instructions, 114 us
+// of issue, take 258 us for a 1.6e6-step fit.  The reverse sweep keeps 192 registers; held
+// to the 168 of three waves it spills (323 us).
 // Adjoint over the forward's list: one listed bunch per thread, its step set up
 // again (bunch count frozen), the bunch recomputed from its random numbers and
 // reversed into the table bins, the step-level part applied per bunch.  Runs only
@@ -3607,6 +3637,8 @@ __global__ void __launch_bounds__(kSoftListThreads) soft_list_kernel(Args a, Sof
     }
 }
 
+// Bound by FP64 issue and the latency of its serial chains: 4.9e7 VALU instructions, 80 us
+// of issue, take 122 us for a 1.6e6-step fit at four waves per SIMD (126 registers).
 // Soft forward over the screening pass's candidate list: one candidate bunch per
 // thread, its step set up again with the frozen count and the bunch recomputed in
 // FP64 exactly as in the tile kernel; S and A are added straight into HBM.  Runs
@@ -3983,8 +4015,7 @@ int launch_soft(RunPlan& p, const SoftPlan& sp, int mode)
     a.tile_segs = a.report_segs = kSoftTS;          // the soft kernels walk 32-step tiles
     hipStream_t st = p.stream;
     const ckv_array* ar = p.arr;
-    // the per-step cull's bound constants (screen_annulus), for the screening pass and
-    // the FP64 tile kernels
+    // the per-step cull's bound constants (screen_annulus) of the FP64 tile kernels
     {
         const ckv_atmo* at = p.atmo;
         if (ar->screen_rmax > 0.0 && 1.0 + at->psi_min >= 0.5) {
