@@ -3480,7 +3480,10 @@ __global__ void __launch_bounds__(soft_max_waves(MODE) * kWave) soft_kernel(Args
 }
 
 constexpr int kSoftListThreads = 512;   // listed adjoint: workgroup size
-constexpr int kSoftCandThreads = 512;   // listed forward: workgroup size
+// listed forward: at most 16 waves a compute unit, in two workgroups where the LDS holds
+// two, else in one (64 showers x 100 spheres, 102 KB of S and A: 3.18 ms with one of 512
+// threads, 2.45 with 1024; 16 showers, where two fit: 122 us in two, 127 in one)
+constexpr int kSoftCandThreads = 1024;
 
 // Listed bunches of a wave (consecutive list entries, one per lane; id is the
 // lane's entry, loaded by the caller): the step setup and the shower lookup are
@@ -4130,7 +4133,8 @@ int launch_soft(RunPlan& p, const SoftPlan& sp, int mode)
             s.shower_lds = lds_c + shr_b <= 160 * 1024 ? 1 : 0;
             if (s.shower_lds) lds_c += shr_b;
             allow_lds((const void*)soft_cand_kernel, 160 * 1024);
-            soft_cand_kernel<<<2 * p.emit_grid, kSoftCandThreads, lds_c, st>>>(a, s);
+            const int groups = lds_c <= 80 * 1024 ? 2 : 1;
+            soft_cand_kernel<<<groups * p.emit_grid, kSoftCandThreads / groups, lds_c, st>>>(a, s);
             if (int rc = check_launch("soft candidates")) return rc;
         }
         soft_kernel<0><<<p.emit_grid, waves * kWave, lds, st>>>(a, s);

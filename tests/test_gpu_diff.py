@@ -110,6 +110,28 @@ def test_soft_forward_with_odd_sphere_counts(n_tel):
     np.testing.assert_allclose(A.cpu().numpy(), Ao, rtol=1e-10, atol=1e-12 * np.abs(Ao).max())
 
 
+@pytest.mark.parametrize("n_showers", [18, 19, 70])
+def test_soft_forward_by_room_for_the_sums(n_showers):
+    """The listed forward keeps S and A of all (shower, sphere) pairs in LDS and runs two
+    workgroups on a compute unit while they leave room (100 spheres: up to 18 showers),
+    then one; with 70 showers they go to device memory.  Each gives the oracle's S and A."""
+    import torch
+    dw = synth.diff_showers(n_showers, 400)
+    orc = Oracle(dw)
+    spec = ckv.ParamSpec(dw.eta0, dw.layer_bounds, dw.n_knots, dw.knot_top, dw.obs_level, dw.step,
+                         dw.top)
+    model = ckv.SoftModel(dw.segs, dw.tels, spec, dw.theta0, dw.sigma, seed=dw.seed,
+                          list_capacity=int(orc.nb.sum()))
+    S, A = model.forward(dw.theta0)
+    torch.cuda.synchronize()
+    n, cap = model.list_state()
+    assert 0 < n <= cap
+    So, Ao = orc.SA(dw.theta0)
+    assert So.sum() > 100
+    np.testing.assert_allclose(S.cpu().numpy(), So, rtol=1e-10, atol=1e-12 * So.max())
+    np.testing.assert_allclose(A.cpu().numpy(), Ao, rtol=1e-10, atol=1e-12 * np.abs(Ao).max())
+
+
 @pytest.mark.parametrize("which", ["theta0", "bumpy"])
 def test_unlisted_forward_matches_oracle(small, which):
     """Without a list the FP64 tile forward computes S and A from every bunch of
