@@ -79,9 +79,12 @@ OPS_FP64 = {
 }
 # Per-bunch issue-slot counts of the whole path, operation by operation (lane-slots
 # per generated bunch, issue-cycle weighted, every instruction the per-bunch work
-# needs): 280-300 for the mixed path, 380-450 for plain FP64; the midpoints are the
-# counts the roofline fraction is priced with.  The itemised algorithmic counts above
-# (arithmetic the method needs, no addressing or control) are reported beside them.
+# needs): 280-300 for the mixed path, 380-450 for plain FP64, midpoints here.  The bunch
+# kernel takes this path only for the bunches whose azimuth can reach a sphere (about 2 %
+# of the TeV shower's); the others are decided by their step and one draw.  So the
+# roofline fraction counts the slots the kernel issues (SQ counters of the same sources),
+# and what every bunch's whole path would take, and the itemised algorithmic counts above
+# (arithmetic the method needs, no addressing or control), stand beside it.
 PATH_SLOTS = {"mixed": 290.0, "fp64": 415.0}
 # MI355X: 256 CUs x 4 SIMDs x 16 lanes x 2.4 GHz, one VALU operation per lane
 # per clock (FP32 non-packed and FP64 both issue at this rate on CDNA4)
@@ -147,15 +150,9 @@ def kernel_source_hash() -> str:
 ZENITH_SAMPLE_STRIDE = 250       # every 250th step of each 5e7-step shower is certified
 
 
-def emit_kernel_name(precision: int, tile_segments: int, waves: int) -> str:
-    """Symbol of the bunch kernel a plain run launches (the mixed kernel has a
-    build for at most 8 waves per workgroup, feature bit 16; the FP64 kernel one
-    for 16 waves, feature bit 64)."""
-    if precision == 1:
-        feat = 16 if waves <= 8 else 0
-    else:
-        feat = 64 if waves > 8 else 0     # the FP64 16-wave build stages part of the table
-    return f"void ckv::emit_kernel<{precision}, {tile_segments}, {feat}>(ckv::Args)"
+def emit_kernel_name(precision: int, tile_segments: int) -> str:
+    """Symbol of the bunch kernel a plain run launches."""
+    return f"void ckv::emit_kernel<{precision}, {tile_segments}, 0>(ckv::Args)"
 
 
 def _profile_kv(path: str) -> dict:
@@ -169,16 +166,17 @@ def _profile_kv(path: str) -> dict:
     return kv
 
 
-def stored_issue_frac(kernel: str, workload: str):
-    """VALU issue fraction of a kernel from the committed rocprofv3 SQ summary of
-    the workload, if it was taken on the current sources; else None."""
+def stored_valu(kernel: str, workload: str):
+    """(VALU wave instructions per launch, VALU issue fraction) of a kernel from the
+    committed rocprofv3 SQ summary of the workload, if it was taken on the current
+    sources; else (None, None)."""
     kv = _profile_kv(os.path.join(ROOT, "profiles", f"sq_bunch_kernel_{workload}.txt"))
     if kv.get("kernel_sources_sha256_16") != kernel_source_hash():
-        return None
+        return None, None
     try:
-        return float(kv[f"issue_frac {kernel}"])
+        return float(kv[f"valu_per_launch {kernel}"]), float(kv[f"issue_frac {kernel}"])
     except (KeyError, ValueError):
-        return None
+        return None, None
 
 
 def stored_traffic(name: str):
@@ -372,15 +370,22 @@ def diff_timing(hip, reps: int, n_showers: int = 64, n_seg: int = 500_000):
 
 
 def roofline_block(slots_path: float, slots_itemised: float, bunches: int, kernel_ms: float,
-                   issue_frac=None) -> dict:
-    """VALU issue-slot roofline of a bunch kernel: algorithmic slots per bunch x
-    bunches / kernel time against 256 CU x 4 SIMD x 16 lanes x 2.4 GHz."""
-    achieved = slots_path * bunches / (kernel_ms * 1e-3) / 1e12
+                   stored=(None, None)) -> dict:
+    """VALU issue-slot roofline of a bunch kernel: the lane slots it issues (64 per VALU
+    wave instruction, counted) / kernel time against 256 CU x 4 SIMD x 16 lanes x 2.4 GHz.
+    every_bunch_*: the same if every bunch went the whole path (above 1: most do not)."""
     peak = PEAK_OPS_PER_S / 1e12
+    per_s = bunches / (kernel_ms * 1e-3)
+    valu, issue_frac = stored
+    achieved = None if valu is None else 64.0 * valu / (kernel_ms * 1e-3) / 1e12
     return {"bound": "alu", "achieved": achieved, "peak": peak, "unit": "TOP/s",
-            "frac": achieved / peak, "slots_per_bunch": slots_path,
-            "frac_itemised_model": slots_itemised * bunches / (kernel_ms * 1e-3) / PEAK_OPS_PER_S,
-            "slots_per_bunch_itemised_model": slots_itemised, "issue_frac": issue_frac}
+            "frac": None if achieved is None else achieved / peak,
+            "slots_per_bunch": None if valu is None else 64.0 * valu / bunches,
+            "slots_per_bunch_whole_path": slots_path,
+            "every_bunch_whole_path_over_peak": slots_path * per_s / PEAK_OPS_PER_S,
+            "slots_per_bunch_itemised_model": slots_itemised,
+            "every_bunch_itemised_over_peak": slots_itemised * per_s / PEAK_OPS_PER_S,
+            "issue_frac": issue_frac}
 
 
 def batched_timing(hip, reps: int, use_cache: bool = True):
@@ -447,9 +452,8 @@ def batched_timing(hip, reps: int, use_cache: bool = True):
                      "launch": {"tile_segments": tuned["tile_segments"],
                                 "waves_per_group": tuned["waves_per_group"]},
                      "roofline": roofline_block(PATH_SLOTS[key], sum(ops.values()), total, kms,
-                                                stored_issue_frac(emit_kernel_name(
-                                                    prec, tuned["tile_segments"],
-                                                    tuned["waves_per_group"]), "batched_256"))}
+                                                stored_valu(emit_kernel_name(prec, tuned["tile_segments"]),
+                                                            "batched_256"))}
         print(f"# batched {name}: {ms:.2f} ms per graph launch, bunch kernel {kms:.2f} ms",
               file=sys.stderr, flush=True)
     out["ms_per_launch"] = out["mixed"]["ms_per_launch"]
@@ -894,14 +898,12 @@ def main(argv=None):
         torch.cuda.synchronize()
         print(f"# copy probe: {args.copy_probe_mib} MiB read + written, 3 launches", file=sys.stderr)
 
-    k_mixed = emit_kernel_name(1, tuned[ckv.CKV_MIXED]["tile_segments"],
-                               tuned[ckv.CKV_MIXED]["waves_per_group"])
-    k_fp64 = emit_kernel_name(0, tuned[ckv.CKV_FP64]["tile_segments"],
-                              tuned[ckv.CKV_FP64]["waves_per_group"])
+    k_mixed = emit_kernel_name(1, tuned[ckv.CKV_MIXED]["tile_segments"])
+    k_fp64 = emit_kernel_name(0, tuned[ckv.CKV_FP64]["tile_segments"])
     roof = roofline_block(PATH_SLOTS["mixed"], sum(OPS_MIXED.values()), nb, kms_mixed,
-                          stored_issue_frac(k_mixed, wl.name))
+                          stored_valu(k_mixed, wl.name))
     roof_fp64 = roofline_block(PATH_SLOTS["fp64"], sum(OPS_FP64.values()), nb, kms_fp64,
-                               stored_issue_frac(k_fp64, wl.name))
+                               stored_valu(k_fp64, wl.name))
     roof["traffic"] = stored_traffic("bunch_kernel_single_tev_mixed")
     hits = res_mixed["n_hits"]
     alg_bytes = wl.segs.n * SEG_BYTES + hits * RECORD_BYTES
