@@ -960,26 +960,42 @@ static_assert(kPairs * sizeof(uint32_t) <= kQueue * sizeof(uint32_t), "pairs sha
 // one LDS read per bunch.
 // Margins: 5 cm, 1e-6 of the distance (FP32 window arithmetic) and the mixed path's
 // ground-point error, twice the screening pass's bound of it.
+// A direction of length other than 1 by rounding, off = ||a|^2 - 1|: the path taken and
+// the windows then use a, b1, b2 that differ from the unit step's orthonormal ones by off
+// / 2, 1.12 off and 1.12 off (the frame's slope along a is below 2.24), so a bunch's p by
+// delta = (0.51 + 1.7 sin_t) off.  Against the unit step's bunch its ground point moves by
+// at most 4.1 delta dh / w_p^2 (p_h / w_p by 2, the advance S by 1.25), the test with its
+// observed direction allows 2 delta R / w_o^2 more, the windows' coordinates of c' are
+// wrong by 1.66 off |c' - P0| and the step's length by off / 2; with shells, where a cell
+// takes the tangent from the invariant and the cosine separately, the first is 6 delta
+// D / cos^2 of the path length D.  Directions stored in FP32 have off up to 1.2e-7 (2 cm at
+// 20 km); refused from 1e-9 on, as they were, a 5e5-step TeV shower with such directions
+// has every bunch propagated: 449 us, now 150.
 //
-// false where the bound does not hold (direction not unit, flat rays, psi's range too
-// large) or where a bunch of the step might be dropped: the caller then takes every
+// false where the bound does not hold (direction farther from unit, flat rays, psi's range
+// too large) or where a bunch of the step might be dropped: the caller then takes every
 // bunch, so drops are counted bunch by bunch as ever.
 // --------------------------------------------------------------------------
 template <bool CURVED, bool SCREEN>
-__device__ __forceinline__ bool light_cone(const Args& a, const Setup& st, double& px, double& py, double& base)
+__device__ __forceinline__ bool light_cone(const Args& a, const Setup& st, double& px, double& py, double& base,
+                                           double& unit)
 {
     const double u = st.u, v = st.v, w = st.w, ct = st.cos_t;
     const double dh0 = st.h0 - a.h_obs;
     px = st.x0;
     py = st.y0;
     base = 0.0;
-    if (!(fabs(u * u + v * v + w * w - 1.0) <= 1e-9) || !(w >= 0.05)) return false;
+    const double h2 = fma(u, u, v * v), e = fma(w, w, h2 - 1.0), off = fabs(e);
+    unit = fma(e, fma(e, 0.375, -0.5), 1.0);         // 1 / |a|, to off^3
+    if (!(off <= (CURVED ? 1e-6 : 1e-4)) || !(w >= 0.05)) return false;
     const double s_hi = st.sin_t * (1.0 + 1e-9) + 1e-12;
-    const double sa = sqrt(fmax(0.0, (1.0 - w) * (1.0 + w)));
+    const double sa = sqrt(h2);
     double wp = w * ct - sa * s_hi - 1e-12;          // lower bound of w_p
     // (the FP64 pass behind the screen drops w_p <= w_min itself)
     if (SCREEN) wp = fmax(wp, a.w_min);
-    if (!(wp >= 0.03) || (!SCREEN && !(wp > a.w_min + 1e-6))) return false;
+    if (!SCREEN && !(wp > a.w_min + 1e-6)) return false;
+    wp -= (0.51 + 1.7 * s_hi) * off;                 // and of the unit step's
+    if (!(wp >= 0.03)) return false;
     // psi_obs - psi_e, with psi_e at the step's start, its highest point
     const double x_psi = a.sec_falls ? fmax(a.sec_psi_max - st.psi + a.sec_slope * (0.5 * st.len), 0.0)
                                      : a.sec_psi_max - a.sec_psi_min;
@@ -994,7 +1010,8 @@ __device__ __forceinline__ bool light_cone(const Args& a, const Setup& st, doubl
         const double alt0 = curved_altitude(R, st.x0, st.y0, st.h0);
         const double x1 = st.x0 + st.len * u, y1 = st.y0 + st.len * v, h1 = st.h0 - st.len * w;
         const double alt1 = curved_altitude(R, x1, y1, h1);
-        const double c1 = (w * (R + h1) - u * x1 - v * y1) / (R + alt1);   // the smaller cosine
+        // the smaller cosine
+        const double c1 = (w * (R + h1) - u * x1 - v * y1) / (R + alt1) * (1.0 - off);
         if (!(c1 > 0.03) || !(alt0 < a.h_top - 1.0)) return false;
         const double c_lo = c1 * ct - sqrt(fmax(0.0, (1.0 - c1) * (1.0 + c1))) * s_hi - 1e-12;
         if (!(c_lo > 0.03)) return false;
@@ -1007,6 +1024,9 @@ __device__ __forceinline__ bool light_cone(const Args& a, const Setup& st, doubl
         const double d = a.sec_dmax + reach;
         base = bend * (alt0 - a.h_obs) / c_ray + 0.51 * d * d / a.r_obs + reach * bend +
                m + 1e-6 * (alt0 - a.h_obs) / c_ray;
+        const double c = fmin(c_ray, wp - bend);
+        base += off * rcp64(c * c) * ((8.0 + 12.0 * s_hi) * ((alt0 - a.h_obs) / c_ray) +
+                                      (4.0 + 4.0 * s_hi) * a.sec_rmax + 3.0 * base);
         if (!(alt1 - a.h_obs > a.sec_rmax + base + 1.0)) return false;
     } else {
         const double x0 = x_psi / (1.0 + a.sec_psi_min);
@@ -1019,9 +1039,11 @@ __device__ __forceinline__ bool light_cone(const Args& a, const Setup& st, doubl
             wo2 = 1.0 - (1.0 + a.sec_psi_max) / (1.0 + a.sec_psi_min) * (1.0 - wp) * (1.0 + wp);
             if (!(wo2 > 1e-3)) return false;
         }
+        const double iwo = rcp64(sqrt(wo2));
         m += dh0 * ((1e-6 * st.sin_t + 2e-9) * (iw + iw2) + 4e-6 * a.sec_psi_max * iw * iw2);
         base = (B - beta0) * t_max * dh0 + beta0 * (s_hi * iw * iwa * dh0 + sa * st.len) +
-               a.sec_rmax * rcp64(sqrt(wo2)) * (0.51 * x0 * (1.0 + 2.0 * iw)) + m;
+               a.sec_rmax * iwo * (0.51 * x0 * (1.0 + 2.0 * iw)) + m;
+        base += off * ((5.0 + 8.0 * s_hi) * (dh0 * iw2 + a.sec_rmax * (iwo * iwo)) + 3.0 * base);
         px = st.x0 - beta0 * dh0 * (u * iwa);
         py = st.y0 - beta0 * dh0 * (v * iwa);
     }
@@ -1240,8 +1262,8 @@ __device__ __forceinline__ TileSetup tile_setup(const Args& a, int64_t t0, int h
     bool cone = false, seen = true;
     const bool live = emits && nb > 0;
     if (a.sec_rmax > 0.0) {
-        double px = 0.0, py = 0.0, base = 0.0;
-        if (live) cone = light_cone<CURVED, SCREEN>(a, st, px, py, base);
+        double px = 0.0, py = 0.0, base = 0.0, unit = 0.0;
+        if (live) cone = light_cone<CURVED, SCREEN>(a, st, px, py, base, unit);
         if (__ballot(cone)) {
             for (int q = lane; q < TS * h_all * kSectorWords; q += kWave) wa.masks[q] = 0u;
             const double ict = cone ? rcp64(st.cos_t) : 0.0;
@@ -1259,9 +1281,10 @@ __device__ __forceinline__ TileSetup tile_setup(const Args& a, int64_t t0, int h
             }
             wave_lds_sync();
             uint32_t* pairs = wa.qk;
-            const double du = cone ? st.u : 0.0, dv = cone ? st.v : 0.0;
+            // (the unit direction: n2 below is the difference of two squares near the distance's)
+            const double du = cone ? st.u * unit : 0.0, dv = cone ? st.v * unit : 0.0, dw = cone ? st.w * unit : 1.0;
             const double rc = cone ? (a.sec_rmax + base) * ict : -1.0;
-            const double kA = cone ? dh0 * st.w : 0.0, kz = dh0 * dh0;
+            const double kA = cone ? dh0 * dw : 0.0, kz = dh0 * dh0;
             const double rl = cone ? -(tn * st.len + rc) : 0.0;
             auto passes = [&](int k) {
                 const double dx = tel_sh[3 * k] - px, dy = tel_sh[3 * k + 1] - py;
@@ -1290,8 +1313,8 @@ __device__ __forceinline__ TileSetup tile_setup(const Args& a, int64_t t0, int h
             if (!far) {
                 bool above = false;
                 if (cone) {
-                    const double iw = rcp64(st.w), s_a = sqrt(fmax(0.0, (1.0 - st.w) * (1.0 + st.w)));
-                    const double room = st.w - tn * s_a;
+                    const double iw = rcp64(dw), s_a = sqrt(du * du + dv * dv);
+                    const double room = dw - tn * s_a;
                     const float r = (float)(fma(tn * dh0, iw, rc) * rcp64(room)) * 1.0001f;
                     const int lv = max(0, (int)ceilf(2.0f * __log2f(r * (float)(1.0 / kReachMin)) + 1e-3f));
                     above = !(room > 1e-3) || !(r < (float)kReachMin * 8.0f) || lv >= kReachLevels;
