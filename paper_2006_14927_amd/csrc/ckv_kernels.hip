@@ -168,6 +168,19 @@ __device__ __forceinline__ void hbm_add(double* p, double v)
 // wave helpers
 // --------------------------------------------------------------------------
 __device__ __forceinline__ int lane_id() { return __lane_id(); }
+
+// Any value, by no instruction, for lanes that never read theirs.  (A variable left
+// uninitialised before a branch and read only behind it is carried round its loop by a
+// register copy a turn: 33 of the 280 instructions a chunk of 64 bunches took.)
+template <typename T>
+__device__ __forceinline__ T any_of()
+{
+    T x;
+    asm volatile("" : "=v"(x));
+    return x;
+}
+__device__ __forceinline__ uint32_t any_u32() { return any_of<uint32_t>(); }
+__device__ __forceinline__ double any_f64() { return any_of<double>(); }
 // bits of m at lanes below this one, and at this lane and below.  The builds of
 // ckv_slowpath.hip, which keep loop invariants in registers, keep the lane's masks there
 // (grazing 3000 steps 874 us, 930 with the counts below).
@@ -1714,33 +1727,48 @@ __global__ void __launch_bounds__(emit_threads(PREC, FEAT)) emit_kernel(Args a)
         // every bunch is taken, whatever its azimuth
         const bool direct = __ballot(ts_.masked) == 0ull;
 
-        // ---- bunches of the span.  First pass, one bunch per lane: its azimuth's draw
-        // against its step's sectors; the bunches that may reach a sphere wait in the
-        // queue until 64 are there, in (step, bunch) order.
+        // ---- bunches of the span, one per lane.  Where azimuths count, a first pass tests
+        // each bunch's draw against its step's sectors; those that may reach a sphere wait
+        // in the queue until 64 are there, in (step, bunch) order.
+        // Where all are taken they go straight to their chunk, past draw test and queue: 5e5
+        // TeV steps in mixed precision whose w_min drops every bunch 275 -> 249 us (297 with
+        // any_of's copies as well; 271 before there were sectors, the table in LDS).
         int c0 = __builtin_amdgcn_readlane(excl, h * TS), qn = 0;
+        // step of bunch c0 + lane: the pass's steps starting at or before c0, plus those
+        // starting inside this chunk at or before it (one to three, by lane reads)
+        auto step_at = [&]() {
+            const int cnt0 = __popcll(__ballot(in_pass && excl <= c0));
+            uint64_t starts = 0;
+            for (uint64_t in = __ballot(in_pass && excl > c0 && excl < c0 + kWave); in; in &= in - 1)
+                starts |= 1ull << (__builtin_amdgcn_readlane(excl, __builtin_ctzll(in)) - c0);
+            return cnt0 - 1 + lanes_upto(starts);
+        };
         for (;;) {
-            while (qn < kWave && c0 < c_end) {
-                const int32_t j = c0 + lane;
-                const bool active = j < c_end;
-                // step of bunch j: the pass's steps starting at or before c0, plus those
-                // starting inside this chunk at or before j (one to three, by lane reads)
-                const int cnt0 = __popcll(__ballot(in_pass && excl <= c0));
-                uint64_t starts = 0;
-                for (uint64_t in = __ballot(in_pass && excl > c0 && excl < c0 + kWave); in; in &= in - 1)
-                    starts |= 1ull << (__builtin_amdgcn_readlane(excl, __builtin_ctzll(in)) - c0);
-                const int si = cnt0 - 1 + lanes_upto(starts);
-                // Philox round keys, advanced on the scalar unit inside the loop
-                const uint32_t opaque = (uint32_t)((uint64_t)(uint32_t)c0 >> 31);   // 0; keeps the schedule in the loop
-                uint32_t kr0 = a.key0 + opaque, kr1 = a.key1 + opaque;
-                bool take = active;
-                int32_t k = 0;
-                if (active) {
-                    const StepPass sp = wa.pass[si];
-                    k = j - sp.boff;
-                    if (!direct) {
+            // ---- a chunk: bunch k of stash entry si
+            bool active;
+            int32_t k = any_of<int32_t>();
+            int si;
+            if (direct) {
+                if (c0 >= c_end) break;
+                wave_lds_sync();
+                active = c0 + lane < c_end;
+                si = step_at();
+                if (active) k = c0 + lane - wa.pass[si].boff;
+                c0 += kWave;
+            } else {
+                while (qn < kWave && c0 < c_end) {
+                    const int sj = step_at();
+                    // Philox round keys, advanced on the scalar unit inside the loop
+                    const uint32_t opaque = (uint32_t)((uint64_t)(uint32_t)c0 >> 31);   // 0; keeps the schedule in the loop
+                    uint32_t kr0 = a.key0 + opaque, kr1 = a.key1 + opaque;
+                    bool take = false;
+                    int32_t kj = any_of<int32_t>();
+                    if (c0 + lane < c_end) {
+                        const StepPass sp = wa.pass[sj];
+                        kj = c0 + lane - sp.boff;
                         // Philox as far as the second draw: its last two rounds need one
                         // product each
-                        const uint64_t f0 = (uint64_t)0xD2511F53u * (uint32_t)k;
+                        const uint64_t f0 = (uint64_t)0xD2511F53u * (uint32_t)kj;
                         const uint32_t f1_lo = 0xCD9E8D57u * shower_id;
                         uint32_t c_0, c_1, c_2, c_3;
                         {
@@ -1773,45 +1801,45 @@ __global__ void __launch_bounds__(emit_threads(PREC, FEAT)) emit_kernel(Args a)
                         const uint32_t w = wa.masks[kSectorWords * sp.sidx + (int)(r1 >> 29)];
                         take = ((w >> ((r1 >> 24) & 31u)) & 1u) != 0;
                     }
+                    const uint64_t m = __ballot(take);
+                    if (take) {
+                        const int at = qn + lanes_below(m);
+                        wa.qk[at] = (uint32_t)kj;
+                        wa.qs[at] = (uint8_t)sj;
+                    }
+                    qn += __popcll(m);
+                    c0 += kWave;
                 }
-                const uint64_t m = __ballot(take);
-                if (take) {
-                    const int at = qn + lanes_below(m);
-                    wa.qk[at] = (uint32_t)k;
-                    wa.qs[at] = (uint8_t)si;
+                if (qn == 0) break;
+                wave_lds_sync();
+                active = lane < qn;
+                k = (int32_t)wa.qk[lane];
+                si = wa.qs[lane];
+                if (qn > kWave && lane < qn - kWave) {
+                    wa.qk[lane] = wa.qk[kWave + lane];
+                    wa.qs[lane] = wa.qs[kWave + lane];
                 }
-                qn += __popcll(m);
-                c0 += kWave;
+                qn = qn > kWave ? qn - kWave : 0;
             }
-            if (qn == 0) break;
-            // ---- a chunk of the queue, one bunch per lane
-            wave_lds_sync();
-            const bool active = lane < qn;
-            const int32_t k = (int32_t)wa.qk[lane];
-            const int si = wa.qs[lane];
-            if (qn > kWave && lane < qn - kWave) {
-                wa.qk[lane] = wa.qk[kWave + lane];
-                wa.qs[lane] = wa.qs[kWave + lane];
-            }
-            qn = qn > kWave ? qn - kWave : 0;
             const uint32_t opaque = (uint32_t)((uint64_t)(uint32_t)c0 >> 31);   // 0, as above
             uint32_t kr0 = a.key0 + opaque, kr1 = a.key1 + opaque;
 
             bool alive = false;
             int drop_why = -1;
-            // read only in lanes that emit a live bunch: left undefined elsewhere
-            double xg, yg, he;
-            double uod, vod;   // observed direction for the sphere test (live bunches)
+            // read only in lanes that emit a live bunch: any value elsewhere
+            double xg = any_f64(), yg = any_f64(), he = any_f64();
+            double uod = any_f64(), vod = any_f64();   // observed direction for the sphere test
             bool screen_all = false;   // screening: listed whatever its sphere tests say
-            double fcell, dcell = 0.0;   // fraction and height of the emission point in its cell
-            int ci;
+            // fraction and height of the emission point in its cell
+            double fcell = any_f64(), dcell = SEARCH ? any_f64() : 0.0;
+            int ci = (int)any_u32();
             // what a crossing's record needs beyond the above; the record itself is
             // completed only in chunks that hold a crossing
-            double t_rec;        // mixed fast path: emission time - t_ref; else the arrival time
-            double w_rec;        // mixed fast path: w of the photon at emission
-            T f_rec;             // mixed fast path: fraction of the emission point in its cell
+            double t_rec = any_f64();   // mixed fast path: emission time - t_ref; else the arrival time
+            double w_rec = any_f64();   // mixed fast path: w of the photon at emission
+            T f_rec = any_of<T>();      // mixed fast path: fraction of the emission point in its cell
             bool fast_rec = false;
-            uint32_t r2_rec;     // the wavelength's draw
+            uint32_t r2_rec = any_u32();   // the wavelength's draw
             if (active) {
                 const Entry& e = stash[si];
                 // Philox4x32-10 with counter (k, step index in shower, shower id, 0)
@@ -2075,8 +2103,9 @@ __global__ void __launch_bounds__(emit_threads(PREC, FEAT)) emit_kernel(Args a)
                 // for those lanes; the mixed path also takes the arrival time's series
                 // (the only user of D_5 and 1/n_e) here, recomputed from the table rather
                 // than kept live through the sphere tests.
-                float uo, vo, t_f, he_f, photons, lam;
-                int32_t sidx_rec;
+                float uo = any_of<float>(), vo = any_of<float>(), t_f = any_of<float>(), he_f = any_of<float>();
+                float photons = any_of<float>(), lam = any_of<float>();
+                int32_t sidx_rec = (int32_t)any_u32();
                 if (sweep || __ballot(my_next != INT_MAX)) {
                     if (sweep ? alive : my_next != INT_MAX) {
                         const Entry& er = stash[si];
