@@ -120,16 +120,24 @@ struct ckv_grid {
     uint32_t* d_cell_ent = nullptr;
 };
 
-// Sphere centres near a ground point, for the bunch kernel's step setup: a uniform grid
-// over the ground; per level l and cell, the spheres whose centre is within
-// kReachMin * 2^(l/2) of some point of the cell.  One device buffer: a record
-// {offset, count} per level and cell, then the lists (uint16, each padded to a multiple
-// of kReachPad with 0xFFFF).
+// Sphere centres near a ground point, for the bunch kernel's step setup: level l lists, per
+// cell of a uniform grid over the ground, the spheres whose centre is within kReachMin *
+// 2^(l/2) of some point of the cell.  A cell is two fifths of that radius (a sphere is then
+// in about 30 lists of a level, and a list half as long again as its disc), and at least 80 m
+// or 1/96 of the array.  One device buffer: a ReachLevel per level, a record {offset, count}
+// per level and cell, then the lists (uint16, each padded to a multiple of kReachPad with
+// 0xFFFF).
+struct alignas(16) ReachLevel {
+    double x0, y0;                   // corner of the grid; no centre is nearer than the level's
+                                     // radius to a point outside it
+    float inv_cell;
+    int32_t nx, ny;
+    uint32_t rec;                    // its first record
+};
 struct ckv_reach {
-    double gx0 = 0, gy0 = 0, inv_cell = 0;
-    int32_t nx = 0, ny = 0;
-    uint32_t* d_data = nullptr;      // null: no grid (few spheres)
-    size_t list_at = 0;              // 32-bit words before the lists
+    int32_t levels = 0;              // 0: no lists
+    uint32_t* d_data = nullptr;
+    size_t rec_at = 0, list_at = 0;  // 32-bit words before the records and before the lists
 };
 
 struct ckv_array {
@@ -163,7 +171,11 @@ void build_depth_table(const double* alt, const double* depth, int64_t n, ckv_at
 int build_array_grid(const ckv_array* arr, const std::vector<double>& radius, ckv_grid* g);
 // data of the reach grid; empty for at most kReachMinTel spheres
 void build_reach(const ckv_array* arr, ckv_reach* g, std::vector<uint32_t>* data);
-constexpr int kReachLevels = 6;      // up to 543 m
+// Levels go on until a list holds about all spheres, at a radius of half the array's extent:
+// at 60 degrees the light lands on an ellipse of 0.8-1.1 km, at 70 of 1.5 km, and with lists up
+// to 543 m only, one step in 17 beyond them (at 60) sent 96 % of the 64-step units past all
+// spheres.
+constexpr int kReachLevels = 14;     // up to 8.7 km
 constexpr double kReachMin = 96.0;
 constexpr int kReachPad = 4;
 // a step tests up to this many spheres one by one (16 double rounds of the wave) sooner

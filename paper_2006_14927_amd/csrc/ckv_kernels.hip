@@ -119,11 +119,11 @@ struct Args {
     // slope with altitude (0 where psi is not non-increasing), largest and smallest value
     double sec_rmax, sec_dmax, sec_slope, sec_psi_max, sec_psi_min;
     int32_t sec_falls;          // psi non-increasing with altitude at every node
-    // sphere centres near a ground point (ckv_reach; reach_rec NULL: none)
+    // sphere centres near a ground point (ckv_reach; reach_levels 0: none)
+    const ReachLevel* reach_lev;
     const uint2* reach_rec;
     const uint2* reach_list;
-    double reach_x0, reach_y0, reach_inv;
-    int32_t reach_nx, reach_ny;
+    int32_t reach_levels;
     int64_t* claims;            // claim counters, kClaimStride apart
     int32_t span_tiles;         // tiles of a unit whose bunches a wave takes together
     int32_t grid_waves;         // waves of the bunch kernel's launch
@@ -734,6 +734,11 @@ struct alignas(16) StepPass {
     uint32_t hi0, lo0;
 };
 
+// Candidate rounds of the sector search that are worth it: for a unit, and for each chunk
+// of 64 bunches in it.
+constexpr int kSearchFree = 8;
+constexpr int kSearchPerChunk = 5;
+
 // Bunches that the first pass let through, waiting for a full chunk of 64.
 constexpr int kQueue = 2 * kWave;
 constexpr int kPairs = 2 * kWave;      // (step, sphere) pairs of the tile setup, same room
@@ -1257,9 +1262,10 @@ __device__ __forceinline__ TileSetup tile_setup(const Args& a, int64_t t0, int h
         }
     }
     const int l_first = l & ~(TS - 1), l_last = l | (TS - 1);
-    int64_t tile_nb;
+    int64_t tile_nb, unit_nb;
     {
         const int64_t n = own ? nb : 0, c = wave_incl_scan(n);
+        unit_nb = scalar64(wave_last(c));
         tile_nb = __shfl(c, l_last) - __shfl(c - n, l_first);
     }
     const bool over = tile_nb >= ((int64_t)1 << 30);
@@ -1277,11 +1283,48 @@ __device__ __forceinline__ TileSetup tile_setup(const Args& a, int64_t t0, int h
     if (a.sec_rmax > 0.0) {
         double px = 0.0, py = 0.0, base = 0.0, unit = 0.0;
         if (live) cone = light_cone<CURVED, SCREEN>(a, st, px, py, base, unit);
+        const double ict = cone ? rcp64(st.cos_t) : 0.0;
+        const double tn = cone ? st.sin_t * ict : 0.0;
+        const double dh0 = cone ? st.h0 - a.h_obs : 0.0;
+        const double rc = cone ? (a.sec_rmax + base) * ict : -1.0;
+        // (the unit direction: n2 below is the difference of two squares near the distance's)
+        const double du = cone ? st.u * unit : 0.0, dv = cone ? st.v * unit : 0.0, dw = cone ? st.w * unit : 1.0;
+        // candidates: the spheres near the cone's ground ellipse: a centre d from G, the
+        // axis's ground point, has n >= d w and A <= dh0 / w + d sin(zeta_a), so passing takes
+        // d (w - t sin(zeta_a)) <= t dh0 / w + rc; all spheres beyond the lists
+        uint2 near{0u, 0u};
+        bool far = true;
+        if (cone && a.reach_levels > 0) {
+            const double iw = rcp64(dw), s_a = sqrt(du * du + dv * dv);
+            const double room = dw - tn * s_a;
+            const float r = (float)(fma(tn * dh0, iw, rc) * rcp64(room)) * 1.0001f;
+            const int lv = max(0, (int)ceilf(2.0f * __log2f(r * (float)(1.0 / kReachMin)) + 1e-3f));
+            far = !(room > 1e-3) || !(r < 1e6f) || lv >= a.reach_levels;
+            if (!far) {
+                const ReachLevel lev = a.reach_lev[lv];
+                const double fx = (fma(dh0 * iw, du, px) - lev.x0) * (double)lev.inv_cell;
+                const double fy = (fma(dh0 * iw, dv, py) - lev.y0) * (double)lev.inv_cell;
+                // (a ground point outside the grid is farther than the level's radius)
+                if (fx >= 0.0 && fy >= 0.0 && fx < (double)lev.nx && fy < (double)lev.ny)
+                    near = a.reach_rec[lev.rec + (uint32_t)((int)fx * lev.ny + (int)fy)];
+            }
+        }
+        int n4 = cone ? ((far ? a.n_tel : (int)near.y) + kReachPad - 1) / kReachPad : 0;
+        const int groups = kWave / (TS * h_all);
+        // A round of 4 candidates a lane costs about a sixth of a chunk of bunches: where the
+        // longest list takes more, all bunches are taken (2e5-3e5 TeV steps, 1024 spheres, us
+        // searched / taken / as ruled: 60 degrees 190 / 300 / 191, with ten times larger
+        // bunches 197 / 152 / 166 and before, all spheres a step, 516 and 730; 75 degrees over
+        // 400 spheres 187 / 222 / 170).  A chunk through the shells costs 50 times as much.
+        if (!CURVED) {
+            const int most = kSearchFree + (int)(min(unit_nb, (int64_t)1 << 20) * kSearchPerChunk / kWave);
+            if (__ballot(n4 > most * groups)) {
+                cone = false;
+                n4 = 0;
+            }
+        }
         if (__ballot(cone)) {
             for (int q = lane; q < TS * h_all * kSectorWords; q += kWave) wa.masks[q] = 0u;
-            const double ict = cone ? rcp64(st.cos_t) : 0.0;
-            const double tn = cone ? st.sin_t * ict : 0.0;
-            const double dh0 = cone ? st.h0 - a.h_obs : 0.0;
             ConeStep* cs = reinterpret_cast<ConeStep*>(wa.stash);
             if (cone && own) {
                 ConeStep& c = cs[l];
@@ -1294,17 +1337,14 @@ __device__ __forceinline__ TileSetup tile_setup(const Args& a, int64_t t0, int h
             }
             wave_lds_sync();
             uint32_t* pairs = wa.qk;
-            // (the unit direction: n2 below is the difference of two squares near the distance's)
-            const double du = cone ? st.u * unit : 0.0, dv = cone ? st.v * unit : 0.0, dw = cone ? st.w * unit : 1.0;
-            const double rc = cone ? (a.sec_rmax + base) * ict : -1.0;
-            const double kA = cone ? dh0 * dw : 0.0, kz = dh0 * dh0;
-            const double rl = cone ? -(tn * st.len + rc) : 0.0;
+            const double kA = dh0 * dw, kz = dh0 * dh0;
+            const double rl = -(tn * st.len + rc);
             auto passes = [&](int k) {
                 const double dx = tel_sh[3 * k] - px, dy = tel_sh[3 * k + 1] - py;
                 const double A = fma(dx, du, fma(dy, dv, kA));
                 const double n2 = fma(-A, A, fma(dx, dx, fma(dy, dy, kz)));
                 const double hi = fma(tn, A, rc), lo = fmax(fma(tn, A, rl), 0.0);
-                return cone && fma(-hi, hi, n2) <= 0.0 && fma(-lo, lo, n2) >= 0.0;
+                return fma(-hi, hi, n2) <= 0.0 && fma(-lo, lo, n2) >= 0.0;
             };
             int np = 0;
             auto windows = [&]() {
@@ -1318,31 +1358,7 @@ __device__ __forceinline__ TileSetup tile_setup(const Args& a, int64_t t0, int h
                 if (np > kWave && lane < np - kWave) pairs[lane] = pairs[kWave + lane];
                 np = np > kWave ? np - kWave : 0;
             };
-            // spheres near the cone's ground ellipse: a centre d from G, the axis's ground
-            // point, has n >= d w and A <= dh0 / w + d sin(zeta_a), so passing takes
-            // d (w - t sin(zeta_a)) <= t dh0 / w + rc
-            uint2 near{0u, 0u};
-            bool far = a.reach_rec == nullptr;
-            if (!far) {
-                bool above = false;
-                if (cone) {
-                    const double iw = rcp64(dw), s_a = sqrt(du * du + dv * dv);
-                    const double room = dw - tn * s_a;
-                    const float r = (float)(fma(tn * dh0, iw, rc) * rcp64(room)) * 1.0001f;
-                    const int lv = max(0, (int)ceilf(2.0f * __log2f(r * (float)(1.0 / kReachMin)) + 1e-3f));
-                    above = !(room > 1e-3) || !(r < (float)kReachMin * 8.0f) || lv >= kReachLevels;
-                    const double fx = (fma(dh0 * iw, du, px) - a.reach_x0) * a.reach_inv;
-                    const double fy = (fma(dh0 * iw, dv, py) - a.reach_y0) * a.reach_inv;
-                    // (a ground point outside the grid is farther than any level's radius)
-                    if (!above && fx >= 0.0 && fy >= 0.0 && fx < (double)a.reach_nx && fy < (double)a.reach_ny)
-                        near = a.reach_rec[(lv * a.reach_nx + (int)fx) * a.reach_ny + (int)fy];
-                }
-                far = __ballot(above) != 0ull;
-            }
-            // candidates 4 at a time: the lane's next list entries, or, when some step of the
-            // unit reaches beyond the lists, all spheres in order
-            const int n4 = far ? (a.n_tel + kReachPad - 1) / kReachPad : ((int)near.y + kReachPad - 1) / kReachPad;
-            const int groups = kWave / (TS * h_all);
+            // candidates 4 at a time: the lane's next list entries, or all spheres in order
             for (int i = lane / (TS * h_all); __ballot(i < n4); i += groups) {
                 uint2 four{0xFFFFFFFFu, 0xFFFFFFFFu};
                 if (!far && i < n4) four = a.reach_list[near.x / kReachPad + i];
@@ -3834,13 +3850,10 @@ Args make_args(const RunPlan& p)
         a.cell_ent = reinterpret_cast<const uint2*>(ar->hit.d_cell_ent);
         const ckv_reach& rg = ar->reach;
         if (rg.d_data) {
-            a.reach_rec = reinterpret_cast<const uint2*>(rg.d_data);
+            a.reach_lev = reinterpret_cast<const ReachLevel*>(rg.d_data);
+            a.reach_rec = reinterpret_cast<const uint2*>(rg.d_data + rg.rec_at);
             a.reach_list = reinterpret_cast<const uint2*>(rg.d_data + rg.list_at);
-            a.reach_x0 = rg.gx0;
-            a.reach_y0 = rg.gy0;
-            a.reach_inv = rg.inv_cell;
-            a.reach_nx = rg.nx;
-            a.reach_ny = rg.ny;
+            a.reach_levels = rg.levels;
         }
     }
     a.bunch_size = p.params.bunch_size;

@@ -3,6 +3,7 @@
 // computed at initialisation so that lookups need no search).
 #include <algorithm>
 #include <cmath>
+#include <cstring>
 
 #include "ckv_internal.h"
 
@@ -208,30 +209,39 @@ void build_reach(const ckv_array* arr, ckv_reach* g, std::vector<uint32_t>* data
     data->clear();
     if (n <= kReachMinTel) return;
     auto radius = [](int l) { return kReachMin * std::pow(2.0, 0.5 * l); };
-    const double top = radius(kReachLevels - 1);
     const auto mx = std::minmax_element(arr->x.begin(), arr->x.end());
     const auto my = std::minmax_element(arr->y.begin(), arr->y.end());
-    const double extent = std::max(*mx.second - *mx.first, *my.second - *my.first) + 2.0 * top;
+    const double wx = *mx.second - *mx.first, wy = *my.second - *my.first, extent = std::max(wx, wy);
     // centres too far apart for a grid of this kind: the step setup tests them all
     if (!(extent < 1e6)) return;
-    const double cell = std::max(80.0, extent / 96.0), margin = 0.01 + 1e-9 * extent;
-    g->gx0 = *mx.first - top - margin;
-    g->gy0 = *my.first - top - margin;
-    g->inv_cell = 1.0 / cell;
-    g->nx = (int32_t)std::floor((*mx.second + top + margin - g->gx0) / cell) + 1;
-    g->ny = (int32_t)std::floor((*my.second + top + margin - g->gy0) / cell) + 1;
-    const size_t n_cells = (size_t)g->nx * g->ny;
+    std::vector<ReachLevel> lev;
+    size_t n_lists = 0;
+    for (int l = 0; l < kReachLevels && (l == 0 || radius(l - 1) < 0.5 * extent); ++l) {
+        // (the margin takes up the device's rounding of a ground point's cell)
+        const double reach = radius(l) + 0.1 + 1e-6 * extent;
+        ReachLevel v;
+        v.inv_cell = (float)(1.0 / std::max({80.0, extent / 96.0, radius(l) / 2.5}));
+        v.x0 = *mx.first - reach;
+        v.y0 = *my.first - reach;
+        v.nx = (int32_t)std::floor((wx + 2.0 * reach) * (double)v.inv_cell) + 1;
+        v.ny = (int32_t)std::floor((wy + 2.0 * reach) * (double)v.inv_cell) + 1;
+        v.rec = (uint32_t)n_lists;
+        n_lists += (size_t)v.nx * v.ny;
+        lev.push_back(v);
+    }
     // each (level, sphere)'s cells, row by row; once to count, once to fill
     auto each = [&](auto&& visit) {
-        std::vector<double> dy2(g->ny);
-        for (int l = 0; l < kReachLevels; ++l) {
-            const double reach = radius(l) + margin;
+        std::vector<double> dy2;
+        for (size_t l = 0; l < lev.size(); ++l) {
+            const ReachLevel& v = lev[l];
+            const double reach = radius((int)l) + 0.1 + 1e-6 * extent, cell = 1.0 / (double)v.inv_cell;
+            dy2.resize(v.ny);
             for (int32_t k = 0; k < n; ++k) {
-                const double X = arr->x[k] - g->gx0, Y = arr->y[k] - g->gy0;
+                const double X = arr->x[k] - v.x0, Y = arr->y[k] - v.y0;
                 const int32_t x0 = std::max(0, (int32_t)std::floor((X - reach) / cell));
-                const int32_t x1 = std::min(g->nx - 1, (int32_t)std::floor((X + reach) / cell));
+                const int32_t x1 = std::min(v.nx - 1, (int32_t)std::floor((X + reach) / cell));
                 const int32_t y0 = std::max(0, (int32_t)std::floor((Y - reach) / cell));
-                const int32_t y1 = std::min(g->ny - 1, (int32_t)std::floor((Y + reach) / cell));
+                const int32_t y1 = std::min(v.ny - 1, (int32_t)std::floor((Y + reach) / cell));
                 for (int32_t iy = y0; iy <= y1; ++iy) {
                     const double dy = std::max({iy * cell - Y, 0.0, Y - (iy + 1) * cell});
                     dy2[iy] = dy * dy;
@@ -239,28 +249,33 @@ void build_reach(const ckv_array* arr, ckv_reach* g, std::vector<uint32_t>* data
                 for (int32_t ix = x0; ix <= x1; ++ix) {
                     const double dx = std::max({ix * cell - X, 0.0, X - (ix + 1) * cell});
                     const double left = reach * reach - dx * dx;
-                    const size_t row = l * n_cells + (size_t)ix * g->ny;
+                    const size_t row = v.rec + (size_t)ix * v.ny;
                     for (int32_t iy = y0; iy <= y1; ++iy)
                         if (dy2[iy] <= left) visit(row + iy, (uint16_t)k);
                 }
             }
         }
     };
-    const size_t n_lists = kReachLevels * n_cells;
-    data->assign(2 * n_lists, 0u);
-    each([&](size_t c, uint16_t) { ++(*data)[2 * c + 1]; });
+    static_assert(sizeof(ReachLevel) == 32, "a level is two 16-byte reads");
+    g->levels = (int32_t)lev.size();
+    g->rec_at = lev.size() * sizeof(ReachLevel) / sizeof(uint32_t);
+    g->list_at = g->rec_at + 2 * n_lists;
+    data->assign(g->list_at, 0u);
+    std::memcpy(data->data(), lev.data(), lev.size() * sizeof(ReachLevel));
+    uint32_t* rec = data->data() + g->rec_at;
+    each([&](size_t c, uint16_t) { ++rec[2 * c + 1]; });
     uint32_t total = 0;
     for (size_t c = 0; c < n_lists; ++c) {
-        (*data)[2 * c] = total;
-        total += ((*data)[2 * c + 1] + kReachPad - 1) / kReachPad * kReachPad;
+        rec[2 * c] = total;
+        total += (rec[2 * c + 1] + kReachPad - 1) / kReachPad * kReachPad;
     }
     // (8-byte reads of the lists: kReachPad entries, from an even word)
     static_assert(kReachPad * sizeof(uint16_t) == 8, "one 8-byte read per kReachPad entries");
-    g->list_at = 2 * n_lists;
     data->resize(g->list_at + total / 2, 0xFFFFFFFFu);
+    rec = data->data() + g->rec_at;
     uint16_t* list = reinterpret_cast<uint16_t*>(data->data() + g->list_at);
     std::vector<uint32_t> at(n_lists);
-    for (size_t c = 0; c < n_lists; ++c) at[c] = (*data)[2 * c];
+    for (size_t c = 0; c < n_lists; ++c) at[c] = rec[2 * c];
     each([&](size_t c, uint16_t k) { list[at[c]++] = k; });
 }
 
