@@ -194,7 +194,7 @@ typedef struct {
     int32_t precision;     /* CKV_FP64 or CKV_MIXED */
     int32_t tile_segments; /* steps per emit tile: 8, 16, 32 or 64; 0 = default (32; with
                               grid 0 as well, short runs work in smaller tiles inside:
-                              n_tiles, the cut and a resume stay those of 32) */
+                              n_tiles, the cut, a resume and error bit 1 stay those of 32) */
     int32_t grid;          /* bunch-kernel workgroups, 0 = one per compute unit */
     int32_t waves_per_group; /* bunch-kernel waves per workgroup: 1, 2, 4, 8 or 16 (with
                               grazing_exact or earth_radius_m: <= 8); 0 = the most that fit the LDS; a value that does not

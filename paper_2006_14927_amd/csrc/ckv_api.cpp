@@ -522,8 +522,8 @@ int run_checked(const ckv_segments* segs, const ckv_showers* showers, const ckv_
 }
 
 // A run of default tiles with few of them works in smaller ones: a tile is one wave's, and
-// the chain from its claim to its runs takes 15 us, most of it waiting.  The report, a cut
-// and a resumed run keep to the default size.  Whole runs, us, tiles of 32 / 16 / 8 / 2
+// the chain from its claim to its runs takes 15 us, most of it waiting.  The report, a cut,
+// a resumed run and the refusal of tiles past the bunch limit keep to the default size.  Whole runs, us, tiles of 32 / 16 / 8 / 2
 // steps: 300 steps 48 / 43 / 42; 5000 steps 67 / 60 / 57; 20 000 steps 65 / 62 / 64 (FP64
 // 91 / 76 / 83); 60 000 steps 84 / 89 / 92.  With grazing_exact every near-horizontal bunch
 // is propagated and meets several spheres, and 3000 steps take 4167 / 2566 / 1734 / 947.
@@ -551,6 +551,8 @@ void refine_tiles(int64_t n_segments, int32_t n_showers, int32_t n_tel, RunPlan*
     const size_t o_th = take(sizeof(int32_t) * (size_t)tiles);
     const size_t o_bsum = take(sizeof(int32_t) * (size_t)blocks * n_tel);
     const size_t o_bh = take(sizeof(int64_t) * (size_t)blocks);
+    const size_t o_heavy = take(sizeof(int32_t) * (size_t)(n_segments / kHeavySteps + 1));
+    const size_t o_hstep = take((size_t)n_segments);
     const int64_t taken = ((int64_t)off + kRunBlock * 8 - 1) / (kRunBlock * 8);
     if (taken > spare) return;
     plan->run_cap -= taken * kRunBlock;
@@ -560,6 +562,8 @@ void refine_tiles(int64_t n_segments, int32_t n_showers, int32_t n_tel, RunPlan*
     plan->tile_hits = (int32_t*)(b + o_th);
     plan->block_sums = (int32_t*)(b + o_bsum);
     plan->block_hits = (int64_t*)(b + o_bh);
+    plan->heavy = (int32_t*)(b + o_heavy);
+    plan->heavy_step = (uint8_t*)(b + o_hstep);
     plan->max_tiles = tiles;
     plan->max_row_blocks = blocks;
     plan->tile_segs = ts;

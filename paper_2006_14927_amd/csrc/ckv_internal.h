@@ -26,6 +26,7 @@ constexpr int kRunBlock = 256;         // run slots a wave claims at once
 constexpr int kMaxEmitGrid = 512;      // bound on bunch-kernel workgroups (workspace sizing)
 constexpr int kMaxEmitWaves = 16;     // waves per bunch-kernel workgroup
 constexpr int kRowBlock = 64;          // tiles per block of the per-telescope scan
+constexpr int kHeavySteps = 1024;      // steps a workgroup checks for tiles past the bunch limit
 // Candidate grids are stacked in levels; level l lists, per cell, the spheres a
 // line through the cell with observed w >= kGridWLevel[l] can meet (reach R/w).
 constexpr int kGridLevels = 3;
@@ -214,6 +215,8 @@ struct RunPlan {
     // derived
     int32_t tile_segs;
     int32_t report_segs;        // tile size of the report and of a cut (a multiple of tile_segs)
+    int32_t* heavy;             // smaller tiles only: steps of refused tiles of the report's size
+    uint8_t* heavy_step;
     int64_t max_tiles, max_row_blocks, stage_slots;
     int32_t emit_grid, emit_waves;
     int32_t prof_bins;          // longitudinal-profile bins, 0 = no profile

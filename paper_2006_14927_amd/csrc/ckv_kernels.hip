@@ -77,6 +77,10 @@ struct Args {
     uint32_t key0, key1;
     int32_t tile_segs;
     int32_t report_segs;        // tile size of the report and of a cut (a multiple of it)
+    // smaller tiles only: per kHeavySteps steps, whether a step of theirs may be in a refused
+    // tile of the report's size, and per step of those, whether it is (else NULL)
+    int32_t* heavy;
+    uint8_t* heavy_step;
     // first step of the run (a resume cursor; step 0 of shower 0 without one)
     int64_t cur_step;
     int32_t cur_shower;
@@ -1242,7 +1246,9 @@ __device__ __forceinline__ TileSetup tile_setup(const Args& a, int64_t t0, int h
     int status = -2;   // -2: no step in this lane
     Setup st;
     uint32_t ctr1 = 0;
+    int32_t heavy = 0;
     if (covered && g < seg1) {
+        if (TS < 32 && a.heavy) heavy = a.heavy[g / kHeavySteps];
         // screening: the frozen count loaded with the step's inputs, not after them
         const int64_t f = SCREEN ? a.nb_frozen[g] : 0;
         ctr1 = a.step_id ? a.step_id[g] : (uint32_t)((a.seg_id_base ? a.seg_id_base[s] : 0) + (g - seg0));
@@ -1268,7 +1274,8 @@ __device__ __forceinline__ TileSetup tile_setup(const Args& a, int64_t t0, int h
         unit_nb = scalar64(wave_last(c));
         tile_nb = __shfl(c, l_last) - __shfl(c - n, l_first);
     }
-    const bool over = tile_nb >= ((int64_t)1 << 30);
+    bool over = tile_nb >= ((int64_t)1 << 30);
+    if (TS < 32 && heavy) over = over || a.heavy_step[g] != 0;
     if (over) {
         // bunch offsets inside a tile are 32-bit: refuse such a tile
         nb = 0;
@@ -2378,8 +2385,53 @@ CKV_SLOWPATH_PREC(extern, 1)
 // --------------------------------------------------------------------------
 // init: control block, shower validation, tile and row-block counts
 // --------------------------------------------------------------------------
+// Tiles of the report's size with 2^30 bunches or more are refused whole, also where the run
+// works in smaller ones.  One of a refused tile's steps has 2^25 or more, so a workgroup
+// looks at the lengths of its steps and of their neighbours; only where one is that long are
+// the tiles counted.  Called by a whole workgroup of kHeavySteps threads (the wave that works
+// on a tile would have to wait for its neighbours' lengths; here it takes no time beside the
+// first workgroup's).
+__device__ __forceinline__ void mark_heavy(const Args& a, int64_t block)
+{
+    constexpr int kTile = 32;
+    const int64_t i = block * kHeavySteps + threadIdx.x;
+    // (a count is at most k_ft L / bunch_size + 1)
+    const double most = ((double)(1 << 25) - 2.0) * a.bunch_size;
+    auto may = [&](int64_t j) {
+        const double N = j >= 0 && j < a.n ? a.k_ft * a.len[j] : 0.0;
+        return N >= most && isfinite(N) ? 1 : 0;
+    };
+    int any = may(i);
+    if (threadIdx.x < kTile) any |= may(i - kTile) | may(i + kHeavySteps);
+    any = __syncthreads_or(any);
+    if (threadIdx.x == 0) a.heavy[block] = any;
+    if (!any || i >= a.n) return;
+    int s = 0;
+    for (int hi = a.n_showers; hi - s > 1;) {
+        const int mid = (s + hi) >> 1;
+        if (a.seg_offsets[mid] <= i) s = mid; else hi = mid;
+    }
+    // the step's tile (kept inside the arrays: the offsets are not validated yet)
+    int64_t first = max(a.seg_offsets[s], (int64_t)0), end = min(a.seg_offsets[s + 1], a.n);
+    if (s == a.cur_shower) first = max(first, a.cur_step);
+    int64_t nb = 0;
+    if (i >= first && i < end) {
+        first += (i - first) / kTile * kTile;
+        for (int64_t j = first; j < min(first + kTile, end); ++j) {
+            Setup st;
+            step_setup(a, j, st);
+            if (st.status < 0) nb += st.nb;
+        }
+    }
+    a.heavy_step[i] = nb >= ((int64_t)1 << 30) ? 1 : 0;
+}
+
 __global__ void __launch_bounds__(1024) init_kernel(Args a)
 {
+    if (blockIdx.x > 0) {
+        mark_heavy(a, (int64_t)blockIdx.x - 1);
+        return;
+    }
     __shared__ int64_t sh_t[1024], sh_b[1024];
     __shared__ unsigned long long report;
     __shared__ int err;
@@ -3868,6 +3920,8 @@ Args make_args(const RunPlan& p)
     a.key1 = (uint32_t)(p.params.seed >> 32);
     a.tile_segs = p.tile_segs;
     a.report_segs = p.report_segs;
+    a.heavy = p.heavy;
+    a.heavy_step = p.heavy_step;
     a.cur_step = p.cursor.step;
     a.cur_shower = p.cursor.shower;
     a.ctrl = p.ctrl;
@@ -4034,7 +4088,8 @@ int launch_run(RunPlan& p)
                           ? 0
                           : (int32_t)std::min<int64_t>((int64_t)p.emit_grid * waves,
                                                        std::min(a.stage_blocks, p.run_cap / kRunBlock));
-    init_kernel<<<1, 1024, 0, st>>>(a);
+    const int64_t heavy_blocks = p.heavy ? (p.segs.n + kHeavySteps - 1) / kHeavySteps : 0;
+    init_kernel<<<1 + (int)heavy_blocks, kHeavySteps, 0, st>>>(a);
     if (int rc = check_launch("init")) return rc;
     if (p.prof_bins > 0) {
         // the profile accumulates by atomics: clear it (a kernel, so the run stays capturable)
