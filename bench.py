@@ -143,8 +143,8 @@ def _elapsed_ms(hip, a, b) -> float:
 
 
 def kernel_source_hash() -> str:
-    from paper_2006_14927_amd.build import source_hash
-    return source_hash()
+    from paper_2006_14927_amd.build import built_hash
+    return built_hash()
 
 
 ZENITH_SAMPLE_STRIDE = 250       # every 250th step of each 5e7-step shower is certified

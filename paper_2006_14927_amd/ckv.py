@@ -89,15 +89,15 @@ _lib = None
 
 def lib():
     """The loaded library; raises CkvError if it was not built, or was built from
-    other sources than the ones beside it."""
+    other sources or with other flags than the ones beside it."""
     global _lib
     if _lib is None:
         if not os.path.exists(LIB_PATH):
             raise CkvError(f"{LIB_PATH} is missing: build it with __graft_entry__.build()")
         from . import build as _build
-        have, want = _build.built_hash(), _build.source_hash()
+        have, want = _build.built_hash(), _build.wanted_hash()
         if have != want:
-            raise CkvError(f"{LIB_PATH} was built from other sources (built {have}, sources {want}): "
+            raise CkvError(f"{LIB_PATH} was built from other sources or flags (built {have}, now {want}): "
                            "rebuild it with __graft_entry__.build()")
         L = C.CDLL(LIB_PATH)
         P, I32, I64, D = C.c_void_p, C.c_int32, C.c_int64, C.c_double
