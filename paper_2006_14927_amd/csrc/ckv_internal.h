@@ -116,7 +116,6 @@ struct ckv_grid {
     // per cell, packed: {offset into cell_list, count | first listed sphere << 16},
     // so a bunch learns its first candidate with the one load that finds its cell
     std::vector<uint32_t> cell_ent;  // 2 x kGridLevels*nx*ny
-    int32_t* d_cell_off = nullptr;
     uint16_t* d_cell_list = nullptr;
     uint32_t* d_cell_ent = nullptr;
 };
@@ -180,7 +179,8 @@ constexpr int kReachLevels = 14;     // up to 8.7 km
 constexpr double kReachMin = 96.0;
 constexpr int kReachPad = 4;
 // a step tests up to this many spheres one by one (16 double rounds of the wave) sooner
-// than it looks its ground point up (two dependent reads) and tests the 4-12 near it
+// than it looks its ground point up (three dependent reads) and tests those near it (4-12 of
+// 100 at 20 degrees)
 constexpr int kReachMinTel = 32;
 constexpr double kSoftZCut = 40.0;   // Phi(-40) underflows to exactly 0 in FP64
 // margin of the soft response's screening spheres over the cut radius [m]

@@ -66,7 +66,6 @@ struct Args {
     const double* tel;          // X, Y, R, R^2
     double gx0, gy0, inv_cell;
     int32_t nx, ny, level_cells;
-    const int32_t* cell_off;
     const uint16_t* cell_list;
     const uint2* cell_ent;      // per cell: {offset, count | first sphere << 16}
     // parameters
@@ -141,7 +140,6 @@ struct Args {
 typedef float f32x4 __attribute__((ext_vector_type(4)));
 using LdsF64 = __attribute__((address_space(3))) double;
 using HbmF64 = __attribute__((address_space(1))) double;
-using LdsF32x4 = __attribute__((address_space(3))) f32x4;
 using HbmF32x4 = __attribute__((address_space(1))) f32x4;
 
 // The launch's argument block at the address the kernel passes to a called function:
@@ -155,7 +153,6 @@ __device__ __forceinline__ const Args& args_from(uint64_t at)
 
 __device__ __forceinline__ const LdsF64* as_lds(const double* p) { return (const LdsF64*)p; }
 __device__ __forceinline__ const HbmF64* as_hbm(const double* p) { return (const HbmF64*)p; }
-__device__ __forceinline__ const LdsF32x4* as_lds4(const float* p) { return (const LdsF32x4*)p; }
 __device__ __forceinline__ const HbmF32x4* as_hbm4(const float* p) { return (const HbmF32x4*)p; }
 
 __device__ __forceinline__ void lds_add(double* p, double v)
@@ -223,19 +220,6 @@ __device__ __forceinline__ int64_t wave_incl_scan(int64_t x)
     x += dpp_take<0x118, 0xf>(x);   // row_shr:8
     x += dpp_take<0x142, 0xa>(x);   // row_bcast:15
     x += dpp_take<0x143, 0xc>(x);   // row_bcast:31
-    return x;
-}
-
-// The same by lane shuffles (LDS round trips, fewer registers): the mixed
-// kernel's called tile setup, where the DPP form's registers cost the bunch loop.
-__device__ __forceinline__ int64_t wave_incl_scan_shfl(int64_t x)
-{
-    const int lane = lane_id();
-#pragma unroll
-    for (int d = 1; d < kWave; d <<= 1) {
-        int64_t y = __shfl_up(x, d);
-        if (lane >= d) x += y;
-    }
     return x;
 }
 
@@ -747,10 +731,11 @@ constexpr int kSearchPerChunk = 5;
 constexpr int kQueue = 2 * kWave;
 constexpr int kPairs = 2 * kWave;      // (step, sphere) pairs of the tile setup, same room
 
-// The largest atmosphere table the library takes: as much as the bunch kernel's LDS
-// would hold beside one wave's area with the table staged there whole (with the profile
-// or the screening pass, its lowest 1536 entries), or, for FP64 runs that ask for 16
-// waves, those entries beside 16 waves' areas.
+// The largest atmosphere table the library takes, the same whatever a kernel keeps in LDS
+// (the bunch kernel leaves the table in global memory, so it needs none of this room): as
+// much as 160 KB hold beside the sphere table and one wave's area of 148 (FP64) or 128 bytes
+// a step (with the profile or the screening pass, the table's lowest 1536 entries count), or,
+// for FP64 runs that ask for 16 waves, those entries beside 16 such areas.
 constexpr int kTableLimitEntries = 1536;
 
 __host__ __device__ inline size_t table_bytes(int prec, int n_nodes, bool part)
@@ -3059,7 +3044,6 @@ struct SoftArgs {
     double* g_P;
     double gx0, gy0, inv_cell;
     int32_t nx, ny, level_cells;
-    const int32_t* cell_off;
     const uint16_t* cell_list;
     const uint2* cell_ent;      // per cell: {offset, count | first sphere << 16}
     // list of the bunches with a nonzero weight: written by the forward, read by the
@@ -3897,7 +3881,6 @@ Args make_args(const RunPlan& p)
         a.tel = ar->d_tel;
         a.gx0 = ar->hit.gx0; a.gy0 = ar->hit.gy0; a.inv_cell = ar->hit.inv_cell;
         a.nx = ar->hit.nx; a.ny = ar->hit.ny; a.level_cells = ar->hit.level_cells;
-        a.cell_off = ar->hit.d_cell_off;
         a.cell_list = ar->hit.d_cell_list;
         a.cell_ent = reinterpret_cast<const uint2*>(ar->hit.d_cell_ent);
         const ckv_reach& rg = ar->reach;
@@ -3995,7 +3978,7 @@ int emit_config(int precision, int n_tel, int prof_bins, const ckv_atmo* atmo, i
                 return CKV_OK;
             }
         }
-    set_error("atmosphere table too large for LDS");
+    set_error("atmosphere table beyond the largest that the library takes");
     return CKV_ERR_TABLE;
 }
 
@@ -4163,7 +4146,6 @@ int launch_soft(RunPlan& p, const SoftPlan& sp, int mode)
     s.nx = ar->soft.nx;
     s.ny = ar->soft.ny;
     s.level_cells = ar->soft.level_cells;
-    s.cell_off = ar->soft.d_cell_off;
     s.cell_list = ar->soft.d_cell_list;
     s.cell_ent = reinterpret_cast<const uint2*>(ar->soft.d_cell_ent);
     s.ids = sp.ids;
@@ -4193,7 +4175,6 @@ int launch_soft(RunPlan& p, const SoftPlan& sp, int mode)
         e.nx = ar->soft.nx;
         e.ny = ar->soft.ny;
         e.level_cells = ar->soft.level_cells;
-        e.cell_off = ar->soft.d_cell_off;
         e.cell_list = ar->soft.d_cell_list;
         e.cell_ent = reinterpret_cast<const uint2*>(ar->soft.d_cell_ent);
         set_sectors(e, p.atmo, ar->screen_rmax, ar->dmax);
@@ -4210,7 +4191,7 @@ int launch_soft(RunPlan& p, const SoftPlan& sp, int mode)
                     e_lds = tel_bytes(e.n_tel) + (size_t)wv * per;
                 }
         if (!e_waves || e.n_nodes - 1 < 2) {
-            set_error("soft response: tables too large for the screening pass");
+            set_error("soft response: atmosphere table beyond the largest that the screening pass takes");
             return CKV_ERR_TABLE;
         }
     }
