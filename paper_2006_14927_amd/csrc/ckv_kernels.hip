@@ -76,10 +76,6 @@ struct Args {
     uint32_t key0, key1;
     int32_t tile_segs;
     int32_t report_segs;        // tile size of the report and of a cut (a multiple of it)
-    // smaller tiles only: per kHeavySteps steps, whether a step of theirs may be in a refused
-    // tile of the report's size, and per step of those, whether it is (else NULL)
-    int32_t* heavy;
-    uint8_t* heavy_step;
     // first step of the run (a resume cursor; step 0 of shower 0 without one)
     int64_t cur_step;
     int32_t cur_shower;
@@ -131,6 +127,10 @@ struct Args {
     int32_t span_tiles;         // tiles of a unit whose bunches a wave takes together
     int32_t grid_waves;         // waves of the bunch kernel's launch
     int32_t static_blocks;      // staging and run blocks dealt to them beforehand
+    // smaller tiles only: per kHeavySteps steps, whether a step of theirs may be in a refused
+    // tile of the report's size, and per step of those, whether it is (else NULL)
+    int32_t* heavy;
+    uint8_t* heavy_step;
 };
 
 // Memory accesses whose address space is explicit.  Where one access may go to LDS
@@ -645,12 +645,16 @@ __device__ __forceinline__ int propagate_curved(const Args& a, double xe, double
 // The two slow propagations as called functions: their loops over the cells then keep
 // their constants in scalar registers of their own (inline, the bunch kernel's spilled
 // ones came back by lane reads in every cell: 24 % more instructions).
+// They start on an instruction cache line: elsewhere, where code before them puts their
+// loops, the same instructions take up to 8 % longer (1e5 steps at 70 degrees 427-461 us
+// by where, 435 on a line).
+#define CKV_LINE __attribute__((aligned(64)))
 struct SlowRay {
     int status;
     double xg, yg, T, uo, vo;    // uo, vo: curved; flat: uo holds n_e
 };
 
-static __device__ __noinline__ SlowRay propagate_curved_call(uint64_t args_at, double xe, double ye, double ze, double he,
+static __device__ __noinline__ CKV_LINE SlowRay propagate_curved_call(uint64_t args_at, double xe, double ye, double ze, double he,
                                                              double u, double v, double w)
 {
     SlowRay r;
@@ -658,7 +662,7 @@ static __device__ __noinline__ SlowRay propagate_curved_call(uint64_t args_at, d
     return r;
 }
 
-static __device__ __noinline__ SlowRay propagate_exact_call(uint64_t args_at, double xe, double ye, double he, double u,
+static __device__ __noinline__ CKV_LINE SlowRay propagate_exact_call(uint64_t args_at, double xe, double ye, double he, double u,
                                                             double v, double w)
 {
     SlowRay r;
@@ -1494,7 +1498,7 @@ __device__ __forceinline__ TileSetup tile_setup_at(uint64_t args_at, int64_t t0,
 // As a called function, for the builds that keep loop invariants in registers
 // (kFeatExact, kFeatCurved): the step setup's then take no room in the bunch loop.
 template <int PREC, int TS, int FEAT>
-__device__ __noinline__ TileSetup tile_setup_call(uint64_t args_at, int64_t t0, int h_first, int h_all, int lane,
+__device__ __noinline__ CKV_LINE TileSetup tile_setup_call(uint64_t args_at, int64_t t0, int h_first, int h_all, int lane,
                                                   uint32_t area_at, uint32_t tel_at)
 {
     return tile_setup_at<PREC, TS, FEAT>(args_at, t0, h_first, h_all, lane, area_at, tel_at);

@@ -1,7 +1,9 @@
-"""Registers of the built bunch kernels (CPU: the code object's own notes).
+"""Registers and placement of the built bunch kernels (CPU: the code objects' own notes and
+symbols).
 
 The plain bunch kernels hold their state in the 128 vector registers that 16 waves leave
-a lane: no scratch, no spilled vector register."""
+a lane: no scratch, no spilled vector register.  The functions that walk a ray through the
+cells start on an instruction cache line."""
 import os
 import shutil
 import subprocess
@@ -14,14 +16,19 @@ LLVM = "/opt/rocm/llvm/bin"
 
 
 @pytest.fixture(scope="module")
-def notes(tmp_path_factory):
+def code_objects(tmp_path_factory):
     if not os.path.exists(ckv.LIB_PATH) or not os.path.exists(f"{LLVM}/llvm-objdump"):
         pytest.skip("needs the built library and llvm-objdump")
     d = tmp_path_factory.mktemp("co")
     shutil.copy(ckv.LIB_PATH, d / "lib.so")
     subprocess.run([f"{LLVM}/llvm-objdump", "--offloading", "lib.so"], cwd=d, check=True, capture_output=True)
+    return sorted(d.glob("lib.so.*gfx950"))
+
+
+@pytest.fixture(scope="module")
+def notes(code_objects):
     kernels, cur = {}, {}
-    for f in sorted(d.glob("lib.so.*gfx950")):
+    for f in code_objects:
         text = subprocess.run([f"{LLVM}/llvm-readelf", "--notes", str(f)], check=True, capture_output=True,
                               text=True).stdout
         for line in text.splitlines():
@@ -42,3 +49,14 @@ def test_plain_bunch_kernels_use_no_scratch(notes, precision, tile, profile):
     assert int(k[".private_segment_fixed_size"]) == 0
     assert int(k[".vgpr_spill_count"]) == 0
     assert int(k[".vgpr_count"]) <= 128
+
+
+def test_ray_walks_start_on_a_cache_line(code_objects):
+    found = {}
+    for f in code_objects:
+        text = subprocess.run([f"{LLVM}/llvm-readelf", "-s", str(f)], check=True, capture_output=True, text=True).stdout
+        for line in text.splitlines():
+            if " FUNC " in line and ("propagate_curved_call" in line or "propagate_exact_call" in line):
+                found[f.name, line.split()[-1]] = int(line.split()[1], 16)
+    assert len(found) >= 2
+    assert all(at % 64 == 0 for at in found.values()), found
