@@ -126,6 +126,7 @@ struct Args {
     int64_t* claims;            // claim counters, kClaimStride apart
     int32_t span_tiles;         // tiles of a unit whose bunches a wave takes together
     int32_t grid_waves;         // waves of the bunch kernel's launch
+    int32_t head_units;         // units of 32 steps at its start (0 or grid_waves)
     int32_t static_blocks;      // staging and run blocks dealt to them beforehand
     // smaller tiles only: per kHeavySteps steps, whether a step of theirs may be in a refused
     // tile of the report's size, and per step of those, whether it is (else NULL)
@@ -725,6 +726,9 @@ struct alignas(16) StepPass {
     int32_t sidx;
     uint32_t hi0, lo0;
 };
+
+// Crossings a step that a run's first units are given room for in the staging area.
+constexpr int kDenseHits = 14;
 
 // Candidate rounds of the sector search that are worth it: for a unit, and for each chunk
 // of 64 bunches in it.
@@ -1521,18 +1525,22 @@ __device__ __forceinline__ void flush_list(const Args& a, const uint64_t* buf, i
 }
 
 // Tiles are worked on in units that a wave sets up together: 64 steps' worth of tiles, then
-// the last two rounds of the grid's waves tile by tile, so that the launch ends evenly.
+// the last two rounds of the grid's waves tile by tile, so that the launch ends evenly.  With
+// head (the waves), the first round goes in units of 32 steps and one at the end tile by tile.
 struct Units {
-    int64_t wide;      // units of kWave / tile_segs tiles
+    int64_t head, wide;      // units of 32 steps (at least a tile), then units of 64
     int64_t count;
 };
 
-__device__ __forceinline__ Units units_of(int64_t n_tiles, int grid_waves, int tile_segs)
+__device__ __forceinline__ Units units_of(int64_t n_tiles, int head, int grid_waves, int tile_segs)
 {
-    const int per = kWave / tile_segs;
-    const int64_t left = n_tiles - 2 * (int64_t)grid_waves;
-    const int64_t wide = left > 0 ? left / per : 0;
-    return Units{wide, wide + (n_tiles - wide * per)};
+    // (tiles of a unit are powers of two)
+    const int per = 6 - __builtin_ctz(tile_segs), half = max(per - 1, 0);
+    int64_t left = max(n_tiles - (head ? 1 : 2) * (int64_t)grid_waves, (int64_t)0);
+    const int64_t first = min((int64_t)head, left >> half);
+    left -= first << half;
+    const int64_t wide = left >> per;
+    return Units{first, wide, first + wide + (n_tiles - (first << half) - (wide << per))};
 }
 
 template <int PREC, int TS, int FEAT>
@@ -1698,16 +1706,19 @@ __global__ void __launch_bounds__(emit_threads(PREC, FEAT)) emit_kernel(Args a)
     const int n_cls = min(kTileClasses, (int)gridDim.x), cls = (int)blockIdx.x % n_cls;
     const int cls_groups = ((int)gridDim.x - cls + n_cls - 1) / n_cls;
     const int cls_waves = cls_groups * (int)(blockDim.x / kWave);
-    const Units units = units_of(n_tiles, a.grid_waves, TS);
+    const Units units = units_of(n_tiles, a.head_units, a.grid_waves, TS);
     int64_t unit = cls + (int64_t)n_cls * scalar64(wave * cls_groups + (int)blockIdx.x / n_cls);
     // a wave with a first unit has a staging and a run block of its own from the start (all
     // waves' first claims would queue at the counters: 50 us of a launch)
     if (unit < a.static_blocks && unit < units.count) blk = rblk = unit;
     while (unit < units.count) {
         int64_t claimed = 0;
-        const bool wide = unit < units.wide;
-        const int64_t t0 = wide ? unit * (kWave / TS) : unit + units.wide * (kWave / TS - 1);
-        const int h_all = wide ? kWave / TS : 1;
+        constexpr int kPer = kWave / TS, kHalf = kPer > 1 ? kPer / 2 : 1;
+        const int64_t at = unit - units.head;
+        const bool wide = at >= 0 && at < units.wide;
+        const int64_t t0 = at < 0 ? unit * kHalf
+                                  : units.head * kHalf + at + min(at, units.wide) * (kPer - 1);
+        const int h_all = wide ? kPer : at < 0 ? kHalf : 1;
         TileSetup ts_;
         ts_.h_end = 0;
         for (int h = 0, h_next; h < h_all; h = h_next) {
@@ -2484,7 +2495,7 @@ __global__ void __launch_bounds__(1024) init_kernel(Args a)
         a.ctrl[kFirstLost] = err ? 0 : run_t;      // no lost tile yet
         int64_t dealt = 0;
         if (!err && a.static_blocks > 0) {
-            dealt = min(units_of(run_t, a.grid_waves, a.tile_segs).count, (int64_t)a.static_blocks);
+            dealt = min(units_of(run_t, a.head_units, a.grid_waves, a.tile_segs).count, (int64_t)a.static_blocks);
         }
         a.ctrl[kBlockCounter] = dealt;
         a.ctrl[kRunCounter] = dealt;
@@ -4068,6 +4079,14 @@ int launch_run(RunPlan& p)
     set_sectors(a, p.atmo, p.arr->rmax, p.arr->dmax);
     a.span_tiles = span;
     a.grid_waves = p.emit_grid * waves;
+    // A run whose crossings pass its capacity writes the tiles before the first one that found
+    // no room in the staging area, and the waves' first units are all worked on at once: if
+    // they fill it, next to nothing is written and a resume gains as little.  4e5 steps over
+    // 400 spheres, 9.5 crossings a step, wrote 346 records of a capacity of 300 000; in units
+    // of 32 steps the 299 826 that whole tiles allow.  So the first round goes by these where
+    // the area holds less than kDenseHits a step of units of 64; with more room it goes by 64
+    // (32 there: 6e5 TeV steps 141 -> 147 us, 3e5 over the 400 spheres 301 -> 334).
+    a.head_units = (int64_t)a.stage_blocks * kStageBlock < (int64_t)a.grid_waves * kWave * kDenseHits ? a.grid_waves : 0;
     // a block per wave of the launch, as far as the workspace holds them beside the claims'
     // (a grid of whole class rounds: the waves' first tiles are then 0 .. waves - 1, each
     // block with an owner that leaves its fill)
