@@ -519,11 +519,14 @@ int run_checked(const ckv_segments* segs, const ckv_showers* showers, const ckv_
 }
 
 // A run of default tiles with few of them works in smaller ones: a tile is one wave's, and
-// the chain from its claim to its runs takes 15 us, most of it waiting.  The report, a cut,
-// a resumed run and the refusal of tiles past the bunch limit keep to the default size.  Whole runs, us, tiles of 32 / 16 / 8 / 2
-// steps: 300 steps 48 / 43 / 42; 5000 steps 67 / 60 / 57; 20 000 steps 65 / 62 / 64 (FP64
-// 91 / 76 / 83); 60 000 steps 84 / 89 / 92.  With grazing_exact every near-horizontal bunch
-// is propagated and meets several spheres, and 3000 steps take 4167 / 2566 / 1734 / 947.
+// the chain from its claim to its runs takes 15 us, most of it waiting.  The report, a cut, a
+// resumed run and the refusal of tiles past the bunch limit keep to the default size.
+// Whole runs, us, tiles of 32 / 16 / 8 steps: 300 steps 45 / 38 / 38; 5000 steps 62 / 60 / 61;
+// 20 000 steps 65 / 64 / 62 (FP64 67 / 66 / 64); 60 000 steps 78 / 75 / 85.  With grazing_exact
+// every near-horizontal bunch is propagated and meets several spheres: 3000 steps take 4071 /
+// 2549 / 2066, in tiles of 2 1012; 20 000 steps 5388 / 3362 / 2488.  (An ordinary shower, where
+// few bunches graze, gains nothing by it and loses little: 3000 steps 58 / 57 / 58 / 60, 20 000
+// steps 72 / 70 / 77.)
 // The smaller tiles' bookkeeping takes the place of run blocks that the layout holds for a
 // larger grid than the device has; without that room the tiles stay as they are.
 void refine_tiles(int64_t n_segments, int32_t n_showers, int32_t n_tel, RunPlan* plan)

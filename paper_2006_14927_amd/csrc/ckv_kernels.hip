@@ -969,7 +969,7 @@ static_assert(kPairs * sizeof(uint32_t) <= kQueue * sizeof(uint32_t), "pairs sha
 // window and 1.7 % lie in one (1.0 % cross), so 81 % of the bunches cost nothing and 98 %
 // no propagation: 3083 VALU instructions per 32-step tile against 9570 with every bunch
 // propagated; mixed kernel 1150 -> 550 us, FP64 2036 -> 580 us (2e6 steps; with the setup
-// and the chunks shared by tiles, below, 1730 instructions, 268 and 264 us); spherical
+// and the chunks shared by tiles, below, 1580 instructions, 239 and 247 us); spherical
 // shells at 70 degrees, where a propagated bunch walks 250 cells, 3608 -> 360 us (1e5
 // steps).  A bitmask of 256 sectors (2.9 m of a 120 m ring) takes any number of windows at
 // one LDS read per bunch.
