@@ -21,7 +21,7 @@ ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 
 
 @pytest.fixture(scope="module")
-def checker(tmp_path_factory):
+def lists_program(tmp_path_factory):
     out = str(tmp_path_factory.mktemp("reach") / "check")
     subprocess.run(["g++", "-std=c++17", "-O2", "-D__HIP_PLATFORM_AMD__", "-I/opt/rocm/include",
                     f"-I{ROOT}/include", f"-I{ROOT}/paper_2006_14927_amd/csrc",
@@ -32,8 +32,8 @@ def checker(tmp_path_factory):
 @pytest.mark.parametrize("n,half,cx", [(32, 500.0, 0.0), (33, 500.0, 0.0), (33, 0.001, 0.0), (100, 1000.0, 0.0),
                                        (400, 2000.0, 3e5), (1024, 3200.0, -1e4), (1024, 4.9e5, 0.0),
                                        (64, 6e5, 0.0)])
-def test_lists_hold_every_near_sphere(checker, n, half, cx):
-    r = subprocess.run([checker, str(n), repr(half), repr(cx)], capture_output=True, text=True)
+def test_lists_hold_every_near_sphere(lists_program, n, half, cx):
+    r = subprocess.run([lists_program, str(n), repr(half), repr(cx)], capture_output=True, text=True)
     assert r.returncode == 0, r.stdout + r.stderr
 
 
